@@ -405,7 +405,7 @@ typedef enum {
     QS_KIND_EXPECT = 3,      /* stand-alone <C>/norm readout */
     QS_KIND_SAMPLE = 4,      /* sampling kernels */
     QS_KIND_ELEMENTWISE = 5, /* init and stand-alone cost-layer kernels */
-    QS_KIND_REDUCE = 6,      /* small reductions of per-workgroup partials */
+    QS_KIND_REDUCE = 6,      /* reductions of per-workgroup partials; phase tables */
     QS_KIND_SMALL = 7,       /* single-workgroup kernels for states of <= 8192 amplitudes */
     QS_KIND_TURNAROUND = 8,  /* the pass where the forward sweep turns into the reverse sweep */
     QS_KIND_HISTOGRAM = 9,   /* cut-value histogram */

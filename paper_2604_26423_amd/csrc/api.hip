@@ -98,6 +98,81 @@ struct DevBuf {
     }
 };
 
+// Pinned host buffers, through which results reach the host: a kernel writes
+// them there (or a copy lands there) and the call reads them after its
+// synchronisation.  A copy into pageable memory instead costs 10 us more per
+// call, a pinned allocation 28 us and its release 170 us, so buffers go back to
+// a process-wide pool: at most kPinnedKeep of them per size stay there.  A
+// handle owns its buffer between ensure and release, and returns it only once
+// its stream has finished.
+constexpr size_t kPinnedSize[] = {(size_t)64 << 10, (size_t)1 << 20};
+constexpr int kPinnedClasses = 2, kPinnedKeep = 16;
+
+struct PinnedPool {
+    std::mutex mu;
+    std::vector<void *> spare[kPinnedClasses];
+    static PinnedPool &get()
+    {
+        static PinnedPool *p = new PinnedPool();  // never freed: outlives static destructors
+        return *p;
+    }
+};
+
+struct HostBuf {
+    void *p = nullptr;
+    int cls = -1;
+    HostBuf() = default;
+    HostBuf(const HostBuf &) = delete;
+    HostBuf &operator=(const HostBuf &) = delete;
+    ~HostBuf() { release(); }
+    // A buffer of at least need bytes, or null (too large, or none to be had):
+    // the caller then goes through pageable memory.  stream: the one whose work
+    // may still use the current buffer (after a call that failed half-way).
+    void *ensure(size_t need, hipStream_t stream)
+    {
+        if (p && need <= kPinnedSize[cls]) return p;
+        int c = 0;
+        while (c < kPinnedClasses && need > kPinnedSize[c]) ++c;
+        if (c == kPinnedClasses) return nullptr;
+        if (p) (void)hipStreamSynchronize(stream);
+        release();
+        PinnedPool &pool = PinnedPool::get();
+        {
+            std::lock_guard<std::mutex> g(pool.mu);
+            if (!pool.spare[c].empty()) {
+                p = pool.spare[c].back();
+                pool.spare[c].pop_back();
+            }
+        }
+        // (portable and mapped on every device: a pooled buffer serves any of them)
+        if (!p && hipHostMalloc(&p, kPinnedSize[c], hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+            return nullptr;
+        }
+        cls = c;
+        return p;
+    }
+    void release()
+    {
+        if (!p) return;
+        PinnedPool &pool = PinnedPool::get();
+        {
+            std::lock_guard<std::mutex> g(pool.mu);
+            try {
+                if (pool.spare[cls].size() < (size_t)kPinnedKeep) {
+                    pool.spare[cls].push_back(p);
+                    p = nullptr;
+                }
+            } catch (...) {
+            }
+        }
+        if (p) (void)hipHostFree(p);
+        p = nullptr;
+        cls = -1;
+    }
+};
+
 }  // namespace
 
 namespace qs {
@@ -120,6 +195,7 @@ struct qs_state_s {
     bool own = false;
     hipStream_t stream = nullptr;
     DevBuf partials, tmp, results, sample, shots_out, lambda, hist, xfer, tab, wts, ctab;
+    HostBuf host;
     int cut_mode = 0;     // qs_debug_set_cut_mode
     bool cut_on = false;  // this call's passes take cut tables
     bool prof = false;
@@ -318,21 +394,18 @@ std::vector<PassGeom> plan_for(qs_state s)
     return s->sym ? plan_passes_sym(s->nq, s->prec) : plan_passes(s->n, s->prec);
 }
 
-// Launch one tile kernel over a persistent grid; returns the grid (the number
-// of per-workgroup partial sums it writes).
+// Launch one tile kernel over its grid.
 qs_status launch_tiles(qs_state s, PassProg &pp, int adjoint, int turnaround, int kind, double bytes,
-                       int64_t *grid_out, const char *where)
+                       const char *where)
 {
     // adjoint: 0 = forward pass, 1 = turnaround, 2 = reverse pass
     const int64_t grid = tile_grid(s->prec, adjoint, pp);
     pp.xcd_remap = (grid % 8 == 0) ? 1 : 0;
-    pp.tab = s->tab.p;
     Launch L(s, kind, bytes);
     HIPCHK(adjoint ? launch_adjoint_pass(s->prec, pp, turnaround, grid, s->stream)
                    : launch_pass(s->prec, pp, grid, s->stream),
            where);
     L.done();
-    if (grid_out) *grid_out = grid;
     return QS_OK;
 }
 
@@ -345,14 +418,81 @@ double pass_bytes(qs_state s, const PassProg &pp)
     return b;
 }
 
-hipError_t ensure_partials(qs_state s, int64_t count)
+// Rows of partial sums (kSlots doubles each) that wait for their reduction at
+// most: 64 MiB, or one pass's rows where those are more.
+constexpr int64_t kMaxRows = (int64_t)1 << 21;
+
+hipError_t ensure_partials(qs_state s, int64_t rows)
 {
-    hipError_t e = s->partials.ensure((size_t)count * kSlots * sizeof(double));
+    hipError_t e = s->partials.ensure((size_t)rows * kSlots * sizeof(double));
     if (e != hipSuccess) return e;
-    e = s->tmp.ensure((size_t)std::max<int64_t>(reduce_tmp_doubles(count), kSlots) * sizeof(double));
-    if (e != hipSuccess) return e;
-    return s->tab.ensure(pass_table_bytes());
+    return s->tmp.ensure((size_t)std::max<int64_t>(reduce_tmp_doubles(rows), kSlots) * sizeof(double));
 }
+
+// Where a call's results go: count doubles in pinned host memory, which the
+// kernels write directly, or in device memory when they are too many.
+struct Results {
+    qs_state s;
+    double *dev = nullptr;   // the kernels' address
+    bool pinned = false;
+    int64_t count = 0;
+    explicit Results(qs_state s_) : s(s_) {}
+    qs_status prepare(int64_t n, const char *where)
+    {
+        count = n;
+        if ((dev = (double *)s->host.ensure((size_t)n * sizeof(double), s->stream))) {
+            pinned = true;
+            return QS_OK;
+        }
+        HIPCHK(s->results.ensure((size_t)n * sizeof(double)), where);
+        dev = (double *)s->results.p;
+        return QS_OK;
+    }
+    // Wait for the stream and copy out.
+    qs_status read(double *out, const char *where)
+    {
+        if (!pinned)
+            HIPCHK(hipMemcpyAsync(out, dev, (size_t)count * sizeof(double), hipMemcpyDeviceToHost, s->stream), where);
+        HIPCHK(hipStreamSynchronize(s->stream), where);
+        if (pinned) memcpy(out, dev, (size_t)count * sizeof(double));
+        return QS_OK;
+    }
+};
+
+// Partial sums of several launches, reduced together: add() gives a launch its
+// rows, flush() sums every launch's rows in a fixed order into kSlots doubles
+// of its own (slot number = order of add()).
+struct Reducer {
+    qs_state s;
+    double *out;
+    int64_t cap, rows = 0;
+    int done = 0;      // slots written by earlier flushes
+    ReduceJobs jobs{};
+    Reducer(qs_state s_, double *out_, int64_t cap_) : s(s_), out(out_), cap(cap_) {}
+    qs_status flush(const char *where)
+    {
+        if (jobs.count == 0) return QS_OK;
+        Launch L(s, QS_KIND_REDUCE, (double)rows * kSlots * 8);
+        HIPCHK(launch_reduce_jobs((const double *)s->partials.p, jobs, (double *)s->tmp.p, out + (int64_t)done * kSlots,
+                                  s->stream),
+               where);
+        L.done();
+        done += jobs.count;
+        jobs.count = 0;
+        rows = 0;
+        return QS_OK;
+    }
+    qs_status add(int64_t n, double **partials, const char *where)
+    {
+        if (jobs.count == kReduceJobs || rows + n > cap)
+            if (qs_status st = flush(where)) return st;
+        jobs.off[jobs.count] = rows;
+        jobs.rows[jobs.count++] = n;
+        *partials = (double *)s->partials.p + rows * kSlots;
+        rows += n;
+        return QS_OK;
+    }
+};
 
 // Small zero-fill kernel (kept out of hipMemsetAsync so that the work can be
 // captured into a graph).
@@ -362,17 +502,51 @@ __global__ void zero_kernel(double *p, int count)
     if (i < count) p[i] = 0.0;
 }
 
-hipError_t zero_results(qs_state s, int count)
-{
-    hipLaunchKernelGGL(zero_kernel, dim3((count + 255) / 256), dim3(256), 0, s->stream, (double *)s->results.p,
-                       count);
-    return hipGetLastError();
-}
+// One tile launch of a call.
+struct TileJob {
+    PassProg pp;
+    int kind;         // 0 = forward pass, 1 = turnaround, 2 = reverse pass
+    int prof_kind;
+    double bytes;
+    bool sums;        // writes partial sums
+};
 
-qs_status read_results(qs_state s, double *host, int count, const char *where)
+// Run total tile launches, make(i) describing launch i.  The phase tables of
+// the next kTableSlots launches are evaluated by one kernel ahead of them (one
+// launch per table cost 4 us each, 20 of them at n = 20, p = 10); the stream's
+// order keeps a slot's previous readers ahead of its next table.
+template <typename F>
+qs_status run_tiles(qs_state s, int64_t total, Reducer *red, F &&make, const char *where)
 {
-    HIPCHK(hipMemcpyAsync(host, s->results.p, count * sizeof(double), hipMemcpyDeviceToHost, s->stream), where);
-    HIPCHK(hipStreamSynchronize(s->stream), where);
+    HIPCHK(s->tab.ensure(pass_table_bytes() * kTableSlots), where);
+    std::vector<TileJob> jobs;
+    for (int64_t i0 = 0; i0 < total; i0 += kTableSlots) {
+        jobs.clear();
+        const int64_t i1 = std::min<int64_t>(total, i0 + kTableSlots);
+        TableArgs ta{};
+        for (int64_t i = i0; i < i1; ++i) {
+            jobs.push_back(make(i));
+            PassProg &pp = jobs.back().pp;
+            if (!pp.has_phase) continue;
+            pp.tab = (char *)s->tab.p + pass_table_bytes() * (size_t)ta.count;
+            ta.theta[ta.count] = pp.theta_zz;
+            ta.f[ta.count] = table_factor(s->prec, pp, jobs.back().kind);
+            ta.levels = pp.phase_levels;
+            ta.W = pp.W;
+            ++ta.count;
+        }
+        if (ta.count) {
+            Launch L(s, QS_KIND_REDUCE, (double)ta.count * pass_table_bytes());
+            HIPCHK(launch_phase_tables(s->prec, ta, s->tab.p, s->stream), where);
+            L.done();
+        }
+        for (TileJob &j : jobs) {
+            const int64_t grid = tile_grid(s->prec, j.kind, j.pp);
+            if (j.sums)
+                if (qs_status st = red->add(grid, &j.pp.partials, where)) return st;
+            if (qs_status st = launch_tiles(s, j.pp, j.kind, j.kind == 1, j.prof_kind, j.bytes, where)) return st;
+        }
+    }
     return QS_OK;
 }
 
@@ -401,7 +575,7 @@ qs_status check_diag(qs_state s, const int32_t *diag, int64_t W)
 }
 
 // ---------------------------------------------------------------- forward
-qs_status run_small_forward(qs_state s, const Circuit &cc, bool readout, const char *where)
+qs_status run_small_forward(qs_state s, const Circuit &cc, double *readout, const char *where)
 {
     // chunks of kSmallMaxLayers layers; readout in the last chunk
     int k0 = 0;
@@ -410,7 +584,7 @@ qs_status run_small_forward(qs_state s, const Circuit &cc, bool readout, const c
         SmallProg sp{};
         sp.psi = s->psi;
         sp.diag = cc.diag;
-        sp.out = (double *)s->results.p;
+        sp.out = readout;
         sp.n = s->n;
         sp.init = first ? 1 : 0;
         sp.nlayers = std::min(kSmallMaxLayers, cc.p - k0);
@@ -432,69 +606,61 @@ qs_status run_small_forward(qs_state s, const Circuit &cc, bool readout, const c
     return QS_OK;
 }
 
-qs_status run_reduce(qs_state s, int64_t count, const int *map, int accumulate, const char *where)
+// <C> and the norm of the state: out[0] = norm, out[1] = sum |a|^2 C_t.
+qs_status run_expect(qs_state s, const int32_t *diag, double *out, const char *where)
 {
-    Launch L(s, QS_KIND_REDUCE, (double)count * kSlots * 8);
-    HIPCHK(launch_reduce((const double *)s->partials.p, count, (double *)s->tmp.p, (double *)s->results.p, map,
-                         accumulate, s->stream),
-           where);
+    HIPCHK(ensure_partials(s, 16384), where);
+    int64_t nb = 0;
+    Launch L(s, QS_KIND_EXPECT, ldexp(1.0, s->n) * (amp_bytes(s->prec) + 4));
+    HIPCHK(launch_expect(s->prec, s->psi, diag, s->n, (double *)s->partials.p, &nb, s->stream), where);
     L.done();
-    return QS_OK;
+    Reducer red(s, out, nb);
+    double *rows = nullptr;
+    if (qs_status st = red.add(nb, &rows, where)) return st;
+    return red.flush(where);
 }
 
-// Fused forward circuit.  With readout, results[0] = norm, results[1] = sum |a|^2 C_t.
-qs_status run_forward(qs_state s, const Circuit &cc, bool readout, const char *where)
+// Fused forward circuit.  With readout (kSlots doubles that the kernels can
+// write): readout[0] = norm, readout[1] = sum |a|^2 C_t.
+qs_status run_forward(qs_state s, const Circuit &cc, double *readout, const char *where)
 {
     const int T = tile_bits(s->prec);
-    HIPCHK(s->results.ensure(64 * sizeof(double)), where);
     if (cc.p == 0) {
         Launch L(s, QS_KIND_ELEMENTWISE, ldexp(1.0, s->n) * amp_bytes(s->prec));
         HIPCHK(launch_init_plus(s->prec, s->psi, s->n, s->nq, s->stream), where);
         L.done();
-        if (readout) {
-            int64_t nb = 0;
-            HIPCHK(ensure_partials(s, 16384), where);
-            Launch E(s, QS_KIND_EXPECT, ldexp(1.0, s->n) * (amp_bytes(s->prec) + 4));
-            HIPCHK(launch_expect(s->prec, s->psi, cc.diag, s->n, (double *)s->partials.p, &nb, s->stream), where);
-            E.done();
-            const int map[kSlots] = {0, 1, -1, -1};
-            return run_reduce(s, nb, map, 0, where);
-        }
-        return QS_OK;
+        return readout ? run_expect(s, cc.diag, readout, where) : QS_OK;
     }
     if (s->n <= T) return run_small_forward(s, cc, readout, where);
 
     const std::vector<PassGeom> geo = plan_for(s);
     std::vector<KSpec> ks = forward_specs((int)geo.size(), cc.p, !s->sym);
     if (readout) ks.back().readout = 1;
-    HIPCHK(ensure_partials(s, pass_grid(s->prec, 0, (int64_t)1 << (s->n - T))), where);
+    const int64_t rows = pass_grid(s->prec, 0, (int64_t)1 << (s->n - T));
+    if (readout) HIPCHK(ensure_partials(s, rows), where);
     if (qs_status st = prepare_cut(s, cc, where)) return st;
-    int64_t grid = 0;
-    for (const KSpec &k : ks) {
+    Reducer red(s, readout, rows);
+    auto make = [&](int64_t i) {
+        const KSpec &k = ks[(size_t)i];
         PassProg pp = make_prog(s, geo[k.pass], k, cc, kFwdThreadBits);
-        if (qs_status st = launch_tiles(s, pp, 0, 0, pp.has_phase ? QS_KIND_PASS_PHASE : QS_KIND_PASS,
-                                        pass_bytes(s, pp), &grid, where))
-            return st;
-    }
-    if (readout) {
-        const int map[kSlots] = {0, 1, -1, -1};
-        return run_reduce(s, grid, map, 0, where);
-    }
-    return QS_OK;
+        return TileJob{pp, 0, pp.has_phase ? QS_KIND_PASS_PHASE : QS_KIND_PASS, pass_bytes(s, pp), pp.readout != 0};
+    };
+    if (qs_status st = run_tiles(s, (int64_t)ks.size(), &red, make, where)) return st;
+    return red.flush(where);
 }
 
 // ---------------------------------------------------------------- adjoint
 // results layout: [0] norm, [1] sum |a|^2 C_t, [2 + k] dE/dtheta_zz[k], [2 + p + k] dE/dtheta_x[k]
-qs_status run_small_adjoint(qs_state s, const Circuit &cc, void *lam, const char *where)
+qs_status run_small_adjoint(qs_state s, const Circuit &cc, void *lam, double *out, const char *where)
 {
-    if (qs_status st = run_small_forward(s, cc, false, where)) return st;
+    if (qs_status st = run_small_forward(s, cc, nullptr, where)) return st;
     const int nch = (cc.p + kSmallMaxLayers - 1) / kSmallMaxLayers;
     for (int ch = nch - 1; ch >= 0; --ch) {
         SmallProg sp{};
         sp.psi = s->psi;
         sp.lam = lam;
         sp.diag = cc.diag;
-        sp.out = (double *)s->results.p;
+        sp.out = out;
         sp.n = s->n;
         sp.layer0 = ch * kSmallMaxLayers;
         sp.nlayers = std::min(kSmallMaxLayers, cc.p - sp.layer0);
@@ -538,69 +704,83 @@ int64_t ckpt_states(qs_state s, int p)
 // Otherwise store: the forward writes the output of pass i to checkpoint i
 // (ckpt + i states, the state buffer for i = P-2) and reverse pass i reads
 // psi from checkpoint i and stores lambda only.
-qs_status run_adjoint(qs_state s, const Circuit &cc, void *lam, const char *where, void *ckpt = nullptr)
+qs_status run_adjoint(qs_state s, const Circuit &cc, void *lam, double *r, const char *where, void *ckpt = nullptr)
 {
     const int T = tile_bits(s->prec);
-    const int nres = 2 + 2 * cc.p;
-    HIPCHK(s->results.ensure((size_t)std::max(64, nres) * sizeof(double)), where);
-    HIPCHK(zero_results(s, nres), where);
-    if (s->n <= T) return run_small_adjoint(s, cc, lam, where);
+    Results res(s);
+    if (s->n <= T) {
+        if (qs_status st = res.prepare(2 + 2 * (int64_t)cc.p, where)) return st;
+        if (qs_status st = run_small_adjoint(s, cc, lam, res.dev, where)) return st;
+        return res.read(r, where);
+    }
 
     const std::vector<PassGeom> geo = plan_for(s);
     const std::vector<KSpec> ks = forward_specs((int)geo.size(), cc.p, !s->sym);
+    const int P = (int)ks.size();
     const int64_t ntiles = (int64_t)1 << (s->n - T);
-    HIPCHK(ensure_partials(s, ntiles), where);  // no tile kernel has more workgroups than tiles
+    // no tile kernel has more workgroups than tiles; P launches write sums
+    const int64_t cap = std::max(ntiles, std::min<int64_t>(kMaxRows, ntiles * P));
+    HIPCHK(ensure_partials(s, cap), where);
+    if (qs_status st = res.prepare((int64_t)P * kSlots, where)) return st;
     if (qs_status st = prepare_cut(s, cc, where)) return st;
     const double dim = ldexp(1.0, s->n), ab = (double)amp_bytes(s->prec);
-
-    int64_t grid = 0;
-
-    const int P = (int)ks.size();
     const size_t sb = qs_state_bytes(s->n, s->prec);
     auto ck = [&](int i) -> void * { return i == P - 2 ? s->psi : (void *)((char *)ckpt + (size_t)i * sb); };
-
-    // forward, all but the last pass
-    for (int i = 0; i + 1 < P; ++i) {
-        PassProg pp = make_prog(s, geo[ks[i].pass], ks[i], cc, kFwdThreadBits);
-        if (ckpt) {
-            if (i > 0) pp.psi = ck(i - 1);
-            pp.psi_out = ck(i);
+    // one-tile kernels run 256 threads (5-bit windows), the persistent
+    // kernel 512; the complement-symmetric layout keeps 512 threads (256
+    // measured no faster there)
+    auto adjoint_prog = [&](const KSpec &k, int kind) {
+        PassProg pp = make_prog(s, geo[k.pass], k, cc, kAdjOneThreadBits, kind);
+        if (s->sym || !adjoint_one_tile(s->prec, pp, kind == 1))
+            pp = make_prog(s, geo[k.pass], k, cc, kAdjThreadBits, kind);
+        pp.lam = lam;
+        return pp;
+    };
+    // Launches: forward passes 0 .. P-2, the turnaround (the last pass
+    // forward, lambda = C psi, the pass undone), reverse passes P-2 .. 0.
+    auto make = [&](int64_t j) {
+        if (j < P - 1) {
+            const int i = (int)j;
+            PassProg pp = make_prog(s, geo[ks[i].pass], ks[i], cc, kFwdThreadBits);
+            if (ckpt) {
+                if (i > 0) pp.psi = ck(i - 1);
+                pp.psi_out = ck(i);
+            }
+            return TileJob{pp, 0, pp.has_phase ? QS_KIND_PASS_PHASE : QS_KIND_PASS, pass_bytes(s, pp), false};
         }
-        if (qs_status st = launch_tiles(s, pp, 0, 0, pp.has_phase ? QS_KIND_PASS_PHASE : QS_KIND_PASS,
-                                        pass_bytes(s, pp), &grid, where))
-            return st;
-    }
-    // turnaround: the last pass forward, lambda = C psi, the pass undone
-    {
-        const KSpec &k = ks.back();
-        // one-tile kernels run 256 threads (5-bit windows), the persistent
-        // kernel 512; the complement-symmetric layout keeps 512 threads (256
-        // measured no faster there)
-        PassProg pp = make_prog(s, geo[k.pass], k, cc, kAdjOneThreadBits, 1);
-        if (s->sym || !adjoint_one_tile(s->prec, pp, 1)) pp = make_prog(s, geo[k.pass], k, cc, kAdjThreadBits, 1);
-        pp.lam = lam;
-        if (qs_status st = launch_tiles(s, pp, 1, 1, QS_KIND_TURNAROUND, dim * (2.0 * ab + (pp.ctab ? 0.0 : 4.0)),
-                                        &grid, where))
-            return st;
-        const int map[kSlots] = {2 + cc.p + k.post, 0, 1, -1};
-        if (qs_status st = run_reduce(s, grid, map, 1, where)) return st;
-    }
-    // reverse passes
-    for (int i = (int)ks.size() - 2; i >= 0; --i) {
-        const KSpec &k = ks[i];
-        PassProg pp = make_prog(s, geo[k.pass], k, cc, kAdjOneThreadBits, 2);
-        if (s->sym || !adjoint_one_tile(s->prec, pp, 0)) pp = make_prog(s, geo[k.pass], k, cc, kAdjThreadBits, 2);
-        pp.lam = lam;
+        if (j == P - 1) {
+            PassProg pp = adjoint_prog(ks.back(), 1);
+            return TileJob{pp, 1, QS_KIND_TURNAROUND, dim * (2.0 * ab + (pp.ctab ? 0.0 : 4.0)), true};
+        }
+        const int i = 2 * P - 2 - (int)j;
+        PassProg pp = adjoint_prog(ks[i], 2);
         pp.load_win = pp.final_win;
         if (ckpt) {
             pp.psi = ck(i);
             pp.psi_out = nullptr;
         }
         const double by = dim * ab * (pp.init ? 2.0 : ckpt ? 3.0 : 4.0) + (pp.has_phase && !pp.ctab ? dim * 4.0 : 0.0);
-        if (qs_status st = launch_tiles(s, pp, 2, 0, QS_KIND_ADJOINT, by, &grid, where)) return st;
-        const int map[kSlots] = {k.post >= 0 ? 2 + cc.p + k.post : -1, k.phase >= 0 ? 2 + k.phase : -1,
-                                 k.pre >= 0 ? 2 + cc.p + k.pre : -1, -1};
-        if (qs_status st = run_reduce(s, grid, map, 1, where)) return st;
+        return TileJob{pp, 2, QS_KIND_ADJOINT, by, true};
+    };
+    Reducer red(s, res.dev, cap);
+    if (qs_status st = run_tiles(s, 2 * (int64_t)P - 1, &red, make, where)) return st;
+    if (qs_status st = red.flush(where)) return st;
+    std::vector<double> v((size_t)P * kSlots);
+    if (qs_status st = res.read(v.data(), where)) return st;
+    // the launches' sums, in launch order
+    for (int i = 0; i < 2 + 2 * cc.p; ++i) r[i] = 0.0;
+    auto take = [&](int at, double x) {
+        if (at >= 0) r[at] += x;
+    };
+    take(2 + cc.p + ks.back().post, v[0]);
+    take(0, v[1]);
+    take(1, v[2]);
+    for (int i = P - 2; i >= 0; --i) {
+        const KSpec &k = ks[i];
+        const double *w = &v[(size_t)(P - 1 - i) * kSlots];
+        take(k.post >= 0 ? 2 + cc.p + k.post : -1, w[0]);
+        take(k.phase >= 0 ? 2 + k.phase : -1, w[1]);
+        take(k.pre >= 0 ? 2 + cc.p + k.pre : -1, w[2]);
     }
     return QS_OK;
 }
@@ -836,7 +1016,7 @@ qs_status qs_free(qs_state s)
     s->shots_out.release();
     s->xfer.release();
     s->lambda.release();
-    delete s;
+    delete s;  // (its pinned buffer goes back to the pool: the stream is idle)
     return QS_OK;
 }
 
@@ -1011,10 +1191,8 @@ qs_status qs_apply_mixer(qs_state s, double theta_x)
     const int T = tile_bits(s->prec);
     const char *where = "qs_apply_mixer";
     if (s->n <= T) {
-        HIPCHK(s->results.ensure(64 * sizeof(double)), where);
         SmallProg sp{};
         sp.psi = s->psi;
-        sp.out = (double *)s->results.p;
         sp.n = s->n;
         sp.nlayers = 1;
         sp.tx[0] = theta_x;
@@ -1025,13 +1203,12 @@ qs_status qs_apply_mixer(qs_state s, double theta_x)
         return QS_OK;
     }
     const std::vector<PassGeom> geo = plan_for(s);
-    HIPCHK(ensure_partials(s, pass_grid(s->prec, 0, (int64_t)1 << (s->n - T))), where);
     const double tx[1] = {theta_x}, tzz[1] = {0.0};
     Circuit cc{nullptr, 0, 1, tzz, tx};
     for (size_t i = 0; i < geo.size(); ++i) {
         KSpec k{(int)i, 0, -1, -1, 0, 0};
         PassProg pp = make_prog(s, geo[i], k, cc, kFwdThreadBits);
-        if (qs_status st = launch_tiles(s, pp, 0, 0, QS_KIND_PASS, pass_bytes(s, pp), nullptr, where)) return st;
+        if (qs_status st = launch_tiles(s, pp, 0, 0, QS_KIND_PASS, pass_bytes(s, pp), where)) return st;
     }
     return QS_OK;
 }
@@ -1046,10 +1223,13 @@ qs_status qs_forward(qs_state s, const int32_t *diag_dev, int64_t w_total_tenths
         if (p > 0 || readout)
             if (qs_status st = check_diag(s, diag_dev, w_total_tenths)) return st;
         Circuit cc{diag_dev, w_total_tenths, p, theta_zz, theta_x};
-        if (qs_status st = run_forward(s, cc, readout, "qs_forward")) return st;
+        Results res(s);
+        if (readout)
+            if (qs_status st = res.prepare(kSlots, "qs_forward")) return st;
+        if (qs_status st = run_forward(s, cc, res.dev, "qs_forward")) return st;
         if (readout) {
-            double r[2];
-            if (qs_status st = read_results(s, r, 2, "qs_forward")) return st;
+            double r[kSlots];
+            if (qs_status st = res.read(r, "qs_forward")) return st;
             *exp_c = (r[1] / 10.0) / r[0];
             if (norm) *norm = r[0] * (s->sym ? 2.0 : 1.0);
         }
@@ -1065,16 +1245,11 @@ qs_status qs_expect(qs_state s, const int32_t *diag_dev, double *exp_c, double *
     if (qs_status st = check_diag(s, diag_dev, 0)) return st;
     if (!exp_c) return fail(QS_ERR_ARG, "null exp_c");
     const char *where = "qs_expect";
-    HIPCHK(s->results.ensure(64 * sizeof(double)), where);
-    HIPCHK(ensure_partials(s, 16384), where);
-    int64_t nb = 0;
-    Launch L(s, QS_KIND_EXPECT, ldexp(1.0, s->n) * (amp_bytes(s->prec) + 4));
-    HIPCHK(launch_expect(s->prec, s->psi, diag_dev, s->n, (double *)s->partials.p, &nb, s->stream), where);
-    L.done();
-    const int map[kSlots] = {0, 1, -1, -1};
-    if (qs_status st = run_reduce(s, nb, map, 0, where)) return st;
-    double r[2];
-    if (qs_status st = read_results(s, r, 2, where)) return st;
+    Results res(s);
+    if (qs_status st = res.prepare(kSlots, where)) return st;
+    if (qs_status st = run_expect(s, diag_dev, res.dev, where)) return st;
+    double r[kSlots];
+    if (qs_status st = res.read(r, where)) return st;
     *exp_c = (r[1] / 10.0) / r[0];
     if (norm) *norm = r[0] * (s->sym ? 2.0 : 1.0);
     return QS_OK;
@@ -1103,7 +1278,6 @@ qs_status qs_sample(qs_state s, uint64_t seed, int64_t shots, uint64_t *out, int
         HIPCHK(s->shots_out.ensure((size_t)shots * 8), where);
         dst = (uint64_t *)s->shots_out.p;
     }
-    HIPCHK(s->results.ensure(64 * sizeof(double)), where);
     hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s->stream, (double *)b.flag, 1);
     HIPCHK(hipGetLastError(), where);
     {
@@ -1252,9 +1426,8 @@ static qs_status adjoint_entry(qs_state s, const int32_t *diag_dev, int64_t w_to
             lam = s->lambda.p;
         }
         Circuit cc{diag_dev, w_total_tenths, p, theta_zz, theta_x};
-        if (qs_status st = run_adjoint(s, cc, lam, where, ckpt)) return st;
         std::vector<double> r(2 + 2 * (size_t)p);
-        if (qs_status st = read_results(s, r.data(), (int)r.size(), where)) return st;
+        if (qs_status st = run_adjoint(s, cc, lam, r.data(), where, ckpt)) return st;
         if (!lambda_buf) s->lambda.release();
         const double nrm = r[0];
         if (exp_c) *exp_c = (r[1] / 10.0) / nrm;

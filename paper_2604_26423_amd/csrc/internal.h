@@ -56,7 +56,7 @@ struct PassProg {
                           // pass reading a checkpoint: psi is not stored)
     const int32_t *diag;  // cost diagonal in tenths
     void *tab;            // phase table of the pass's cost layer (kTabMax entries of float2 / double2),
-                          // written by the launcher's table kernel just before the pass
+                          // written before the pass (launch_phase_tables)
     int32_t *ctab;        // cut table of the pass (layout kCt* below), written by the launcher just
                           // before the pass, from which the pass evaluates C_t in registers instead of
                           // loading the diagonal; null: the pass loads the diagonal
@@ -206,6 +206,18 @@ hipError_t launch_pass(int prec, const PassProg &pp, int64_t grid, hipStream_t s
 bool adjoint_one_tile(int prec, const PassProg &pp, int turnaround);
 // Bytes of the device buffer PassProg::tab points to (any precision).
 size_t pass_table_bytes();
+// Phase tables of up to kTableSlots launches, evaluated by one kernel into
+// base + i * pass_table_bytes(): angle theta[i], real factor f[i].
+constexpr int kTableSlots = 64;
+struct TableArgs {
+    int count, levels;
+    int64_t W;
+    double theta[kTableSlots], f[kTableSlots];
+};
+hipError_t launch_phase_tables(int prec, const TableArgs &ta, void *base, hipStream_t st);
+// The real factor that the table of pass pp carries (kind 0 = forward pass,
+// 1 = turnaround, 2 = reverse pass).
+double table_factor(int prec, const PassProg &pp, int kind);
 // Recover the weights of the cut function in diag (2^n entries, full layout)
 // into wts (kWtSize int32) and check them against the diagonal.
 hipError_t launch_cut_weights(const int32_t *diag, int n, int64_t W, int32_t *wts, hipStream_t st);
@@ -325,10 +337,17 @@ hipError_t launch_cost_layer(int prec, void *psi, const int32_t *diag, int n, in
                              double theta, hipStream_t st);
 hipError_t launch_expect(int prec, const void *psi, const int32_t *diag, int n,
                          double *partials, int64_t *nblocks, hipStream_t st);
-// Fixed-order reduction of kSlots-wide partials into dst[map[k]] (+= if accumulate).
-hipError_t launch_reduce(const double *partials, int64_t count, double *tmp, double *dst,
-                         const int *map, int accumulate, hipStream_t st);
-int64_t reduce_tmp_doubles(int64_t count);
+// Fixed-order sums of several launches' partials: job j's rows (kSlots doubles
+// each) start at row off[j]; out gets kSlots doubles per job.  tmp:
+// reduce_tmp_doubles(rows of all jobs) doubles.
+constexpr int kReduceJobs = 64;
+struct ReduceJobs {
+    int count;
+    int64_t off[kReduceJobs], rows[kReduceJobs];
+};
+hipError_t launch_reduce_jobs(const double *partials, const ReduceJobs &jobs, double *tmp, double *out,
+                              hipStream_t st);
+int64_t reduce_tmp_doubles(int64_t rows);
 
 // Cost diagonal.
 // sym = 1: the 2^(n-1) entries of the complement-symmetric layout (plan.h)

@@ -41,11 +41,13 @@ __global__ void __launch_bounds__(1 << TB) pass_kernel(PassProg pp)
 
 // The phase table of a pass (see build_phase_table): the same for every
 // workgroup, so it is evaluated once, by one workgroup, into pp.tab, and each
-// workgroup of the pass copies it into LDS.
+// workgroup of the pass copies it into LDS.  Workgroup i writes table i.
 template <typename V>
-__global__ void __launch_bounds__(256) phase_table_kernel(V *tab, int levels, double theta, int64_t W, double f)
+__global__ void __launch_bounds__(256) phase_table_kernel(char *base, size_t stride, TableArgs ta)
 {
-    build_phase_table(tab, levels, theta, W, f, threadIdx.x, 256);
+    const int i = blockIdx.x;
+    build_phase_table(reinterpret_cast<V *>(base + stride * i), ta.levels, ta.theta[i], ta.W, ta.f[i], threadIdx.x,
+                      256);
 }
 
 // Weights of the cut function that a full-layout diagonal encodes, and a
@@ -507,22 +509,24 @@ int64_t tile_grid(int prec, int adjoint, const PassProg &pp)
     return adjoint_one_tile(prec, pp, adjoint == 1) ? pp.ntiles : pass_grid(prec, adjoint, pp.ntiles);
 }
 
-namespace {
-// Evaluate the table of a phase pass into pp.tab, ahead of the pass on the
-// same stream.  f: the real factor folded into the table.
-hipError_t launch_phase_table(int prec, const PassProg &pp, double f, hipStream_t st)
+hipError_t launch_phase_tables(int prec, const TableArgs &ta, void *base, hipStream_t st)
 {
-    if (!pp.has_phase) return hipSuccess;
-    if (!pp.tab) return hipErrorInvalidValue;
-    if (prec == 0)
-        hipLaunchKernelGGL(phase_table_kernel<float2>, dim3(1), dim3(256), 0, st, static_cast<float2 *>(pp.tab),
-                           pp.phase_levels, pp.theta_zz, pp.W, f);
-    else
-        hipLaunchKernelGGL(phase_table_kernel<double2>, dim3(1), dim3(256), 0, st, static_cast<double2 *>(pp.tab),
-                           pp.phase_levels, pp.theta_zz, pp.W, f);
+    if (ta.count < 1) return hipSuccess;
+    if (ta.count > kTableSlots || !base) return hipErrorInvalidValue;
+    const dim3 g((unsigned)ta.count), b(256);
+    if (prec == 0) hipLaunchKernelGGL(phase_table_kernel<float2>, g, b, 0, st, (char *)base, pass_table_bytes(), ta);
+    else hipLaunchKernelGGL(phase_table_kernel<double2>, g, b, 0, st, (char *)base, pass_table_bytes(), ta);
     return hipGetLastError();
 }
-}  // namespace
+
+// Forward passes fold their stages' tangent-form factors into the table;
+// reverse passes in tangent form too, unless they undo the first forward pass
+// (see rev_tile).
+double table_factor(int prec, const PassProg &pp, int kind)
+{
+    if (kind == 0) return pp.factor;
+    return kind == 2 && adjoint_mode(prec, pp) != kModeGeneral && !pp.init ? pp.factor : 1.0;
+}
 
 namespace {
 // The window in which a pass evaluates C_t (the layout tiles.h loads the
@@ -550,7 +554,7 @@ hipError_t launch_cut_table(int prec, const PassProg &pp, int kind, int tb, hipS
 
 hipError_t launch_pass(int prec, const PassProg &pp, int64_t grid, hipStream_t st)
 {
-    if (hipError_t e = launch_phase_table(prec, pp, pp.factor, st)) return e;
+    if (pp.has_phase && !pp.tab) return hipErrorInvalidValue;
     if (hipError_t e = launch_cut_table(prec, pp, 0, kFwdThreadBits, st)) return e;
     switch (tile_mode(pp, tile_bits(prec), kFwdThreadBits)) {
     case kModeTan: launch_pass_m<kModeTan>(prec, pp, grid, st); break;
@@ -566,10 +570,7 @@ hipError_t launch_adjoint_pass(int prec, const PassProg &pp, int turnaround, int
     if (pp.tb != kAdjThreadBits && (pp.tb != kAdjOneThreadBits || !adjoint_one_tile(prec, pp, turnaround)))
         return hipErrorInvalidValue;
     const int mode = adjoint_mode(prec, pp);
-    // reverse passes in tangent form fold the stages' factors into the table
-    // (see rev_tile)
-    const bool fold = !turnaround && mode != kModeGeneral && !pp.init;
-    if (hipError_t e = launch_phase_table(prec, pp, fold ? pp.factor : 1.0, st)) return e;
+    if (pp.has_phase && !pp.tab) return hipErrorInvalidValue;
     if (hipError_t e = launch_cut_table(prec, pp, turnaround ? 1 : 2, pp.tb, st)) return e;
     switch (mode) {
     case kModeTan: launch_adjoint_m<kModeTan>(prec, pp, turnaround, grid, st); break;

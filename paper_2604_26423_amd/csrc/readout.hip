@@ -4,6 +4,8 @@
 // <C> (arXiv:2604.26423, eq. 5 with exact probabilities): sum |a_x|^2 C(x)
 // over the normalised state.  Partial sums are FP64, combined in a fixed
 // order (no atomics), so the result is identical from run to run.
+#include <algorithm>
+
 #include "device.h"
 
 namespace qs {
@@ -12,7 +14,7 @@ namespace {
 
 constexpr int kElemThreads = 256;
 constexpr int64_t kElemMaxBlocks = 16384;
-constexpr int kReduceChunk = 4096;
+constexpr int kReduceChunk = 1024;
 
 int64_t elem_grid(int64_t dim)
 {
@@ -62,13 +64,14 @@ __global__ void __launch_bounds__(kElemThreads) expect_kernel(const V *psi, cons
     }
 }
 
-// Level 1: workgroup b sums partials [b*4096, (b+1)*4096) slot by slot.
-__global__ void __launch_bounds__(256) reduce_l1_kernel(const double *in, int64_t count, double *out)
+// The rows of a job are summed in chunks of kReduceChunk, one workgroup each,
+// and the chunks' sums by one workgroup per job: a fixed order.  A workgroup
+// reads four rows per thread, so that a job of one chunk (up to 2^10 tiles)
+// costs one launch and the time of a few loads.
+__device__ __forceinline__ void sum_rows(const double *in, int64_t lo, int64_t hi, double *red, double *out)
 {
-    __shared__ double red[kSlots * 4];
     double acc[kSlots] = {0.0, 0.0, 0.0, 0.0};
-    const int64_t lo = (int64_t)blockIdx.x * kReduceChunk;
-    const int64_t hi = lo + kReduceChunk < count ? lo + kReduceChunk : count;
+#pragma unroll 4
     for (int64_t i = lo + threadIdx.x; i < hi; i += 256) {
 #pragma unroll
         for (int k = 0; k < kSlots; ++k) acc[k] += in[i * kSlots + k];
@@ -76,30 +79,35 @@ __global__ void __launch_bounds__(256) reduce_l1_kernel(const double *in, int64_
     block_sum(acc, red, threadIdx.x, 256);
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int k = 0; k < kSlots; ++k) out[blockIdx.x * kSlots + k] = acc[k];
+        for (int k = 0; k < kSlots; ++k) out[k] = acc[k];
     }
 }
 
-struct SlotMap {
-    int m[kSlots];
-};
+__host__ __device__ __forceinline__ int64_t reduce_chunks(int64_t rows)
+{
+    return (rows + kReduceChunk - 1) / kReduceChunk;
+}
 
-// Level 2: one workgroup sums all (<= 4096) rows and writes dst[map[k]].
-__global__ void __launch_bounds__(256) reduce_l2_kernel(const double *in, int64_t count, double *dst,
-                                                        SlotMap map, int accumulate)
+// Workgroup (b, j): chunk b of job j.
+__global__ void __launch_bounds__(256) reduce_chunks_kernel(const double *in, ReduceJobs jobs, int64_t stride,
+                                                            double *tmp)
 {
     __shared__ double red[kSlots * 4];
-    double acc[kSlots] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t i = threadIdx.x; i < count; i += 256) {
-#pragma unroll
-        for (int k = 0; k < kSlots; ++k) acc[k] += in[i * kSlots + k];
-    }
-    block_sum(acc, red, threadIdx.x, 256);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < kSlots; ++k)
-            if (map.m[k] >= 0) dst[map.m[k]] = (accumulate ? dst[map.m[k]] : 0.0) + acc[k];
-    }
+    const int j = blockIdx.y;
+    const int64_t rows = jobs.rows[j], lo = (int64_t)blockIdx.x * kReduceChunk;
+    if (lo >= rows) return;
+    const int64_t hi = lo + kReduceChunk < rows ? lo + kReduceChunk : rows;
+    sum_rows(in + jobs.off[j] * kSlots, lo, hi, red, tmp + (j * stride + blockIdx.x) * kSlots);
+}
+
+// Workgroup j: job j, from its rows (stride 0) or from its chunks' sums.
+__global__ void __launch_bounds__(256) reduce_jobs_kernel(const double *in, ReduceJobs jobs, int64_t stride,
+                                                          double *out)
+{
+    __shared__ double red[kSlots * 4];
+    const int j = blockIdx.x;
+    if (stride) sum_rows(in + j * stride * kSlots, 0, reduce_chunks(jobs.rows[j]), red, out + j * kSlots);
+    else sum_rows(in + jobs.off[j] * kSlots, 0, jobs.rows[j], red, out + j * kSlots);
 }
 
 }  // namespace
@@ -177,25 +185,26 @@ hipError_t launch_expect(int prec, const void *psi, const int32_t *diag, int n, 
     return hipGetLastError();
 }
 
-int64_t reduce_tmp_doubles(int64_t count)
+int64_t reduce_tmp_doubles(int64_t rows)
 {
-    return ((count + kReduceChunk - 1) / kReduceChunk) * kSlots;
+    // every job has at most kReduceJobs times the chunks of the longest
+    return kReduceJobs * (reduce_chunks(rows) + 1) * kSlots;
 }
 
-hipError_t launch_reduce(const double *partials, int64_t count, double *tmp, double *dst, const int *map,
-                         int accumulate, hipStream_t st)
+hipError_t launch_reduce_jobs(const double *partials, const ReduceJobs &jobs, double *tmp, double *out,
+                              hipStream_t st)
 {
-    SlotMap sm;
-    for (int k = 0; k < kSlots; ++k) sm.m[k] = map[k];
-    if (count <= kReduceChunk) {
-        hipLaunchKernelGGL(reduce_l2_kernel, dim3(1), dim3(256), 0, st, partials, count, dst, sm, accumulate);
-        return hipGetLastError();
+    if (jobs.count < 1 || jobs.count > kReduceJobs) return hipErrorInvalidValue;
+    int64_t chunks = 0;
+    for (int j = 0; j < jobs.count; ++j) chunks = std::max(chunks, reduce_chunks(jobs.rows[j]));
+    const int64_t stride = chunks > 1 ? chunks : 0;
+    if (stride) {
+        hipLaunchKernelGGL(reduce_chunks_kernel, dim3((unsigned)chunks, (unsigned)jobs.count), dim3(256), 0, st,
+                           partials, jobs, stride, tmp);
+        if (hipError_t e = hipGetLastError()) return e;
     }
-    const int64_t nb = (count + kReduceChunk - 1) / kReduceChunk;
-    hipLaunchKernelGGL(reduce_l1_kernel, dim3((unsigned)nb), dim3(256), 0, st, partials, count, tmp);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_l2_kernel, dim3(1), dim3(256), 0, st, (const double *)tmp, nb, dst, sm, accumulate);
+    hipLaunchKernelGGL(reduce_jobs_kernel, dim3((unsigned)jobs.count), dim3(256), 0, st, stride ? tmp : partials, jobs,
+                       stride, out);
     return hipGetLastError();
 }
 

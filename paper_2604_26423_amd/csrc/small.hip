@@ -490,8 +490,7 @@ __global__ void __launch_bounds__(SmallCfg<N>::NT) small_adjoint(SmallProg sp)
     if (tid < 2 * sp.nlayers) {
         double s = 0.0;
         for (int w = 0; w < NW; ++w) s += gsum[tid * NW + w];
-        const int L = tid >> 1;
-        if ((tid & 1) ? sp.do_mixer[L] : sp.do_phase[L]) sp.out[2 + (tid & 1 ? ptotal : 0) + sp.layer0 + L] += s;
+        sp.out[2 + (tid & 1 ? ptotal : 0) + sp.layer0 + (tid >> 1)] = s;
     }
     if (sp.store) {
 #pragma unroll
