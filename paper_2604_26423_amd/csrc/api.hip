@@ -609,10 +609,10 @@ qs_status run_small_forward(qs_state s, const Circuit &cc, double *readout, cons
 // <C> and the norm of the state: out[0] = norm, out[1] = sum |a|^2 C_t.
 qs_status run_expect(qs_state s, const int32_t *diag, double *out, const char *where)
 {
-    HIPCHK(ensure_partials(s, 16384), where);
-    int64_t nb = 0;
+    const int64_t nb = expect_grid((int64_t)1 << s->n);
+    HIPCHK(ensure_partials(s, nb), where);
     Launch L(s, QS_KIND_EXPECT, ldexp(1.0, s->n) * (amp_bytes(s->prec) + 4));
-    HIPCHK(launch_expect(s->prec, s->psi, diag, s->n, (double *)s->partials.p, &nb, s->stream), where);
+    HIPCHK(launch_expect(s->prec, s->psi, diag, s->n, (double *)s->partials.p, s->stream), where);
     L.done();
     Reducer red(s, out, nb);
     double *rows = nullptr;
@@ -1271,25 +1271,40 @@ qs_status qs_sample(qs_state s, uint64_t seed, int64_t shots, uint64_t *out, int
     const size_t o_flag = o_chunk + (size_t)(nchunk + 1) * 8;
     HIPCHK(s->sample.ensure(o_flag + 256), where);
     char *base = (char *)s->sample.p;
+    // Host results: the flag and the shots in pinned memory when they fit (the
+    // shots drawn in device memory and copied, 8-byte writes to the host being
+    // slow), else the flag cleared, read and the shots copied separately.
+    const bool to_host = !out_on_device && shots > 0;
+    constexpr size_t kHead = 64;
+    char *pin = (char *)s->host.ensure(kHead + (to_host ? (size_t)shots * 8 : 0), s->stream);
     SampleBufs b{(uint64_t *)(base + o_sub), (uint64_t *)(base + o_blk), (uint64_t *)(base + o_chunk),
-                 (int32_t *)(base + o_flag)};
+                 (int32_t *)(pin ? pin : base + o_flag)};
     uint64_t *dst = out;
-    if (!out_on_device && shots > 0) {
+    if (to_host) {
         HIPCHK(s->shots_out.ensure((size_t)shots * 8), where);
         dst = (uint64_t *)s->shots_out.p;
     }
-    hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s->stream, (double *)b.flag, 1);
-    HIPCHK(hipGetLastError(), where);
+    if (pin) {
+        *(int32_t *)pin = 0;
+    } else {
+        hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s->stream, (double *)b.flag, 1);
+        HIPCHK(hipGetLastError(), where);
+    }
     {
         Launch L(s, QS_KIND_SAMPLE, ldexp(1.0, s->n) * amp_bytes(s->prec) + (double)shots * 8);
         HIPCHK(launch_sample(s->prec, s->psi, s->n, b, seed, shots, dst, s->stream, s->sym ? s->nq : 0), where);
         L.done();
     }
     int32_t flag = 0;
-    HIPCHK(hipMemcpyAsync(&flag, b.flag, 4, hipMemcpyDeviceToHost, s->stream), where);
-    if (!out_on_device && shots > 0)
-        HIPCHK(hipMemcpyAsync(out, dst, (size_t)shots * 8, hipMemcpyDeviceToHost, s->stream), where);
+    if (!pin) HIPCHK(hipMemcpyAsync(&flag, b.flag, 4, hipMemcpyDeviceToHost, s->stream), where);
+    if (to_host)
+        HIPCHK(hipMemcpyAsync(pin ? (void *)(pin + kHead) : (void *)out, dst, (size_t)shots * 8, hipMemcpyDeviceToHost,
+                              s->stream), where);
     HIPCHK(hipStreamSynchronize(s->stream), where);
+    if (pin) {
+        flag = *(int32_t *)pin;
+        if (to_host) memcpy(out, pin + kHead, (size_t)shots * 8);
+    }
     if (flag == 1) return fail(QS_ERR_STATE, "qs_sample: state has zero norm");
     if (flag == 2) return fail(QS_ERR_STATE, "qs_sample: state norm too large (|a|^2 sums to 4 or more)");
     return QS_OK;
@@ -1342,7 +1357,7 @@ qs_status qs_cost_histogram(qs_state s, const int32_t *diag_dev, int32_t nbins, 
     if (out_on_device && !aligned(mass, 8)) return fail(QS_ERR_ARG, "output must be 8-byte aligned");
     const char *where = "qs_cost_histogram";
     const HistGeom g = hist_geom(s->prec, s->n, nbins);
-    // scratch: rows of nbins uint64, the device output, per-workgroup FP64 sums, the flag
+    // scratch: rows of nbins uint64, the device output, per-workgroup FP64 sums, total and flag
     const size_t o_rows = 0;
     const size_t o_out = o_rows + (((size_t)g.rows * nbins * 8 + 255) & ~(size_t)255);
     const size_t o_fsum = o_out + (((size_t)nbins * 8 + 255) & ~(size_t)255);
@@ -1350,11 +1365,20 @@ qs_status qs_cost_histogram(qs_state s, const int32_t *diag_dev, int32_t nbins, 
     HIPCHK(s->hist.ensure(o_flag + 256), where);
     char *base = (char *)s->hist.p;
     uint64_t *rows = (uint64_t *)(base + o_rows);
-    uint64_t *dst = out_on_device ? mass : (uint64_t *)(base + o_out);
     double *fsum = (double *)(base + o_fsum);
-    int32_t *flag = (int32_t *)(base + o_flag);
-    hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s->stream, (double *)flag, 1);
-    HIPCHK(hipGetLastError(), where);
+    // the total, the flag and the masses for the host: written into pinned
+    // memory when they fit, else copied
+    constexpr size_t kHead = 64;
+    char *pin = (char *)s->host.ensure(kHead + (out_on_device ? 0 : (size_t)nbins * 8), s->stream);
+    double *total_d = (double *)(pin ? pin : base + o_flag);
+    int32_t *flag = (int32_t *)(total_d + 1);
+    uint64_t *dst = out_on_device ? mass : (uint64_t *)(pin ? pin + kHead : base + o_out);
+    if (pin) {
+        *flag = 0;
+    } else {
+        hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s->stream, total_d, 2);
+        HIPCHK(hipGetLastError(), where);
+    }
     if (!g.lds) {  // the global-atomic form adds into one zeroed row
         const int64_t words = nbins;
         hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s->stream,
@@ -1363,18 +1387,24 @@ qs_status qs_cost_histogram(qs_state s, const int32_t *diag_dev, int32_t nbins, 
     }
     {
         Launch L(s, QS_KIND_HISTOGRAM, ldexp(1.0, s->n) * (amp_bytes(s->prec) + 4));
-        HIPCHK(launch_histogram(s->prec, s->psi, diag_dev, nbins, g, rows, fsum, flag, dst, s->stream, s->sym), where);
+        HIPCHK(launch_histogram(s->prec, s->psi, diag_dev, nbins, g, rows, fsum, flag, dst, total_d, s->stream, s->sym),
+               where);
         L.done();
     }
-    std::vector<double> fs((size_t)g.groups);
-    int32_t fl = 0;
-    HIPCHK(hipMemcpyAsync(fs.data(), fsum, fs.size() * 8, hipMemcpyDeviceToHost, s->stream), where);
-    HIPCHK(hipMemcpyAsync(&fl, flag, 4, hipMemcpyDeviceToHost, s->stream), where);
-    if (!out_on_device) HIPCHK(hipMemcpyAsync(mass, dst, (size_t)nbins * 8, hipMemcpyDeviceToHost, s->stream), where);
+    double head[2];
+    if (!pin) {
+        HIPCHK(hipMemcpyAsync(head, total_d, sizeof head, hipMemcpyDeviceToHost, s->stream), where);
+        if (!out_on_device)
+            HIPCHK(hipMemcpyAsync(mass, dst, (size_t)nbins * 8, hipMemcpyDeviceToHost, s->stream), where);
+    }
     HIPCHK(hipStreamSynchronize(s->stream), where);
-    double total = 0.0;
-    for (double v : fs) total += v;
-    if (s->sym) total *= 2.0;
+    if (pin) {
+        memcpy(head, pin, sizeof head);
+        if (!out_on_device) memcpy(mass, dst, (size_t)nbins * 8);
+    }
+    int32_t fl = 0;
+    memcpy(&fl, &head[1], sizeof fl);
+    const double total = head[0] * (s->sym ? 2.0 : 1.0);
     if (fl == 2 || !(total < 3.999))
         return fail(QS_ERR_STATE, "qs_cost_histogram: state norm too large (|a|^2 sums to 4 or more)");
     return QS_OK;

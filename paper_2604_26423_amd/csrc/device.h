@@ -404,6 +404,36 @@ __device__ __forceinline__ void store_nt(V *p, V v)
     __builtin_nontemporal_store(t, reinterpret_cast<typename NtVec<V>::T *>(p));
 }
 
+// Readouts read the state and the diagonal once: 16 bytes of the state per load
+// and lane, nontemporal (streaming), which measured the n = 32 histogram 5%
+// faster in both precisions.
+template <typename V> struct WideLoad;
+template <> struct WideLoad<float2> {  // two amplitudes per 16-byte load
+    static constexpr int K = 2;
+    __device__ static void load(const float2 *p, int64_t x, float2 (&a)[2])
+    {
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        const f4 v = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p + x));
+        a[0] = make_float2(v.x, v.y);
+        a[1] = make_float2(v.z, v.w);
+    }
+    __device__ static void load_c(const int32_t *d, int64_t x, int32_t (&c)[2])
+    {
+        typedef int i2 __attribute__((ext_vector_type(2)));
+        const i2 v = __builtin_nontemporal_load(reinterpret_cast<const i2 *>(d + x));
+        c[0] = v.x;
+        c[1] = v.y;
+    }
+};
+template <> struct WideLoad<double2> {
+    static constexpr int K = 1;
+    __device__ static void load(const double2 *p, int64_t x, double2 (&a)[1]) { a[0] = load_nt(p + x); }
+    __device__ static void load_c(const int32_t *d, int64_t x, int32_t (&c)[1])
+    {
+        c[0] = __builtin_nontemporal_load(d + x);
+    }
+};
+
 // LDS byte offset of slot (thread part) XOR slot (register part).  The slot
 // map is linear over XOR, so the address of register r in a layout is the
 // thread's part XOR a part that depends only on r and the (uniform) window:

@@ -335,8 +335,8 @@ hipError_t launch_copy_amplitudes(int prec, void *psi, int64_t first, int64_t co
                                   hipStream_t st);
 hipError_t launch_cost_layer(int prec, void *psi, const int32_t *diag, int n, int64_t W,
                              double theta, hipStream_t st);
-hipError_t launch_expect(int prec, const void *psi, const int32_t *diag, int n,
-                         double *partials, int64_t *nblocks, hipStream_t st);
+int64_t expect_grid(int64_t dim);  // workgroups of launch_expect: rows of partials
+hipError_t launch_expect(int prec, const void *psi, const int32_t *diag, int n, double *partials, hipStream_t st);
 // Fixed-order sums of several launches' partials: job j's rows (kSlots doubles
 // each) start at row off[j]; out gets kSlots doubles per job.  tmp:
 // reduce_tmp_doubles(rows of all jobs) doubles.
@@ -386,7 +386,7 @@ constexpr DiagScratch diag_scratch_plan(int nmax, int nres, int64_t nwg)
 struct SampleBufs {
     uint64_t *sub;     // in-block exclusive prefix of 64-amplitude sub-block sums
     uint64_t *blk;     // in-chunk exclusive prefix of block sums
-    uint64_t *chunk;   // global exclusive prefix of chunk sums, then the total at [nchunks]
+    uint64_t *chunk;   // chunk sums
     int32_t *flag;     // overflow / zero-total flag
 };
 void sample_sizes(int n, int64_t *nsub, int64_t *nblk, int64_t *nchunk);
@@ -407,9 +407,9 @@ struct HistGeom {
 };
 HistGeom hist_geom(int prec, int n, int nbins);
 // shift: the per-bin sums are multiplied by 2^shift (1 for the complement-symmetric layout,
-// where each stored amplitude stands for two basis states).
+// where each stored amplitude stands for two basis states).  total: the FP64 sum of |a|^2.
 hipError_t launch_histogram(int prec, const void *psi, const int32_t *diag, int nbins, const HistGeom &g,
-                            uint64_t *rows, double *fsum, int32_t *flag, uint64_t *out, hipStream_t st,
-                            int shift = 0);
+                            uint64_t *rows, double *fsum, int32_t *flag, uint64_t *out, double *total,
+                            hipStream_t st, int shift = 0);
 
 }  // namespace qs

@@ -42,20 +42,63 @@ __global__ void __launch_bounds__(kElemThreads) cost_layer_kernel(V *psi, const 
         psi[x] = cmul(psi[x], expi<V>(theta * (double)(2 * (int64_t)diag[x] - W) / 20.0));
 }
 
+// Bound by the read of the state and the diagonal (12 B per complex64
+// amplitude): 16-byte streaming loads from a contiguous range per workgroup, four
+// strides in flight (strides of the whole grid instead: 275 us), and
+// no more workgroups than fill the chip, so that one reduction chunk takes
+// their sums (one amplitude per load and 16384 workgroups: 283 us + 16 us of
+// reductions at n = 27, now 230 + 5).
+constexpr int kExpectThreads = 512;
+constexpr int64_t kExpectMaxBlocks = 512;
 template <typename V>
-__global__ void __launch_bounds__(kElemThreads) expect_kernel(const V *psi, const int32_t *diag,
-                                                              int64_t dim, double *partials)
+__global__ void __launch_bounds__(kExpectThreads) expect_kernel(const V *psi, const int32_t *diag, int64_t dim,
+                                                                double *partials)
 {
-    __shared__ double red[2 * (kElemThreads / 64)];
+    using Wd = WideLoad<V>;
+    constexpr int K = Wd::K, U = 4;
+    __shared__ double red[2 * (kExpectThreads / 64)];
     double acc[2] = {0.0, 0.0};
-    for (int64_t x = (int64_t)blockIdx.x * kElemThreads + threadIdx.x; x < dim;
-         x += (int64_t)gridDim.x * kElemThreads) {
-        const V a = psi[x];
-        const double pr = (double)a.x * (double)a.x + (double)a.y * (double)a.y;
-        acc[0] += pr;
-        acc[1] += pr * (double)diag[x];
+    auto add = [&](const V (&a)[K], const int32_t (&c)[K]) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const double pr = (double)a[k].x * (double)a[k].x + (double)a[k].y * (double)a[k].y;
+            acc[0] += pr;
+            acc[1] += pr * (double)c[k];
+        }
+    };
+    if (dim < K) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            V a[K] = {};
+            int32_t c[K] = {};
+            a[0] = psi[0];
+            c[0] = diag[0];
+            add(a, c);
+        }
+    } else {
+        // a contiguous range per workgroup (dim and the grid are powers of two;
+        // at least one stride)
+        const int64_t S = kExpectThreads * K, per = dim / gridDim.x, lo = blockIdx.x * per, hi = lo + per;
+        int64_t x = lo + (int64_t)threadIdx.x * K;
+        for (; x + (U - 1) * S < hi; x += U * S) {
+            V a[U][K];
+            int32_t c[U][K];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                Wd::load(psi, x + u * S, a[u]);
+                Wd::load_c(diag, x + u * S, c[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) add(a[u], c[u]);
+        }
+        for (; x < hi; x += S) {
+            V a[K];
+            int32_t c[K];
+            Wd::load(psi, x, a);
+            Wd::load_c(diag, x, c);
+            add(a, c);
+        }
     }
-    block_sum(acc, red, threadIdx.x, kElemThreads);
+    block_sum(acc, red, threadIdx.x, kExpectThreads);
     if (threadIdx.x == 0) {
         partials[blockIdx.x * kSlots + 0] = acc[0];
         partials[blockIdx.x * kSlots + 1] = acc[1];
@@ -170,18 +213,18 @@ hipError_t launch_cost_layer(int prec, void *psi, const int32_t *diag, int n, in
     return hipGetLastError();
 }
 
-hipError_t launch_expect(int prec, const void *psi, const int32_t *diag, int n, double *partials,
-                         int64_t *nblocks, hipStream_t st)
+int64_t expect_grid(int64_t dim)
+{
+    const int64_t g = (dim + 2 * kExpectThreads - 1) / (2 * kExpectThreads);
+    return g < kExpectMaxBlocks ? g : kExpectMaxBlocks;
+}
+
+hipError_t launch_expect(int prec, const void *psi, const int32_t *diag, int n, double *partials, hipStream_t st)
 {
     const int64_t dim = (int64_t)1 << n;
-    const int64_t g = elem_grid(dim);
-    *nblocks = g;
-    if (prec == 0)
-        hipLaunchKernelGGL(expect_kernel<float2>, dim3((unsigned)g), dim3(kElemThreads), 0, st,
-                           (const float2 *)psi, diag, dim, partials);
-    else
-        hipLaunchKernelGGL(expect_kernel<double2>, dim3((unsigned)g), dim3(kElemThreads), 0, st,
-                           (const double2 *)psi, diag, dim, partials);
+    const dim3 g((unsigned)expect_grid(dim)), b(kExpectThreads);
+    if (prec == 0) hipLaunchKernelGGL(expect_kernel<float2>, g, b, 0, st, (const float2 *)psi, diag, dim, partials);
+    else hipLaunchKernelGGL(expect_kernel<double2>, g, b, 0, st, (const double2 *)psi, diag, dim, partials);
     return hipGetLastError();
 }
 

@@ -7,9 +7,10 @@
 // The CDF is never stored.  Pass A writes exclusive prefix sums at three
 // levels: 64-amplitude sub-blocks within 8192-amplitude blocks, blocks within
 // 2^26-amplitude chunks, and chunks; integer sums make the result independent
-// of summation order.  Each shot then descends the three levels by binary
-// search and scans 64 amplitudes.  Small states (n < 13) use one workgroup
-// and a full CDF in LDS.
+// of summation order.  Each shot then descends the three levels and scans 64
+// amplitudes.  Small states (n < 13) use a full CDF in LDS.
+#include <algorithm>
+
 #include "device.h"
 
 namespace qs {
@@ -123,156 +124,206 @@ __global__ void __launch_bounds__(256) sample_blocks_kernel(const V *psi, uint64
     }
 }
 
+// Exclusive prefix over the workgroup of one value per thread (1024 threads at
+// most); *total: the sum.  red: 16 words of LDS.
+__device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t *red, int tid, uint64_t *total)
+{
+    const int wave = tid >> 6, lane = tid & 63, nw = blockDim.x >> 6;
+    const uint64_t incl = wave_scan_u64(v, lane);
+    if (lane == 63) red[wave] = incl;
+    __syncthreads();
+    uint64_t before = 0, all = 0;
+    for (int w = 0; w < nw; ++w) {
+        before += w < wave ? red[w] : 0;
+        all += red[w];
+    }
+    *total = all;
+    return before + incl - v;
+}
+
 // In-place exclusive scan of block sums within each chunk; chunk sums out.
-__global__ void __launch_bounds__(256) scan_blocks_kernel(uint64_t *blk, int64_t nblk, uint64_t *chunk)
+// One workgroup per chunk: eight consecutive entries per thread, all loaded
+// before any is summed (a serial pass of one thread over 256 partial sums took
+// 20 us at n = 27, this one 5).
+constexpr int kScanThreads = 1024;
+__global__ void __launch_bounds__(kScanThreads) scan_blocks_kernel(uint64_t *blk, int64_t nblk, uint64_t *chunk)
 {
-    __shared__ uint64_t tsum[256];
+    __shared__ uint64_t red[kScanThreads / 64];
+    constexpr int per = kBlkPerChunk / kScanThreads;
     const int tid = threadIdx.x;
-    const int64_t c = blockIdx.x;
-    const int64_t lo = c * kBlkPerChunk;
-    const int64_t len = (nblk - lo) < kBlkPerChunk ? (nblk - lo) : kBlkPerChunk;
-    const int per = kBlkPerChunk / 256;  // 32 entries per thread
-    uint64_t loc = 0;
-    for (int k = 0; k < per; ++k) {
-        const int64_t i = (int64_t)tid * per + k;
-        if (i < len) loc += blk[lo + i];
-    }
-    tsum[tid] = loc;
-    __syncthreads();
-    if (tid == 0) {
-        uint64_t acc = 0;
-        for (int t = 0; t < 256; ++t) {
-            const uint64_t v = tsum[t];
-            tsum[t] = acc;
-            acc += v;
-        }
-        chunk[c] = acc;
-    }
-    __syncthreads();
-    uint64_t acc = tsum[tid];
-    for (int k = 0; k < per; ++k) {
-        const int64_t i = (int64_t)tid * per + k;
-        if (i < len) {
-            const uint64_t v = blk[lo + i];
-            blk[lo + i] = acc;
-            acc += v;
-        }
-    }
-}
-
-// Exclusive scan of chunk sums; total T at chunk[nchunk].  Flags a zero total
-// or a 64-bit wrap.
-__global__ void scan_chunks_kernel(uint64_t *chunk, int64_t nchunk, int32_t *flag)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    uint64_t acc = 0;
-    for (int64_t c = 0; c < nchunk; ++c) {
-        const uint64_t v = chunk[c];
-        chunk[c] = acc;
-        if (acc + v < acc) *flag = 2;
-        acc += v;
-    }
-    chunk[nchunk] = acc;
-    if (acc == 0) *flag = 1;
-}
-
-// Largest i in [0, len) with a[i] <= u (a nondecreasing, a[0] = 0 <= u).
-__device__ __forceinline__ int64_t last_le(const uint64_t *a, int64_t len, uint64_t u)
-{
-    int64_t lo = 0, hi = len - 1;
-    while (lo < hi) {
-        const int64_t mid = lo + (hi - lo + 1) / 2;
-        if (a[mid] <= u) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
-template <typename V>
-__global__ void __launch_bounds__(256) sample_shots_kernel(const V *psi, const uint64_t *sub, const uint64_t *blk,
-                                                           const uint64_t *chunk, int64_t nchunk, int64_t nblk,
-                                                           uint64_t seed, int64_t shots, uint64_t *out,
-                                                           int32_t *flag, int sym_n)
-{
-    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (s >= shots) return;
-    const uint64_t T = chunk[nchunk];
-    uint64_t r0, r1;
-    philox_words01((uint64_t)s, seed, r0, r1);
-    uint64_t u = __umul64hi(r0, T);
-    const int64_t c = last_le(chunk, nchunk, u);
-    u -= chunk[c];
-    const int64_t b0 = c * kBlkPerChunk;
-    const int64_t blen = (nblk - b0) < kBlkPerChunk ? (nblk - b0) : kBlkPerChunk;
-    const int64_t b = b0 + last_le(blk + b0, blen, u);
-    u -= blk[b];
-    const int64_t j = last_le(sub + b * kSubPerBlock, kSubPerBlock, u);
-    u -= sub[b * kSubPerBlock + j];
-    const int64_t x0 = (b << kBlockBits) + (j << kSubBits);
-    const int64_t fb = swz_fold(b) << kSwzDst;
-    uint64_t acc = 0;
-    int64_t x = x0 + 63;
-    for (int t = 0; t < 64; ++t) {
-        acc += qval_of(psi[(x0 + t) ^ fb], flag);
-        if (acc > u) {
-            x = x0 + t;
-            break;
-        }
-    }
-    uint64_t xo = (uint64_t)x;
-    if (sym_n) {  // z -> y(z) (suffix XOR), or its complement over sym_n bits
+    const int64_t lo = (int64_t)blockIdx.x * kBlkPerChunk + (int64_t)tid * per;
+    uint64_t v[per], loc = 0, total;
 #pragma unroll
-        for (int sh = 1; sh < 64; sh <<= 1) xo ^= xo >> sh;
-        if (r1 >> 63) xo ^= (~0ull) >> (64 - sym_n);
+    for (int k = 0; k < per; ++k) v[k] = lo + k < nblk ? blk[lo + k] : 0;
+#pragma unroll
+    for (int k = 0; k < per; ++k) loc += v[k];
+    uint64_t acc = block_scan_u64(loc, red, tid, &total);
+#pragma unroll
+    for (int k = 0; k < per; ++k) {
+        if (lo + k < nblk) blk[lo + k] = acc;
+        acc += v[k];
     }
-    out[s] = xo;
+    if (tid == 0) chunk[blockIdx.x] = total;
 }
 
-// n < 13: the whole CDF in LDS, one workgroup.
-template <typename V>
-__global__ void __launch_bounds__(256) sample_small_kernel(const V *psi, int n, uint64_t seed, int64_t shots,
-                                                           uint64_t *out, int32_t *flag)
+// Lanes that work on one shot together, and the shots that such a group draws
+// one after the other: one, or kShotRounds from kManyShots on.
+constexpr int kShotLanes = 16;
+constexpr int kShotThreads = 256;
+constexpr int64_t kManyShots = 1 << 19;
+constexpr int kShotRounds = 16;
+constexpr int kMaxChunks = 256;  // 2^34 stored amplitudes
+
+// Number of leading lanes of the shot's group for which yes holds.
+__device__ __forceinline__ int group_count(bool yes)
 {
+    const uint64_t m = __ballot(yes) >> (threadIdx.x & 63 & ~(kShotLanes - 1));
+    return __builtin_ctzll(~(m & ((1ull << kShotLanes) - 1ull)));
+}
+
+// Largest i in [0, len) with a[i] <= u (a nondecreasing, a[0] = 0 <= u, len a
+// power of two), kShotLanes probes at a time.  The first probe of every step
+// holds, whatever a is, so the result is in range also where sums wrapped.
+__device__ __forceinline__ int64_t group_last_le(const uint64_t *a, int64_t len, uint64_t u, int g)
+{
+    int64_t base = 0;
+    for (int64_t span = len; span > 1;) {
+        const int64_t step = span > kShotLanes ? span / kShotLanes : 1;
+        const bool in = g * step < span;
+        const int c = group_count(in && a[in ? base + g * step : base] <= u);
+        base += (int64_t)(c - 1) * step;
+        span = step;
+    }
+    return base;
+}
+
+// A shot is a chain of dependent reads.  Sixteen lanes share it: four probes
+// find the block of 8192 in a chunk, two the sub-block, and the 64 amplitudes
+// are read at once and scanned across the lanes (one lane per shot took 20
+// binary-search steps and a serial walk over the amplitudes: 24 us for 10,000
+// shots at n = 27, 10 us now).  The chunk sums are scanned by every workgroup
+// in LDS; the first one reports a zero total or a 64-bit wrap.  With shots
+// enough to fill the chip the latency is hidden and the work per shot counts:
+// a group then draws 16 shots in turn, so that the chunk scan is shared by 256
+// shots and a wave's lanes evaluate 64 Philox outputs at once (whole calls with
+// 10^6 shots, n = 16 / 27: one lane per shot 167 / 612 us, a group's single
+// shot 218 / 487, 16 in turn 131 / 488; with 10^5 shots at n = 27 16 in turn leave
+// the chip idle, 269 against 233; four lanes per shot lost, 289 / 888).
+template <typename V>
+__global__ void __launch_bounds__(kShotThreads) sample_shots_kernel(const V *psi, const uint64_t *sub,
+                                                                    const uint64_t *blk, const uint64_t *chunk,
+                                                                    int64_t nchunk, int64_t nblk, uint64_t seed,
+                                                                    int64_t shots, int rounds, uint64_t *out,
+                                                                    int32_t *flag, int sym_n)
+{
+    __shared__ uint64_t cs[kMaxChunks];
+    __shared__ uint64_t red[kShotThreads / 64];
+    constexpr int kGroups = 64 / kShotLanes;  // of a wave
+    const int tid = threadIdx.x, lane = tid & 63, g = lane & (kShotLanes - 1);
+    uint64_t T;
+    const uint64_t mine = tid < nchunk ? chunk[tid] : 0;
+    const uint64_t excl = block_scan_u64(mine, red, tid, &T);
+    cs[tid] = excl;
+    if (blockIdx.x == 0) {
+        if (excl + mine < excl) *flag = 2;
+        else if (T == 0 && tid == 0) *flag = 1;
+    }
+    __syncthreads();
+    // lane i evaluates the draw of the wave's shot i (i < kGroups * rounds <= 64)
+    const int64_t s0 = ((int64_t)blockIdx.x * (kShotThreads / 64) + (tid >> 6)) * (kGroups * rounds);
+    uint64_t w0, w1;
+    philox_words01((uint64_t)(s0 + lane), seed, w0, w1);
+    for (int i = 0; i < rounds; ++i) {
+        const int at_lane = i * kGroups + lane / kShotLanes;
+        const int64_t s = s0 + at_lane;
+        const uint64_t r0 = __shfl(w0, at_lane, 64), r1 = __shfl(w1, at_lane, 64);
+        if (s >= shots) return;  // a whole group, and its later shots
+        uint64_t u = __umul64hi(r0, T);
+        const int64_t c = group_last_le(cs, nchunk, u, g);
+        u -= cs[c];
+        const int64_t b0 = c * kBlkPerChunk;
+        const int64_t blen = (nblk - b0) < kBlkPerChunk ? (nblk - b0) : kBlkPerChunk;
+        const int64_t b = b0 + group_last_le(blk + b0, blen, u, g);
+        u -= blk[b];
+        const int64_t j = group_last_le(sub + b * kSubPerBlock, kSubPerBlock, u, g);
+        u -= sub[b * kSubPerBlock + j];
+        const int64_t x0 = (b << kBlockBits) + (j << kSubBits);
+        const int64_t fb = swz_fold(b) << kSwzDst;
+        constexpr int per = 64 / kShotLanes;  // consecutive amplitudes of a lane (the fold keeps runs of 16)
+        const V *p = psi + ((x0 + g * per) ^ fb);
+        uint64_t q[per], loc = 0;
+#pragma unroll
+        for (int t = 0; t < per; ++t) q[t] = qval_of(p[t], flag);
+#pragma unroll
+        for (int t = 0; t < per; ++t) loc += q[t];
+        uint64_t acc = loc;
+#pragma unroll
+        for (int off = 1; off < kShotLanes; off <<= 1) {
+            const uint64_t t = __shfl_up(acc, off, kShotLanes);
+            if (g >= off) acc += t;
+        }
+        // the first lane whose inclusive sum exceeds u holds the shot; none
+        // (only if the state changed meanwhile): the last amplitude
+        const int at = group_count(!(acc > u));
+        if (g == (at < kShotLanes ? at : kShotLanes - 1)) {
+            acc -= loc;
+            int64_t x = x0 + 63;
+            bool found = false;
+#pragma unroll
+            for (int t = 0; t < per; ++t) {
+                acc += q[t];
+                if (!found && acc > u) {
+                    x = x0 + g * per + t;
+                    found = true;
+                }
+            }
+            uint64_t xo = (uint64_t)x;
+            if (sym_n) {  // z -> y(z) (suffix XOR), or its complement over sym_n bits
+#pragma unroll
+                for (int sh = 1; sh < 64; sh <<= 1) xo ^= xo >> sh;
+                if (r1 >> 63) xo ^= (~0ull) >> (64 - sym_n);
+            }
+            out[s] = xo;
+        }
+    }
+}
+
+// n < 13: every workgroup builds the whole CDF in LDS and draws kSmallShots
+// shots, one per thread.
+constexpr int kSmallShots = 1024;
+template <typename V>
+__global__ void __launch_bounds__(kSmallShots) sample_small_kernel(const V *psi, int n, uint64_t seed, int64_t shots,
+                                                                   uint64_t *out, int32_t *flag)
+{
+    constexpr int per = (1 << (kBlockBits - 1)) / kSmallShots;
     __shared__ uint64_t F[1 << (kBlockBits - 1)];
-    __shared__ uint64_t tsum[256];
+    __shared__ uint64_t red[kSmallShots / 64];
     const int tid = threadIdx.x, dim = 1 << n;
-    const int per = (dim + 255) / 256;
-    uint64_t loc = 0;
+    uint64_t q[per], loc = 0, T;
+#pragma unroll
     for (int k = 0; k < per; ++k) {
         const int x = tid * per + k;
-        if (x < dim) {
-            loc += qval_of(psi[x], flag);
-            F[x] = loc;
-        }
+        q[k] = x < dim ? qval_of(psi[x], flag) : 0;
+        loc += q[k];
     }
-    tsum[tid] = loc;
-    __syncthreads();
-    if (tid == 0) {
-        uint64_t acc = 0;
-        for (int t = 0; t < 256; ++t) {
-            const uint64_t v = tsum[t];
-            tsum[t] = acc;
-            acc += v;
-        }
-        if (acc == 0) *flag = 1;
-    }
-    __syncthreads();
+    uint64_t acc = block_scan_u64(loc, red, tid, &T);
+#pragma unroll
     for (int k = 0; k < per; ++k) {
-        const int x = tid * per + k;
-        if (x < dim) F[x] += tsum[tid];
+        acc += q[k];
+        F[tid * per + k] = acc;
     }
+    if (blockIdx.x == 0 && tid == 0 && T == 0) *flag = 1;
     __syncthreads();
-    const uint64_t T = F[dim - 1];
-    for (int64_t s = tid; s < shots; s += 256) {
-        const uint64_t u = __umul64hi(philox_word0((uint64_t)s, seed), T);
-        int lo = 0, hi = dim - 1;  // first x with F[x] > u
-        while (lo < hi) {
-            const int mid = (lo + hi) / 2;
-            if (F[mid] > u) hi = mid;
-            else lo = mid + 1;
-        }
-        out[s] = (uint64_t)lo;
+    const int64_t s = (int64_t)blockIdx.x * kSmallShots + tid;
+    if (s >= shots) return;
+    const uint64_t u = __umul64hi(philox_word0((uint64_t)s, seed), T);
+    int lo = 0, hi = dim - 1;  // first x with F[x] > u
+    while (lo < hi) {
+        const int mid = (lo + hi) / 2;
+        if (F[mid] > u) hi = mid;
+        else lo = mid + 1;
     }
+    out[s] = (uint64_t)lo;
 }
 
 }  // namespace
@@ -292,13 +343,15 @@ void sample_sizes(int n, int64_t *nsub, int64_t *nblk, int64_t *nchunk)
 hipError_t launch_sample(int prec, const void *psi, int n, const SampleBufs &b, uint64_t seed, int64_t shots,
                          uint64_t *out, hipStream_t st, int sym_n)
 {
+    // (also without shots: a workgroup reports a state that cannot be sampled)
+    const auto groups = [&](int64_t per) { return dim3((unsigned)std::max<int64_t>(1, (shots + per - 1) / per)); };
     if (n < kBlockBits) {
         if (prec == 0)
-            hipLaunchKernelGGL(sample_small_kernel<float2>, dim3(1), dim3(256), 0, st, (const float2 *)psi, n, seed,
-                               shots, out, b.flag);
+            hipLaunchKernelGGL(sample_small_kernel<float2>, groups(kSmallShots), dim3(kSmallShots), 0, st,
+                               (const float2 *)psi, n, seed, shots, out, b.flag);
         else
-            hipLaunchKernelGGL(sample_small_kernel<double2>, dim3(1), dim3(256), 0, st, (const double2 *)psi, n,
-                               seed, shots, out, b.flag);
+            hipLaunchKernelGGL(sample_small_kernel<double2>, groups(kSmallShots), dim3(kSmallShots), 0, st,
+                               (const double2 *)psi, n, seed, shots, out, b.flag);
         return hipGetLastError();
     }
     int64_t nsub, nblk, nchunk;
@@ -311,22 +364,20 @@ hipError_t launch_sample(int prec, const void *psi, int n, const SampleBufs &b, 
                            (const double2 *)psi, b.sub, b.blk, b.flag);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)nchunk), dim3(256), 0, st, b.blk, nblk, b.chunk);
+    if (nchunk > kMaxChunks) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)nchunk), dim3(kScanThreads), 0, st, b.blk, nblk, b.chunk);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_chunks_kernel, dim3(1), dim3(64), 0, st, b.chunk, nchunk, b.flag);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (shots > 0) {
-        const int64_t g = (shots + 255) / 256;
-        if (prec == 0)
-            hipLaunchKernelGGL(sample_shots_kernel<float2>, dim3((unsigned)g), dim3(256), 0, st, (const float2 *)psi,
-                               (const uint64_t *)b.sub, (const uint64_t *)b.blk, (const uint64_t *)b.chunk, nchunk,
-                               nblk, seed, shots, out, b.flag, sym_n);
-        else
-            hipLaunchKernelGGL(sample_shots_kernel<double2>, dim3((unsigned)g), dim3(256), 0, st,
-                               (const double2 *)psi, (const uint64_t *)b.sub, (const uint64_t *)b.blk,
-                               (const uint64_t *)b.chunk, nchunk, nblk, seed, shots, out, b.flag, sym_n);
-        e = hipGetLastError();
-    }
+    const int rounds = shots < kManyShots ? 1 : kShotRounds;
+    const dim3 g = groups((int64_t)(kShotThreads / kShotLanes) * rounds);
+    if (prec == 0)
+        hipLaunchKernelGGL(sample_shots_kernel<float2>, g, dim3(kShotThreads), 0, st, (const float2 *)psi,
+                           (const uint64_t *)b.sub, (const uint64_t *)b.blk, (const uint64_t *)b.chunk, nchunk, nblk,
+                           seed, shots, rounds, out, b.flag, sym_n);
+    else
+        hipLaunchKernelGGL(sample_shots_kernel<double2>, g, dim3(kShotThreads), 0, st, (const double2 *)psi,
+                           (const uint64_t *)b.sub, (const uint64_t *)b.blk, (const uint64_t *)b.chunk, nchunk, nblk,
+                           seed, shots, rounds, out, b.flag, sym_n);
+    e = hipGetLastError();
     return e;
 }
 
