@@ -197,7 +197,7 @@ def symmetric_run(torch, Simulator, w, tzz, tx, exp_c_full, stream):
 
 def batch_run(torch, workloads, stream, cpu: bool):
     """512 uneven circuits (n = 14..22, p in {3, 5, 10}): forward + adjoint
-    gradient of all of them in one persistent launch, in complex64 (timed) and
+    gradient of all of them, one launch per pass, in complex64 (timed) and
     in complex128 (the per-circuit reference for the complex64 errors)."""
     import numpy as np
     from paper_2604_26423_amd import Batch

@@ -302,12 +302,9 @@ qs_status qs_adjoint_ckpt_bytes(qs_state s, int p, size_t *bytes);
 /*
  * Batched circuits (target workload: hundreds of small, uneven circuits).
  * Each circuit has its own instance, depth and angles; all of them run the
- * forward circuit and the adjoint gradient of qs_adjoint_grad in one
- * persistent kernel launch that hands out (circuit, pass, chunk of tiles)
- * work items from a global queue in rounds (pass r of every circuit, largest
- * circuits first); a work item waits for its circuit's previous pass through
- * completion counters.  Single-circuit tile kernels and the batched kernel
- * compute the same arithmetic.
+ * forward circuit and the adjoint gradient of qs_adjoint_grad in rounds:
+ * launch r works on pass r of every circuit that has one.  Single-circuit tile
+ * kernels and the batched kernel compute the same arithmetic.
  */
 #define QS_BATCH_MAX_QUBITS 30
 
@@ -335,8 +332,7 @@ qs_status qs_batch_info(qs_batch b, int i, int64_t *w_total_tenths, int32_t *cma
  * theta_zz, theta_x, d_theta_zz, d_theta_x: host arrays with the circuits'
  * per-layer values concatenated in circuit order (sum of p entries);
  * exp_c: host array of count values.  Synchronises.
- * Errors: QS_ERR_ARG, QS_ERR_HIP (including a dependency wait that exceeded
- * its bound, which cannot happen while the queue drains normally).
+ * Errors: QS_ERR_ARG, QS_ERR_OOM, QS_ERR_HIP.
  */
 qs_status qs_batch_forward_grad(qs_batch b, const double *theta_zz, const double *theta_x, double *exp_c,
                                 double *d_theta_zz, double *d_theta_x);

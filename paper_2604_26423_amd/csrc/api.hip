@@ -219,11 +219,16 @@ struct qs_batch_s {
     std::vector<int32_t> cmax;
     std::vector<size_t> off_psi, off_lam, off_diag;
     void *mem = nullptr;
-    DevBuf steps, tabs, partials, counters, results, index;
+    DevBuf steps, items, tabs, partials, results, index;
+    HostBuf host;
+    // the plan, fixed at creation: circuits in item order, their first steps,
+    // the items, and the items of each round
+    std::vector<int> order, step0;
+    std::vector<qs::BatchItem> items_h;
+    std::vector<int64_t> round_items;
+    std::vector<int> summed_h;     // steps that write sums
     std::vector<qs::BatchStep> steps_h;
-    std::vector<int> idx_h;        // cstep list, then cstep offsets
-    std::vector<int64_t> res_off_h;
-    std::vector<double> res_h;
+    std::vector<double> sums_h;
 };
 
 namespace {
@@ -815,24 +820,55 @@ size_t layout_batch(qs_batch b, int count, const qs_circuit *circuits, int prec)
     return off;
 }
 
+// Tiles of a work item: one, or as many as leave 2048 items per step.
+int64_t batch_chunk(int64_t ntiles) { return std::max<int64_t>(1, ntiles >> 11); }
+
+// The part of the plan that the angles do not change (host only).
+void plan_batch(qs_batch b)
+{
+    const int T = tile_bits(b->prec), count = b->count;
+    std::vector<int> nsteps(count);
+    for (int c = 0; c < count; ++c)
+        nsteps[c] = 2 * (int)forward_specs((int)plan_passes(b->n[c], b->prec).size(), b->p[c], true).size() - 1;
+    b->order.resize(count);
+    for (int c = 0; c < count; ++c) b->order[c] = c;
+    std::stable_sort(b->order.begin(), b->order.end(), [&](int x, int y) {
+        return nsteps[x] != nsteps[y] ? nsteps[x] > nsteps[y] : b->n[x] > b->n[y];
+    });
+    b->step0.assign(count, 0);
+    int at = 0;
+    for (int c : b->order) {
+        b->step0[c] = at;
+        at += nsteps[c];
+        const int64_t ntiles = (int64_t)1 << (b->n[c] - T), per = batch_chunk(ntiles);
+        for (int64_t k = 0; k * per < ntiles; ++k) b->items_h.push_back(BatchItem{b->step0[c], (int)k});
+        if (b->round_items.size() < (size_t)nsteps[c]) b->round_items.resize((size_t)nsteps[c], 0);
+        // (the circuits before this one have at least as many steps)
+        for (int r = 0; r < nsteps[c]; ++r) b->round_items[(size_t)r] = (int64_t)b->items_h.size();
+    }
+}
+
 struct BatchSchedule {
-    int64_t items = 0, tabs = 0, nres = 0;
-    int nidx = 0;
+    int64_t rows = 0, tabs = 0;
+    bool fast = false;   // every stage in tangent form (see batch.hip)
+    int tb = 0;          // log2 threads of the kernel
 };
 
-// The steps of every circuit (forward passes, turnaround, reverse passes) in
-// round order -- step r of every circuit, largest circuits first -- with item
-// numbers, predecessor links, table offsets and the per-circuit step lists
-// used by the reduction.  Host only: pointers into b->mem are computed, never
+// The steps of every circuit (forward passes, turnaround, reverse passes) with
+// their rows and tables.  Host only: pointers into b->mem are computed, never
 // dereferenced.
 BatchSchedule build_batch_schedule(qs_batch b, const double *theta_zz, const double *theta_x)
 {
     BatchSchedule sch;
     const int T = tile_bits(b->prec);
-    const int count = b->count;
-    // per-circuit step lists (in the circuit's own order)
-    std::vector<std::vector<BatchStep>> cs(count);
-    for (int c = 0; c < count; ++c) {
+    double factor;
+    sch.fast = true;
+    for (int64_t k = 0; k < b->angle_off.back(); ++k) sch.fast = sch.fast && rx_stage(theta_x[k], 1, &factor).tan;
+    sch.tb = batch_thread_bits(b->prec, sch.fast);
+    b->steps_h.clear();
+    b->summed_h.clear();
+    const int tabn = batch_table_entries();
+    for (int c : b->order) {
         const int n = b->n[c], p = b->p[c];
         void *psi = (char *)b->mem + b->off_psi[c];
         void *lam = (char *)b->mem + b->off_lam[c];
@@ -840,9 +876,10 @@ BatchSchedule build_batch_schedule(qs_batch b, const double *theta_zz, const dou
         const Circuit cc{diag, b->W[c], p, theta_zz + b->angle_off[c], theta_x + b->angle_off[c]};
         const std::vector<PassGeom> geo = plan_passes(n, b->prec);
         const std::vector<KSpec> ks = forward_specs((int)geo.size(), p, true);
+        const int64_t ntiles = (int64_t)1 << (n - T);
         auto add = [&](const KSpec &k, int kind) {
             BatchStep s{};
-            s.pp = make_prog_raw(psi, n, b->prec, nullptr, geo[k.pass], k, cc, kBatchThreadBits);
+            s.pp = make_prog_raw(psi, n, b->prec, nullptr, geo[k.pass], k, cc, sch.tb);
             s.pp.xcd_remap = 0;
             s.kind = kind;
             s.circuit = c;
@@ -858,54 +895,22 @@ BatchSchedule build_batch_schedule(qs_batch b, const double *theta_zz, const dou
                 s.map[1] = k.phase >= 0 ? 2 + k.phase : -1;
                 s.map[2] = k.pre >= 0 ? 2 + p + k.pre : -1;
             }
-            s.mode = tile_mode(s.pp, T, kBatchThreadBits);
-            const int64_t ntiles = (int64_t)1 << (n - T);
-            s.tiles_per_chunk = (int)std::min<int64_t>(ntiles, 16);
+            s.mode = tile_mode(s.pp, T, sch.tb);
+            s.tiles_per_chunk = batch_chunk(ntiles);
             s.chunks = (int)((ntiles + s.tiles_per_chunk - 1) / s.tiles_per_chunk);
-            cs[c].push_back(s);
+            s.row0 = -1;
+            if (kind >= 1) {
+                s.row0 = sch.rows;
+                sch.rows += s.chunks;
+                b->summed_h.push_back((int)b->steps_h.size());
+            }
+            s.tab_off = s.pp.has_phase ? (sch.tabs++) * tabn : -1;
+            b->steps_h.push_back(s);
         };
         for (size_t i = 0; i + 1 < ks.size(); ++i) add(ks[i], 0);
         add(ks.back(), 1);
         for (int i = (int)ks.size() - 2; i >= 0; --i) add(ks[i], 2);
     }
-    // rounds: step r of every circuit, the largest circuits first
-    std::vector<int> order(count);
-    for (int c = 0; c < count; ++c) order[c] = c;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-        const double wx = ldexp((double)cs[x].size(), b->n[x]), wy = ldexp((double)cs[y].size(), b->n[y]);
-        return wx > wy;
-    });
-    size_t maxsteps = 0;
-    for (int c = 0; c < count; ++c) maxsteps = std::max(maxsteps, cs[c].size());
-    b->steps_h.clear();
-    std::vector<std::vector<int>> where_c(count);
-    std::vector<int> last(count, -1);
-    int64_t &items = sch.items, &tabs = sch.tabs;
-    const int tabn = batch_table_entries();
-    for (size_t r = 0; r < maxsteps; ++r)
-        for (int c : order) {
-            if (r >= cs[c].size()) continue;
-            BatchStep s = cs[c][r];
-            s.prev = last[c];
-            s.item0 = items;
-            items += s.chunks;
-            s.tab_off = s.pp.has_phase ? (tabs++) * tabn : -1;
-            last[c] = (int)b->steps_h.size();
-            where_c[c].push_back(last[c]);
-            b->steps_h.push_back(s);
-        }
-    b->idx_h.clear();
-    std::vector<int> coff(count + 1, 0);
-    for (int c = 0; c < count; ++c) {
-        coff[c] = (int)b->idx_h.size();
-        for (int j : where_c[c]) b->idx_h.push_back(j);
-    }
-    coff[count] = (int)b->idx_h.size();
-    sch.nidx = (int)b->idx_h.size();
-    b->idx_h.insert(b->idx_h.end(), coff.begin(), coff.end());
-    b->res_off_h.assign(count + 1, 0);
-    for (int c = 0; c < count; ++c) b->res_off_h[c + 1] = b->res_off_h[c] + 2 + 2 * b->p[c];
-    sch.nres = b->res_off_h[count];
     return sch;
 }
 
@@ -1567,6 +1572,7 @@ qs_status qs_batch_create(int count, const qs_circuit *circuits, int prec, void 
         b0 = b;
         b->stream = (hipStream_t)hip_stream;
         const size_t off = layout_batch(b, count, circuits, prec);
+        plan_batch(b);
         hipError_t he = hipMalloc(&b->mem, off);
         if (he != hipSuccess) {
             delete b0;
@@ -1575,6 +1581,10 @@ qs_status qs_batch_create(int count, const qs_circuit *circuits, int prec, void 
         const DiagScratch L = diag_scratch_layout(nmax, count);
         char *scratch = nullptr;
         he = hipMalloc(&scratch, L.total);
+        if (he == hipSuccess) he = b->items.ensure(b->items_h.size() * sizeof(BatchItem));
+        if (he == hipSuccess)
+            he = hipMemcpyAsync(b->items.p, b->items_h.data(), b->items_h.size() * sizeof(BatchItem),
+                                hipMemcpyHostToDevice, b->stream);
         for (int i = 0; i < count && he == hipSuccess; ++i)
             he = build_diagonal(b->n[i], wms[i].data(), (int32_t *)((char *)b->mem + b->off_diag[i]), scratch, L, i,
                                 b->stream);
@@ -1620,67 +1630,52 @@ qs_status qs_batch_forward_grad(qs_batch b, const double *theta_zz, const double
             if (!std::isfinite(theta_zz[k]) || !std::isfinite(theta_x[k]))
                 return fail(QS_ERR_ARG, "non-finite angle at index %lld", (long long)k);
         const char *where = "qs_batch_forward_grad";
-        const int count = b->count;
 
         const BatchSchedule sch = build_batch_schedule(b, theta_zz, theta_x);
-        const int nsteps = (int)b->steps_h.size();
-        const int64_t items = sch.items, tabs = sch.tabs, nres = sch.nres;
-        const int nidx = sch.nidx;
+        const int nsteps = (int)b->steps_h.size(), nsum = (int)b->summed_h.size();
         const int tabn = batch_table_entries();
-
         const size_t ab = b->prec == QS_C64 ? 8 : 16;
         HIPCHK(b->steps.ensure(sizeof(BatchStep) * nsteps), where);
-        HIPCHK(b->tabs.ensure((size_t)std::max<int64_t>(tabs, 1) * tabn * ab), where);
-        HIPCHK(b->partials.ensure((size_t)items * kSlots * sizeof(double)), where);
-        // counters: ticket (8 B), abort flag, per-step done counters
-        const size_t cnt_doubles = (16 + (size_t)nsteps * 4 + 7) / 8;
-        HIPCHK(b->counters.ensure(cnt_doubles * 8), where);
-        HIPCHK(b->results.ensure((size_t)nres * sizeof(double)), where);
-        HIPCHK(b->index.ensure(b->idx_h.size() * sizeof(int) + 64 + b->res_off_h.size() * sizeof(int64_t)), where);
-        char *idx_d = (char *)b->index.p;
-        const size_t roff_pos = (b->idx_h.size() * sizeof(int) + 63) & ~(size_t)63;
+        HIPCHK(b->tabs.ensure((size_t)std::max<int64_t>(sch.tabs, 1) * tabn * ab), where);
+        HIPCHK(b->partials.ensure((size_t)sch.rows * kSlots * sizeof(double)), where);
+        HIPCHK(b->index.ensure((size_t)nsum * sizeof(int)), where);
+        // every summed step's kSlots sums: written into pinned memory when they fit
+        const size_t sbytes = (size_t)nsum * kSlots * sizeof(double);
+        double *pin = (double *)b->host.ensure(sbytes, b->stream), *sums = pin;
+        if (!pin) {
+            HIPCHK(b->results.ensure(sbytes), where);
+            sums = (double *)b->results.p;
+        }
         HIPCHK(hipMemcpyAsync(b->steps.p, b->steps_h.data(), sizeof(BatchStep) * nsteps, hipMemcpyHostToDevice,
                               b->stream), where);
-        HIPCHK(hipMemcpyAsync(idx_d, b->idx_h.data(), b->idx_h.size() * sizeof(int), hipMemcpyHostToDevice, b->stream),
-               where);
-        HIPCHK(hipMemcpyAsync(idx_d + roff_pos, b->res_off_h.data(), b->res_off_h.size() * sizeof(int64_t),
-                              hipMemcpyHostToDevice, b->stream), where);
-        hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((cnt_doubles + 255) / 256)), dim3(256), 0, b->stream,
-                           (double *)b->counters.p, (int)cnt_doubles);
-        HIPCHK(hipGetLastError(), where);
-        hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((nres + 255) / 256)), dim3(256), 0, b->stream,
-                           (double *)b->results.p, (int)nres);
-        HIPCHK(hipGetLastError(), where);
-        HIPCHK(launch_batch_tables(b->prec, (const BatchStep *)b->steps.p, nsteps, b->tabs.p, b->stream), where);
+        HIPCHK(hipMemcpyAsync(b->index.p, b->summed_h.data(), (size_t)nsum * sizeof(int), hipMemcpyHostToDevice,
+                              b->stream), where);
         BatchArgs args{};
         args.steps = (const BatchStep *)b->steps.p;
-        args.nsteps = nsteps;
-        args.nitems = items;
-        args.ticket = (unsigned long long *)b->counters.p;
-        args.abort_flag = (int *)((char *)b->counters.p + 8);
-        args.done = (unsigned *)((char *)b->counters.p + 16);
+        args.items = (const BatchItem *)b->items.p;
         args.partials = (double *)b->partials.p;
         args.tabs = b->tabs.p;
-        args.spin_limit = 4000000;
-        HIPCHK(launch_batch(b->prec, args, batch_grid(b->prec), b->stream), where);
-        HIPCHK(launch_batch_reduce((const BatchStep *)b->steps.p, (const int *)idx_d, (const int *)idx_d + nidx,
-                                   (const int64_t *)(idx_d + roff_pos), (const double *)b->partials.p,
-                                   (double *)b->results.p, count, b->stream),
-               where);
-        b->res_h.assign(nres, 0.0);
-        int32_t abort_flag = 0;
-        HIPCHK(hipMemcpyAsync(b->res_h.data(), b->results.p, (size_t)nres * sizeof(double), hipMemcpyDeviceToHost,
-                              b->stream), where);
-        HIPCHK(hipMemcpyAsync(&abort_flag, args.abort_flag, 4, hipMemcpyDeviceToHost, b->stream), where);
+        HIPCHK(launch_batch_tables(b->prec, args.steps, nsteps, b->tabs.p, b->stream), where);
+        for (size_t r = 0; r < b->round_items.size(); ++r)
+            HIPCHK(launch_batch_round(b->prec, sch.fast, args, (int)r, b->round_items[r], b->stream), where);
+        HIPCHK(launch_batch_reduce(args.steps, (const int *)b->index.p, nsum, args.partials, sums, b->stream), where);
+        b->sums_h.resize((size_t)nsum * kSlots);
+        if (!pin) HIPCHK(hipMemcpyAsync(b->sums_h.data(), sums, sbytes, hipMemcpyDeviceToHost, b->stream), where);
         HIPCHK(hipStreamSynchronize(b->stream), where);
-        if (abort_flag) return fail(QS_ERR_HIP, "%s: a work item waited too long for its predecessor", where);
-        for (int c = 0; c < count; ++c) {
-            const double *r = b->res_h.data() + b->res_off_h[c];
-            const int p = b->p[c];
-            exp_c[c] = (r[1] / 10.0) / r[0];
+        if (pin) memcpy(b->sums_h.data(), pin, sbytes);
+        std::vector<double> res;
+        for (int j = 0; j < nsum;) {  // the steps of one circuit, in step order
+            const int c = b->steps_h[(size_t)b->summed_h[(size_t)j]].circuit, p = b->p[c];
+            res.assign(2 + 2 * (size_t)p, 0.0);
+            for (; j < nsum && b->steps_h[(size_t)b->summed_h[(size_t)j]].circuit == c; ++j) {
+                const BatchStep &st = b->steps_h[(size_t)b->summed_h[(size_t)j]];
+                for (int k = 0; k < kSlots; ++k)
+                    if (st.map[k] >= 0) res[(size_t)st.map[k]] += b->sums_h[(size_t)j * kSlots + k];
+            }
+            exp_c[c] = (res[1] / 10.0) / res[0];
             for (int k = 0; k < p; ++k) {
-                d_theta_zz[b->angle_off[c] + k] = r[2 + k] / r[0];
-                d_theta_x[b->angle_off[c] + k] = r[2 + p + k] / r[0];
+                d_theta_zz[b->angle_off[c] + k] = res[2 + k] / res[0];
+                d_theta_x[b->angle_off[c] + k] = res[2 + p + k] / res[0];
             }
         }
         return QS_OK;
@@ -1836,6 +1831,7 @@ int qs_batch_plan_check(int count, const qs_circuit *circuits, int prec, char *m
     const size_t total = layout_batch(&b, count, circuits, prec);
     b.mem = (void *)(uintptr_t)((uint64_t)1 << 40);  // never dereferenced
     std::vector<double> tzz(b.angle_off.back(), 0.3), tx(b.angle_off.back(), 0.4);
+    plan_batch(&b);
     const BatchSchedule sch = build_batch_schedule(&b, tzz.data(), tx.data());
     const std::vector<BatchStep> &st = b.steps_h;
     const int nsteps = (int)st.size();
@@ -1849,23 +1845,26 @@ int qs_batch_plan_check(int count, const qs_circuit *circuits, int prec, char *m
             return bad("circuit %d: buffers overlap or exceed the allocation", c);
         if (c + 1 < count && b.off_diag[c] + db > b.off_psi[c + 1]) return bad("circuits %d, %d overlap", c, c + 1);
     }
-    // items: contiguous in step order; predecessors earlier and of the same circuit
-    int64_t next = 0;
-    std::vector<int> seen(count, 0), lastk(count, -1);
+    // steps: consecutive per circuit, starting from |+>; rows contiguous in step order
+    int64_t row = 0;
+    int nsum = 0;
+    std::vector<int> seen(count, 0);
     for (int i = 0; i < nsteps; ++i) {
         const BatchStep &s = st[i];
-        if (s.item0 != next) return bad("step %d: items not contiguous", i);
-        next += s.chunks;
+        if (s.circuit < 0 || s.circuit >= count) return bad("step %d: circuit", i);
+        if (i != b.step0[s.circuit] + seen[s.circuit]) return bad("step %d: not at its circuit's place", i);
         const int64_t ntiles = (int64_t)1 << (b.n[s.circuit] - T);
         if (s.tiles_per_chunk < 1 || (int64_t)s.chunks * s.tiles_per_chunk < ntiles ||
             (int64_t)(s.chunks - 1) * s.tiles_per_chunk >= ntiles)
             return bad("step %d: chunks do not cover the tiles", i);
         if (s.pp.ntiles != ntiles) return bad("step %d: tile count", i);
-        if (s.prev != lastk[s.circuit]) return bad("step %d: predecessor %d, expected %d", i, s.prev, lastk[s.circuit]);
-        if (s.prev >= 0 && (st[s.prev].circuit != s.circuit || st[s.prev].item0 + st[s.prev].chunks > s.item0))
-            return bad("step %d: predecessor not strictly earlier", i);
-        if ((s.prev < 0) != (s.pp.init != 0 && s.kind == 0)) return bad("step %d: first step must start from |+>", i);
-        lastk[s.circuit] = i;
+        if ((seen[s.circuit] == 0) != (s.pp.init != 0 && s.kind == 0)) return bad("step %d: first step must start from |+>", i);
+        if ((s.kind >= 1) != (s.row0 >= 0)) return bad("step %d: rows", i);
+        if (s.row0 >= 0) {
+            if (s.row0 != row || nsum >= (int)b.summed_h.size() || b.summed_h[nsum] != i) return bad("step %d: rows", i);
+            row += s.chunks;
+            ++nsum;
+        }
         ++seen[s.circuit];
         const char *psi = (const char *)s.pp.psi, *dg = (const char *)s.pp.diag;
         if (psi != lo + b.off_psi[s.circuit] || s.pp.psi_out != s.pp.psi || dg != lo + b.off_diag[s.circuit] ||
@@ -1875,22 +1874,31 @@ int qs_batch_plan_check(int count, const qs_circuit *circuits, int prec, char *m
         if (s.tab_off >= 0 && (s.tab_off % tabn || s.tab_off / tabn >= sch.tabs)) return bad("step %d: table offset", i);
         for (int k = 0; k < kSlots; ++k)
             if (s.map[k] >= 2 + 2 * b.p[s.circuit]) return bad("step %d: result slot", i);
-        if (s.mode != tile_mode(s.pp, T, kBatchThreadBits)) return bad("step %d: stage mode", i);
+        if (s.mode != tile_mode(s.pp, T, sch.tb) || (sch.fast && !batch_step_fast(s)))
+            return bad("step %d: stage mode", i);
     }
-    if (next != sch.items) return bad("item count");
+    if (row != sch.rows || nsum != (int)b.summed_h.size()) return bad("row count");
     for (int c = 0; c < count; ++c) {
         const int P = (int)plan_passes(b.n[c], prec).size();
         const int fwd = b.p[c] * (P - 1) + 1;
         if (seen[c] != 2 * fwd - 1) return bad("circuit %d: %d steps, expected %d", c, seen[c], 2 * fwd - 1);
     }
-    // the reduction's per-circuit step lists and result offsets
-    const int *cstep = b.idx_h.data(), *coff = b.idx_h.data() + sch.nidx;
-    for (int c = 0; c < count; ++c) {
-        if (coff[c + 1] - coff[c] != seen[c]) return bad("circuit %d: step list", c);
-        for (int j = coff[c]; j < coff[c + 1]; ++j)
-            if (cstep[j] < 0 || cstep[j] >= nsteps || st[cstep[j]].circuit != c) return bad("circuit %d: step list entry", c);
-        if (b.res_off_h[c + 1] - b.res_off_h[c] != 2 + 2 * b.p[c]) return bad("circuit %d: result offsets", c);
+    // rounds: round r's items are exactly the chunks of step r of every circuit that has one
+    for (size_t r = 0; r < b.round_items.size(); ++r) {
+        int64_t want = 0;
+        for (int c = 0; c < count; ++c)
+            if ((int)r < seen[c]) want += st[b.step0[c]].chunks;
+        if (b.round_items[r] != want) return bad("round %d: %lld items, expected %lld", (int)r, (long long)b.round_items[r], (long long)want);
     }
+    size_t next = 0;
+    for (int i = 0; i < count; ++i) {
+        const int c = b.order[i];
+        if (i > 0 && seen[b.order[i - 1]] < seen[c]) return bad("circuit %d: out of order", c);
+        for (int k = 0; k < st[b.step0[c]].chunks; ++k, ++next)
+            if (next >= b.items_h.size() || b.items_h[next].step0 != b.step0[c] || b.items_h[next].chunk != k)
+                return bad("circuit %d: item %d", c, k);
+    }
+    if (next != b.items_h.size() || (int)b.round_items.size() != (count ? seen[b.order[0]] : 0)) return bad("item count");
 #undef bad
     return 0;
 }
@@ -1904,7 +1912,7 @@ qs_status qs_batch_free(qs_batch b)
     b->steps.release();
     b->tabs.release();
     b->partials.release();
-    b->counters.release();
+    b->items.release();
     b->results.release();
     b->index.release();
     delete b;

@@ -1,134 +1,142 @@
-// Batched forward + adjoint gradient of many circuits in one persistent
-// launch.  Each circuit runs the same pass sequence as a single circuit:
-// forward passes, the turnaround, reverse passes.  Work items (a chunk of
-// tiles of one pass of one circuit) are claimed from a global ticket counter
-// in rounds -- step r of every circuit, largest circuits first -- so a
-// circuit's previous pass has almost always finished when its next pass is
-// claimed.  A workgroup that finds it unfinished waits on that pass's
-// completion counter.  The wait only ever targets items with lower ticket
-// numbers, which running workgroups hold and finish without waiting on later
-// items, so the queue always drains; a bounded spin additionally lets every
-// wave exit (and raise a flag) should a dependency never complete.
-//
-// Memory ordering between workgroups: stores of an item are released at
-// agent scope before its completion counter is incremented, and a workgroup
-// acquires at agent scope after observing a complete predecessor.
+// Batched forward + adjoint gradient of many circuits.  Each circuit runs the
+// same pass sequence as a single circuit: forward passes, the turnaround,
+// reverse passes.  Launch r runs step r of every circuit that has one: its
+// workgroups are the items (a tile, or a few tiles of a large state) of all
+// those steps, whatever their shape.  The kernel boundary is the only
+// synchronisation.  (One persistent launch with a ticket queue and completion
+// counters, agent-scope release and acquire fences around every item, took
+// 20.6 ms instead of 13.9 for 128 circuits of 14 to 22 qubits, 79 instead of 52
+// for 512, 4.6 instead of 0.8 for 64 circuits of 14 to 17: each fence writes
+// back or drops a whole L2, and halving the items' size doubled the time.)
 #include "tiles.h"
 
 namespace qs {
 
 namespace {
 
-constexpr int TBB = kBatchThreadBits;
-
-__device__ __forceinline__ int find_step(const BatchStep *steps, int nsteps, int64_t item)
-{
-    int lo = 0, hi = nsteps - 1;  // last step with item0 <= item
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (steps[mid].item0 <= item) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
+// Kernel shapes.  FAST: every stage of the batch is in tangent form; each pass
+// runs code fixed for its shape (see pass_shape), psi and lambda are exchanged
+// one after the other through a one-tile buffer, and two workgroups share a
+// CU: 512 threads within 128 registers in complex64, 256 threads within 256 in
+// complex128 (the thread counts of the single-circuit kernels that do not
+// spill).  One workgroup's loads and barriers then overlap the other's
+// arithmetic.  Otherwise any pass runs runtime-shape code, 512 threads, one
+// workgroup per CU with a two-tile buffer.
+template <typename V, bool FAST> constexpr int batch_tb = FAST && sizeof(V) == 16 ? 8 : 9;
 
 // Tiles [t0, t1) of one step, with the stage code path of that step.
 template <typename V, int T, int MODE>
 __device__ __forceinline__ void run_item(const BatchStep &st, int64_t t0, int64_t t1, V *lds, const V *tab,
                                          double (&acc)[kSlots], int tid)
 {
-    constexpr int NR = TileCfg<V, T, TBB>::NR;
+    constexpr int TB = batch_tb<V, false>, NR = TileCfg<V, T, TB>::NR;
     const PassProg &pp = st.pp;
     if (st.kind == 0) {
         double fa[2] = {0.0, 0.0};
-        for (int64_t t = t0; t < t1; ++t) fwd_tile<V, T, TBB, MODE>(pp, t, lds, tab, fa, tid);
+        for (int64_t t = t0; t < t1; ++t) fwd_tile<V, T, TB, MODE>(pp, t, lds, tab, fa, tid);
         acc[0] = fa[0];
         acc[1] = fa[1];
     } else if (st.kind == 1) {
-        for (int64_t t = t0; t < t1; ++t) turn_tile<V, T, TBB, MODE>(pp, t, lds, acc, tid);
+        for (int64_t t = t0; t < t1; ++t) turn_tile<V, T, TB, MODE>(pp, t, lds, acc, tid);
     } else {
         for (int64_t t = t0; t < t1; ++t) {
             V p[NR], l[NR];
             int32_t dg[NR];
-            if (pp.has_phase) rev_load_diag<V, T, TBB>(pp, t, dg, tid);
-            rev_load_vectors<V, T, TBB>(pp, t, p, l, tid);
-            rev_tile<V, T, TBB, MODE>(pp, t, p, l, dg, lds, tab, acc, tid);
+            if (pp.has_phase) rev_load_diag<V, T, TB>(pp, t, dg, tid);
+            rev_load_vectors<V, T, TB>(pp, t, p, l, tid);
+            rev_tile<V, T, TB, MODE>(pp, t, p, l, dg, lds, tab, acc, tid);
         }
     }
 }
 
-template <typename V, int T>
-__global__ void __launch_bounds__(1 << TBB) batch_kernel(BatchArgs a)
+// The same in tangent form, with code fixed for each shape.
+template <typename V, int T, int TB, int SH>
+__device__ __forceinline__ void fwd_tiles(const PassProg &pp, int64_t t0, int64_t t1, V *lds, const V *tab, int tid)
 {
-    using Cfg = TileCfg<V, T, TBB>;
-    constexpr int NT = Cfg::NT;
-    __shared__ V lds[2 << T];  // two tiles for the reverse passes
+    double fa[2] = {0.0, 0.0};  // no readout: the turnaround takes the last pass
+    for (int64_t t = t0; t < t1; ++t) fwd_tile<V, T, TB, kModeTan, SH>(pp, t, lds, tab, fa, tid);
+}
+
+template <typename V, int T, int TB, int SH>
+__device__ __forceinline__ void rev_tiles(const PassProg &pp, int64_t t0, int64_t t1, V *lds, const V *tab,
+                                          double (&acc)[kSlots], int tid)
+{
+    constexpr int NR = TileCfg<V, T, TB>::NR;
+    constexpr bool LATE = SH == (kShPre | kShPhase | kShPost);  // within the registers (see adjoint_kernel)
+    for (int64_t t = t0; t < t1; ++t) {
+        V p[NR], l[NR];
+        int32_t dg[NR];
+        if (!LATE && (SH & kShPhase)) rev_load_diag<V, T, TB>(pp, t, dg, tid);
+        rev_load_vectors<V, T, TB>(pp, t, p, l, tid);
+        rev_tile<V, T, TB, kModeTan, SH, false, LATE>(pp, t, p, l, dg, lds, tab, acc, tid);
+    }
+}
+
+template <typename V, int T>
+__device__ __forceinline__ void run_item_fast(const BatchStep &st, int64_t t0, int64_t t1, V *lds, const V *tab,
+                                              double (&acc)[kSlots], int tid)
+{
+    constexpr int TB = batch_tb<V, true>, NR = TileCfg<V, T, TB>::NR;
+    constexpr int kFirst = kShInit | kShPhase | kShPost, kJunc = kShPre | kShPhase | kShPost;
+    const PassProg &pp = st.pp;
+    const int sh = __builtin_amdgcn_readfirstlane(pass_shape(pp));
+    if (st.kind == 0) {
+        if (sh == kFirst) fwd_tiles<V, T, TB, kFirst>(pp, t0, t1, lds, tab, tid);
+        else if (sh == kJunc) fwd_tiles<V, T, TB, kJunc>(pp, t0, t1, lds, tab, tid);
+        else fwd_tiles<V, T, TB, kShPost>(pp, t0, t1, lds, tab, tid);
+    } else if (st.kind == 1) {
+        for (int64_t t = t0; t < t1; ++t) {
+            V p[NR];
+            int32_t dg[NR];
+            turn_load_diag<V, T, TB>(pp, t, dg, tid);
+            turn_load<V, T, TB>(pp, t, p, tid);
+            turn_compute<V, T, TB, kModeTan, false>(pp, t, p, dg, lds, acc, tid);
+        }
+    } else {
+        if (sh == kFirst) rev_tiles<V, T, TB, kFirst>(pp, t0, t1, lds, tab, acc, tid);
+        else if (sh == kJunc) rev_tiles<V, T, TB, kJunc>(pp, t0, t1, lds, tab, acc, tid);
+        else rev_tiles<V, T, TB, kShPost>(pp, t0, t1, lds, tab, acc, tid);
+    }
+}
+
+// Workgroup b of launch `round` takes item i of the first nitems.  Workgroups
+// go to XCDs round-robin; runs of kBatchRun consecutive items go to one XCD, so
+// that neighbouring tiles, whose 64-byte runs share 128-byte lines, share an
+// L2, while each XCD still gets items of every circuit (the circuits of a
+// launch may be at passes of very different cost).
+constexpr int kBatchRun = 16;
+
+template <typename V, int T, bool FAST>
+__global__ void __launch_bounds__((1 << batch_tb<V, FAST>), (!FAST ? 1 : batch_tb<V, FAST> == 9 ? 4 : 2))
+    batch_kernel(BatchArgs a, int round, int64_t nitems)
+{
+    constexpr int NT = 1 << batch_tb<V, FAST>;
+    __shared__ V lds[(FAST ? 1 : 2) << T];
     __shared__ V tab[kTabMax];
     __shared__ double red[kSlots * (NT / 64)];
-    __shared__ int64_t s_item;
-    __shared__ int s_step, s_ok;
     const int tid = threadIdx.x;
-    int tab_step = -1;
-    const V *tabs = reinterpret_cast<const V *>(a.tabs);
-    const BatchStep *__restrict__ steps = a.steps;
-
-    for (;;) {
-        if (tid == 0) {
-            const int64_t item = (int64_t)atomicAdd(a.ticket, 1ull);
-            int ok = 1, si = 0;
-            if (item < a.nitems) {
-                si = find_step(steps, a.nsteps, item);
-                const int prev = steps[si].prev;
-                if (prev >= 0) {
-                    const unsigned need = (unsigned)steps[prev].chunks;
-                    int64_t spins = 0;
-                    while (__hip_atomic_load(&a.done[prev], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
-                        if (__hip_atomic_load(a.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-                            ++spins > a.spin_limit) {
-                            __hip_atomic_store(a.abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            ok = 0;
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(8);
-                    }
-                }
-            }
-            s_item = item;
-            s_step = si;
-            s_ok = ok;
-        }
+    const int64_t k = blockIdx.x >> 3;
+    const int64_t item = ((k / kBatchRun) * 8 + (blockIdx.x & 7)) * kBatchRun + k % kBatchRun;
+    if (item >= nitems) return;
+    const BatchItem it = a.items[item];
+    const BatchStep &st = a.steps[__builtin_amdgcn_readfirstlane(it.step0) + round];
+    const PassProg &pp = st.pp;
+    const int64_t t0 = (int64_t)__builtin_amdgcn_readfirstlane(it.chunk) * st.tiles_per_chunk;
+    const int64_t t1 = t0 + st.tiles_per_chunk < pp.ntiles ? t0 + st.tiles_per_chunk : pp.ntiles;
+    if (pp.has_phase) {
+        load_phase_table(tab, reinterpret_cast<const V *>(a.tabs) + st.tab_off, pp.phase_levels, tid, NT);
         __syncthreads();
-        // values shared through LDS are uniform; readfirstlane tells the
-        // compiler so, keeping the step's descriptor in scalar registers
-        const int64_t item = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(s_item >> 32)) << 32) |
-                                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(s_item & 0xffffffff)));
-        const int ok = __builtin_amdgcn_readfirstlane(s_ok);
-        if (item >= a.nitems || !ok) break;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        const int si = __builtin_amdgcn_readfirstlane(s_step);
-        const BatchStep &st = steps[si];
-        const PassProg &pp = st.pp;
-        if (pp.has_phase && si != tab_step) {
-            load_phase_table(tab, tabs + st.tab_off, pp.phase_levels, tid, NT);
-            __syncthreads();
-            tab_step = si;
-        }
-        const int64_t chunk = item - st.item0;
-        const int64_t t0 = chunk * st.tiles_per_chunk;
-        const int64_t t1 = t0 + st.tiles_per_chunk < pp.ntiles ? t0 + st.tiles_per_chunk : pp.ntiles;
-        double acc[kSlots] = {0.0, 0.0, 0.0, 0.0};
-        if (st.mode == kModeTan) run_item<V, T, kModeTan>(st, t0, t1, lds, tab, acc, tid);
-        else run_item<V, T, kModeGeneral>(st, t0, t1, lds, tab, acc, tid);
-        block_sum(acc, red, tid, NT);
-        if (tid == 0) {
+    }
+    double acc[kSlots] = {0.0, 0.0, 0.0, 0.0};
+    if constexpr (FAST) run_item_fast<V, T>(st, t0, t1, lds, tab, acc, tid);
+    else if (st.mode == kModeTan) run_item<V, T, kModeTan>(st, t0, t1, lds, tab, acc, tid);
+    else run_item<V, T, kModeGeneral>(st, t0, t1, lds, tab, acc, tid);
+    if (st.kind == 0) return;
+    block_sum(acc, red, tid, NT);
+    if (tid == 0) {
+        double *row = a.partials + (st.row0 + it.chunk) * kSlots;
 #pragma unroll
-            for (int k = 0; k < kSlots; ++k) a.partials[item * kSlots + k] = acc[k];
-        }
-        // every thread's stores (and the partial sums) are released before the
-        // item is counted as done
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        __syncthreads();
-        if (tid == 0) __hip_atomic_fetch_add(&a.done[si], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int j = 0; j < kSlots; ++j) row[j] = acc[j];
     }
 }
 
@@ -145,27 +153,22 @@ __global__ void __launch_bounds__(256) batch_table_kernel(const BatchStep *steps
     build_phase_table(tabs + st.tab_off, st.pp.phase_levels, st.pp.theta_zz, st.pp.W, f, threadIdx.x, 256);
 }
 
-// One workgroup per circuit, fixed order: steps in the listed order, items in order.
-__global__ void __launch_bounds__(256) batch_reduce_kernel(const BatchStep *steps, const int *cstep,
-                                                           const int *cstep_off, const int64_t *res_off,
-                                                           const double *partials, double *res)
+// One workgroup per step that writes sums: they go to sums[kSlots * its number
+// among those steps], added up in a fixed order.
+__global__ void __launch_bounds__(256) batch_reduce_kernel(const BatchStep *steps, const int *summed,
+                                                           const double *partials, double *sums)
 {
     __shared__ double red[kSlots * 4];
-    const int c = blockIdx.x;
-    for (int j = cstep_off[c]; j < cstep_off[c + 1]; ++j) {
-        const BatchStep &st = steps[cstep[j]];
-        double acc[kSlots] = {0.0, 0.0, 0.0, 0.0};
-        for (int64_t i = threadIdx.x; i < st.chunks; i += 256) {
+    const BatchStep &st = steps[summed[blockIdx.x]];
+    double acc[kSlots] = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t i = threadIdx.x; i < st.chunks; i += 256) {
 #pragma unroll
-            for (int k = 0; k < kSlots; ++k) acc[k] += partials[(st.item0 + i) * kSlots + k];
-        }
-        block_sum(acc, red, threadIdx.x, 256);
-        if (threadIdx.x == 0) {
+        for (int k = 0; k < kSlots; ++k) acc[k] += partials[(st.row0 + i) * kSlots + k];
+    }
+    block_sum(acc, red, threadIdx.x, 256);
+    if (threadIdx.x == 0) {
 #pragma unroll
-            for (int k = 0; k < kSlots; ++k)
-                if (st.map[k] >= 0) res[res_off[c] + st.map[k]] += acc[k];
-        }
-        __syncthreads();
+        for (int k = 0; k < kSlots; ++k) sums[(int64_t)blockIdx.x * kSlots + k] = acc[k];
     }
 }
 
@@ -173,18 +176,30 @@ __global__ void __launch_bounds__(256) batch_reduce_kernel(const BatchStep *step
 
 int batch_table_entries() { return kTabMax; }
 
-int64_t batch_grid(int prec)
+namespace {
+// f(kernel, threads) for the batch kernel of a precision and shape.
+template <typename F>
+auto with_batch_kernel(int prec, bool fast, F &&f)
 {
-    int dev = 0, cus = 256, per_cu = 1;
-    if (hipGetDevice(&dev) == hipSuccess)
-        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (prec == 0)
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel<float2, kTileBitsC64>, 1 << TBB, 0);
-    else
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel<double2, kTileBitsC128>, 1 << TBB,
-                                                           0);
-    if (per_cu < 1) per_cu = 1;
-    return (int64_t)cus * per_cu;
+        return fast ? f(batch_kernel<float2, kTileBitsC64, true>, 1 << batch_tb<float2, true>)
+                    : f(batch_kernel<float2, kTileBitsC64, false>, 1 << batch_tb<float2, false>);
+    return fast ? f(batch_kernel<double2, kTileBitsC128, true>, 1 << batch_tb<double2, true>)
+                : f(batch_kernel<double2, kTileBitsC128, false>, 1 << batch_tb<double2, false>);
+}
+}  // namespace
+
+int batch_thread_bits(int prec, bool fast)
+{
+    if (prec == 0) return fast ? batch_tb<float2, true> : batch_tb<float2, false>;
+    return fast ? batch_tb<double2, true> : batch_tb<double2, false>;
+}
+
+bool batch_step_fast(const BatchStep &s)
+{
+    const int sh = pass_shape(s.pp);
+    return s.mode == kModeTan &&
+           (sh == kShPost || sh == (kShInit | kShPhase | kShPost) || sh == (kShPre | kShPhase | kShPost));
 }
 
 hipError_t launch_batch_tables(int prec, const BatchStep *steps, int nsteps, void *tabs, hipStream_t st)
@@ -196,20 +211,19 @@ hipError_t launch_batch_tables(int prec, const BatchStep *steps, int nsteps, voi
     return hipGetLastError();
 }
 
-hipError_t launch_batch(int prec, const BatchArgs &a, int64_t grid, hipStream_t st)
+hipError_t launch_batch_round(int prec, bool fast, const BatchArgs &a, int round, int64_t nitems, hipStream_t st)
 {
-    if (prec == 0)
-        hipLaunchKernelGGL((batch_kernel<float2, kTileBitsC64>), dim3((unsigned)grid), dim3(1 << TBB), 0, st, a);
-    else
-        hipLaunchKernelGGL((batch_kernel<double2, kTileBitsC128>), dim3((unsigned)grid), dim3(1 << TBB), 0, st, a);
-    return hipGetLastError();
+    const int64_t per = 8 * kBatchRun, grid = (nitems + per - 1) / per * per;
+    return with_batch_kernel(prec, fast, [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, st, a, round, nitems);
+        return hipGetLastError();
+    });
 }
 
-hipError_t launch_batch_reduce(const BatchStep *steps, const int *cstep, const int *cstep_off, const int64_t *res_off,
-                               const double *partials, double *res, int ncircuits, hipStream_t st)
+hipError_t launch_batch_reduce(const BatchStep *steps, const int *summed, int count, const double *partials,
+                               double *sums, hipStream_t st)
 {
-    hipLaunchKernelGGL(batch_reduce_kernel, dim3(ncircuits), dim3(256), 0, st, steps, cstep, cstep_off, res_off,
-                       partials, res);
+    hipLaunchKernelGGL(batch_reduce_kernel, dim3((unsigned)count), dim3(256), 0, st, steps, summed, partials, sums);
     return hipGetLastError();
 }
 

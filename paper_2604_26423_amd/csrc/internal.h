@@ -237,45 +237,44 @@ int tile_mode(const PassProg &pp, int T, int tb);
 int64_t pass_grid(int prec, int adjoint, int64_t ntiles);
 int64_t tile_grid(int prec, int adjoint, const PassProg &pp);
 
-// ---- batched circuits: one persistent launch over a ticket queue ----
-constexpr int kBatchThreadBits = 9;   // batched tile kernels: 512 threads
+// ---- batched circuits: one launch per round, round r = step r of every circuit ----
 
-// One pass of one circuit.  Its tiles are split into `chunks` work items; the
-// items of all steps are numbered in rounds (step r of every circuit that has
-// one), largest circuits first, and workgroups claim them in that order.
+// One pass of one circuit.  Its tiles are split into `chunks` work items.  The
+// steps of a circuit are consecutive.
 struct BatchStep {
     PassProg pp;
     int kind;             // 0 = forward pass, 1 = turnaround, 2 = reverse pass
     int mode;             // stage code path (tile_mode)
     int circuit;
-    int prev;             // previous step of the same circuit, -1 if none
-    int chunks;           // work items of this step
-    int tiles_per_chunk;
-    int map[kSlots];      // accumulator index of each partial-sum slot (-1: unused)
-    int64_t item0;        // first item number of this step
+    int chunks;           // work items of this step (the same for every step of a circuit)
+    int64_t tiles_per_chunk;
+    int map[kSlots];      // result index of each partial-sum slot (-1: unused)
+    int64_t row0;         // first row of partial sums, -1 if none (forward passes)
     int64_t tab_off;      // offset of this step's phase table (entries), -1 if none
+};
+
+// Work item: chunk `chunk` of the circuit whose steps begin at step0.  Items
+// are listed circuit by circuit, the circuits with the most steps first, so
+// that the items of a round are the first ones.
+struct BatchItem {
+    int step0, chunk;
 };
 
 struct BatchArgs {
     const BatchStep *steps;
-    int nsteps;
-    int64_t nitems;
-    unsigned long long *ticket;  // next item to claim
-    unsigned *done;              // finished items per step
-    int *abort_flag;             // set when a dependency wait exceeds spin_limit
-    double *partials;            // kSlots doubles per item
+    const BatchItem *items;
+    double *partials;            // kSlots doubles per row
     void *tabs;                  // phase tables (float2 / double2)
-    int64_t spin_limit;
 };
 
+// fast: every stage in tangent form, every step one that batch_step_fast accepts (see batch.hip)
+int batch_thread_bits(int prec, bool fast);  // log2 threads its windows are planned for
+bool batch_step_fast(const BatchStep &s);
 hipError_t launch_batch_tables(int prec, const BatchStep *steps, int nsteps, void *tabs, hipStream_t st);
-hipError_t launch_batch(int prec, const BatchArgs &a, int64_t grid, hipStream_t st);
-int64_t batch_grid(int prec);
-// Fixed-order per-circuit reduction: for circuit c, res[res_off[c] + map[k]] +=
-// sum over its steps' items of slot k (steps listed in cstep[cstep_off[c]..]).
-hipError_t launch_batch_reduce(const BatchStep *steps, const int *cstep, const int *cstep_off,
-                               const int64_t *res_off, const double *partials, double *res, int ncircuits,
-                               hipStream_t st);
+hipError_t launch_batch_round(int prec, bool fast, const BatchArgs &a, int round, int64_t nitems, hipStream_t st);
+// sums[kSlots * j + k] = slot k of step summed[j], over its items in a fixed order, j < count.
+hipError_t launch_batch_reduce(const BatchStep *steps, const int *summed, int count, const double *partials,
+                               double *sums, hipStream_t st);
 int batch_table_entries();
 
 // Single-workgroup kernels for n <= T: a chunk of up to kSmallMaxLayers layers.

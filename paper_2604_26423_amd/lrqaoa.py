@@ -307,7 +307,7 @@ def expect_c(gammas, betas, sim: Simulator, convention: str = "paper", mode: str
 
 class Batch:
     """Many LR-QAOA circuits (own instance, depth and angles each) whose forward
-    circuits and adjoint gradients run in one persistent kernel launch."""
+    circuits and adjoint gradients run together, one launch per pass."""
 
     def __init__(self, instances, precision: str = "c64", stream=None):
         """instances: sequence of (w_tenths, p)."""
