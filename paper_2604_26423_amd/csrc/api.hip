@@ -1784,6 +1784,7 @@ qs_status qs_noise_run(qs_noise h, int p, const double *theta_zz, const double *
         np.n = h->n;
         np.p = p;
         np.levels = levels;
+        np.direct = noise_direct(h->W, levels);
         np.amp0 = std::sqrt(std::ldexp(1.0, -h->n));
         HIPCHK(launch_noise(h->prec, tangent ? 1 : 0, np, ntraj, h->stream), where);
         return QS_OK;

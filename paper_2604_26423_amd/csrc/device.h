@@ -502,6 +502,44 @@ __device__ __forceinline__ void exchange2(V (&a)[NR], V (&b)[NR], V *lds, int fr
     }
 }
 
+// Index bits held by a lane.  A butterfly on index bit B takes the partner's
+// value from the lane that holds the index with bit B flipped.  One lane
+// permutation each reaches lane ^ 1, ^ 2 (quad permutations), ^ 7 (half-row
+// mirror) and ^ 8 (row rotation by 8), while ^ 4 would take two dependent
+// ones; so index bit 2 toggles lane bits 0, 1 and 2 (n = 12 trajectories: 1380
+// us with ^ 4, 1125 with ^ 7).
+__host__ __device__ __forceinline__ constexpr uint32_t lane_index(uint32_t lane)
+{
+    return lane ^ (((lane >> 2) & 1u) * 3u);
+}
+
+// Value of the lane whose index (lane_index) differs in bit B.
+template <int B>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x)
+{
+    if constexpr (B < 4) {
+        constexpr int ctrl = B == 0 ? 0xB1 : B == 1 ? 0x4E : B == 2 ? 0x141 : 0x128;
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, ctrl, 0xF, 0xF, true);
+    } else if constexpr (B == 4) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (threadIdx.x & 16) ? r[0] : r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return (threadIdx.x & 32) ? r[0] : r[1];
+    }
+}
+template <int B>
+__device__ __forceinline__ float lane_xor(float x) { return __uint_as_float(lane_xor<B>(__float_as_uint(x))); }
+template <int B>
+__device__ __forceinline__ double lane_xor(double x)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint64_t lo = lane_xor<B>((uint32_t)u), hi = lane_xor<B>((uint32_t)(u >> 32));
+    return __longlong_as_double((long long)(hi << 32 | lo));
+}
+template <int B, typename V>
+__device__ __forceinline__ V lane_xor_v(V a) { return V{lane_xor<B>(a.x), lane_xor<B>(a.y)}; }
+
 // Deterministic workgroup sum of NV doubles (fixed shuffle tree, then waves in
 // order).  Result valid in thread 0.  `red` holds NV * (blockDim/64) doubles.
 template <int NV>

@@ -303,13 +303,13 @@ hipError_t launch_small_adjoint(int prec, const SmallProg &sp, hipStream_t st);
 
 // ---- noisy trajectories (noise.hip): one workgroup per trajectory ----
 constexpr int kNoiseMaxQubits = 12;
-constexpr int kNoiseChunk = 32;  // layers whose error draws are made together
+constexpr int kNoiseChunk = 16;  // layers whose error draws are made together
 
 struct NoiseProg {
     const int32_t *diag;     // 2^n cut values (tenths)
     const int32_t *edges;    // per edge: a | b << 4 | w << 8 (a < b, w in tenths)
     const double *layers;    // per layer: theta_zz, u or cos, 0 or sin, mixer factor
-    void *tabs;              // per layer: kTabMax phase-table entries (float2 / double2)
+    void *tabs;              // per layer: noise_table_entries() phase-table entries (float2 / double2)
     double *exp_c;           // [ntraj] normalized <C> in units
     double *norm;            // [ntraj] or null
     int32_t *nerr;           // [ntraj] non-identity errors, or null
@@ -317,11 +317,13 @@ struct NoiseProg {
     uint64_t traj0, seed, thr;
     int64_t W;
     int n, p, levels;
+    int direct;              // the tables hold a factor per cut value (noise_direct)
     double amp0;
 };
 
 int noise_threads(int n);
 int noise_table_entries();  // phase-table entries per layer
+int noise_direct(int64_t W, int levels);
 hipError_t launch_noise(int prec, int tangent, const NoiseProg &np, int64_t ntraj, hipStream_t st);
 
 // Elementwise and readout kernels.

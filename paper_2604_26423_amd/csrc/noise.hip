@@ -23,6 +23,17 @@
 //   K = (W - 2 C(y)) - 2 (W_F - 2 C_F(y)),  y = x ^ m,
 // C_F the cut of y over the flipped gates (a short list, empty without
 // errors).  The mixer is unchanged.
+//
+// Nothing of this reaches HBM; the vector units bound it (about 640
+// instructions per wave and layer at n = 12, 384 of them the RX updates), then
+// LDS.  So the layer is kept short: a register's cut values stay in registers
+// (reloaded when the frame moves), a layer without flips takes its phase from
+// one table entry per cut value, four qubits are updated across lanes instead
+// of through a second exchange, and the exchange has one barrier.  20,000
+// trajectories, p = 10, eps = 0.003, before (diagonal and two-level table in
+// LDS, two exchanges of two barriers) and now: n = 12 complex64 1546 -> 1120
+// us, complex128 3203 -> 1971, n = 11 669 -> 525, n = 9 186 -> 151.  Registers
+// for three workgroups per CU instead of four: 8% slower.
 #include "tiles.h"
 
 namespace qs {
@@ -61,20 +72,29 @@ template <int N> struct NoiseCfg {
     static constexpr int RB = N - TB;
     static constexpr int NR = 1 << RB, NT = 1 << TB;
     static constexpr int WL = NT < 64 ? NT : 64;  // lanes of the bookkeeping wave
-    static constexpr int NW = (N + RB - 1) / RB;  // register windows per layer
+    static constexpr int NW = (N + RB - 1) / RB;  // groups of RB qubits, see mid
     static constexpr int G = N * (N - 1) / 2;     // gates per cost layer
-    static constexpr int pos(int j) { return j * RB < N - RB ? j * RB : N - RB; }
-    static constexpr uint32_t win(int j) { return ((1u << RB) - 1u) << pos(j); }
-    // register-bit targets of window j when the windows run in ascending
-    // (ASC) or descending order: its qubits not covered by an earlier window
-    static constexpr uint32_t targets(int j, bool asc)
+    // Two layouts of the index bits.  The top layout holds bits [HI, N) in
+    // registers, the low layout bits [0, RB); the M bits between them are
+    // thread bits 0 .. M - 1 (lanes: M <= 4) in both, and the other window's
+    // bits the thread bits above.  (n = 3: the windows share a bit, M = 0 and
+    // the top layout's thread bit is bit 0.)
+    static constexpr int HI = N - RB;
+    static constexpr int M = N > 2 * RB ? N - 2 * RB : 0;
+    static constexpr int XB = TB - M;             // thread bits of the other window
+    // The i-th middle qubit of a layer: ascending, or in groups of RB from the
+    // highest down and ascending within each (the groups begin at multiples of
+    // RB, the last at HI): the order in which the state is rounded.
+    static constexpr int mid(int i, bool asc)
     {
-        uint32_t done = 0;
-        if (asc)
-            for (int i = 0; i < j; ++i) done |= win(i);
-        else
-            for (int i = NW - 1; i > j; --i) done |= win(i);
-        return (win(j) & ~done) >> pos(j);
+        if (asc) return RB + i;
+        int at = 0;
+        for (int j = NW - 2; j >= 1; --j) {
+            const int lo = j * RB, hi = lo + RB < HI ? lo + RB : HI;
+            for (int q = lo; q < hi; ++q, ++at)
+                if (at == i) return q;
+        }
+        return RB;
     }
 };
 
@@ -94,13 +114,37 @@ __device__ __forceinline__ void noise_sum(double (&x)[2], double *red, int tid)
     }
 }
 
-// LDS slot of cut value x: the low 4 bits are XORed with bits 6..9, so that
-// the 64 lanes of a wave reading one register's values -- consecutive x in
-// the layouts whose window holds the high bits, x 16 (or 2^RB) apart in the
-// layout whose window holds the low bits, both XORed with the frame -- hit
-// 64 different banks.
-// The map is linear over XOR: slot(a ^ b) = slot(a) ^ slot(b).
-__host__ __device__ constexpr int dg_slot(uint32_t x) { return (int)(x ^ ((x >> 6) & 15u)); }
+// Index bits of register r in the low or the top layout, and the LDS slot
+// through which it passes to the other one: the same slot, so that a thread
+// writes exactly the slots that it has read last (one barrier per exchange).
+// Rows of 2^TB + 2^M slots put the lanes of half a wave on distinct banks
+// either way, at a constant distance from register to register.
+template <int N, bool TOP>
+__host__ __device__ __forceinline__ constexpr uint32_t noise_x(int r, int tid)
+{
+    using Cfg = NoiseCfg<N>;
+    // (the middle bits are lane bits, see lane_index)
+    const uint32_t l = (uint32_t)tid & ((1u << Cfg::M) - 1u), o = (uint32_t)tid >> Cfg::M;
+    const uint32_t m = Cfg::M > 2 ? lane_index(l) : l;
+    return TOP ? o | (m << Cfg::RB) | ((uint32_t)r << Cfg::HI) : (uint32_t)r | (m << Cfg::RB) | (o << (N - Cfg::XB));
+}
+template <int N> constexpr int kNoiseRow = (1 << NoiseCfg<N>::TB) + (1 << NoiseCfg<N>::M);
+template <int N, bool TOP>
+__host__ __device__ __forceinline__ constexpr int noise_slot(int r, int tid)
+{
+    using Cfg = NoiseCfg<N>;
+    const int m = tid & ((1 << Cfg::M) - 1), o = tid >> Cfg::M;
+    if (!TOP) return r * kNoiseRow<N> + tid;
+    // the row is the low RB index bits, the place in it the high XB ones
+    if (2 * Cfg::RB > N)  // (n = 3: the windows share a bit)
+        return (o | ((r << Cfg::HI) & ((1 << Cfg::RB) - 1))) * kNoiseRow<N> + (r >> (Cfg::RB - Cfg::XB));
+    return o * kNoiseRow<N> + (r << Cfg::M) + m;
+}
+
+// Cut values 0 .. W_t of a layer without sign flips: one table entry each, the
+// product of the two levels, when they are at most kNoiseDirect (this many let
+// four workgroups of n = 12 share a CU's LDS).
+constexpr int kNoiseDirect = 528;
 
 struct NoiseShared {
     int nf, wf, ph, cnt;
@@ -116,24 +160,84 @@ __device__ __forceinline__ V noise_phase(const V *tab, int levels, int u)
     else return phase_factor(tab, levels, u);
 }
 
-// Cost layer with its errors, then the mixer, for layer k.  The state enters
-// in the layout of the first window of this layer's order and leaves in the
-// layout of the last.
+// RX on one qubit: a register bit, or a lane bit (the partner's value through a
+// lane permutation; the same fused operations for both ends of the pair).
+template <int B, int MODE, typename V, int NR, typename R>
+__device__ __forceinline__ void noise_rx_reg(V (&v)[NR], R a, R b)
+{
+    if constexpr (MODE == kModeTan) rxt_reg_bit<B>(v, a);
+    else rx_reg_bit<B>(v, a, b);
+}
+template <int B, int MODE, typename V, int NR, typename R>
+__device__ __forceinline__ void noise_rx_lane(V (&v)[NR], R a, R b)
+{
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const V o = v[r], p = lane_xor_v<B>(o);
+        if constexpr (MODE == kModeTan) v[r] = V{fma(a, p.y, o.x), fma(-a, p.x, o.y)};
+        else v[r] = V{fma(a, o.x, b * p.y), fma(a, o.y, -(b * p.x))};
+    }
+}
+template <int N, int MODE, bool ASC, int I = 0, typename V, int NR, typename R>
+__device__ __forceinline__ void noise_mid(V (&v)[NR], R a, R b)
+{
+    using Cfg = NoiseCfg<N>;
+    if constexpr (I < Cfg::M) {
+        noise_rx_lane<Cfg::mid(I, ASC) - Cfg::RB, MODE>(v, a, b);
+        noise_mid<N, MODE, ASC, I + 1>(v, a, b);
+    }
+}
+// Register bits LO .. RB - 1.
+template <int N, int MODE, int LO, typename V, int NR, typename R>
+__device__ __forceinline__ void noise_regs(V (&v)[NR], R a, R b)
+{
+    if constexpr (LO < NoiseCfg<N>::RB) {
+        noise_rx_reg<LO, MODE>(v, a, b);
+        noise_regs<N, MODE, LO + 1>(v, a, b);
+    }
+}
+
+// The thread index, hidden from the optimizer: what the rare paths derive from
+// it is computed there and does not occupy registers through every layer.
+__device__ __forceinline__ int noise_tid(int tid)
+{
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
+// Cut values of the thread's registers in both layouts, for frame m.
+template <int N, int NR>
+__device__ __forceinline__ void noise_cuts(const int32_t *diag, uint32_t m, int tid, int32_t (&lo)[NR], int32_t (&hi)[NR])
+{
+    tid = noise_tid(tid);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        lo[r] = diag[noise_x<N, false>(r, tid) ^ m];
+        hi[r] = diag[noise_x<N, true>(r, tid) ^ m];
+    }
+}
+
+// Cost layer with its errors, then the mixer, for layer k.  Ascending layers
+// take the state from the low layout to the top one, the others back.
 template <typename V, int N, int MODE, int LV, bool ASC>
 __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[NoiseCfg<N>::NR], V *lds,
-                                            const int32_t *dg, V *tab, uint8_t *codes, uint32_t *fm, int *fw,
-                                            NoiseShared &sh, uint32_t &m, int &phi, int &nerr, double &fprev,
-                                            int tid)
+                                            int32_t (&clo)[NoiseCfg<N>::NR], int32_t (&chi)[NoiseCfg<N>::NR],
+                                            V *tab, uint8_t *codes, uint8_t *drawn, uint32_t *fm, int *fw,
+                                            NoiseShared &sh, uint32_t &m, int &phi, int &nerr, double &fprev, int tid)
 {
     using Cfg = NoiseCfg<N>;
     using R = typename Real<V>::T;
-    constexpr int RB = Cfg::RB, NR = Cfg::NR, NT = Cfg::NT, G = Cfg::G, WL = Cfg::WL, NW = Cfg::NW;
+    constexpr int RB = Cfg::RB, NR = Cfg::NR, NT = Cfg::NT, G = Cfg::G, WL = Cfg::WL;
     const double *lay = np.layers + 4 * k;
+    const int at = k % kNoiseChunk;
 
-    // draws of the next chunk of layers (counter-based: any order gives the same codes)
-    if (k % kNoiseChunk == 0) {
+    // draws of the next chunk of layers (counter-based: any order gives the
+    // same codes), and whether a layer has any error
+    if (at == 0) {
         const int len = np.p - k < kNoiseChunk ? np.p - k : kNoiseChunk;
         __syncthreads();  // the previous chunk's codes are no longer read
+        for (int i = tid; i < len; i += NT) drawn[i] = 0;
+        __syncthreads();
         for (int i = tid; i < len * G; i += NT) {
             uint8_t c = 0;
             if (np.thr != 0) {
@@ -142,28 +246,26 @@ __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[N
                 c = (r0 >> 11) < np.thr ? (uint8_t)(r1 & 15u) : (uint8_t)0;
             }
             codes[i] = c;
+            if (c) drawn[i / G] = 1;
         }
+        __syncthreads();
     }
-    __syncthreads();  // codes visible; the previous layer's table and F reads done
+    const bool errs = __builtin_amdgcn_readfirstlane(drawn[at]) != 0;
 
-    // phase table of this layer (the same for every trajectory, built by noise_table_kernel)
-    {
-        const V *src = reinterpret_cast<const V *>(np.tabs) + (size_t)k * kTabMax;
-        const int ntab = 64 * (np.levels - 1) + 128;
-        for (int i = tid; i < ntab; i += NT) tab[i] = src[i];
-    }
+    // Table of a layer without flips (the same for every trajectory, built by
+    // noise_table_kernel).  The last reads of the previous layer's table and
+    // flags lie before that layer's exchange.
+    const V *two = reinterpret_cast<const V *>(np.tabs) + (size_t)k * (kTabMax + kNoiseDirect);
+    if (np.direct)
+        for (int i = tid; i <= (int)np.W; i += NT) tab[i] = two[kTabMax + i];
 
     // the layer's errors, moved to its end (one wave, gates in order)
-    if (tid < WL) {
+    if (errs && tid < WL) {
         const int lane = tid;
-        const uint8_t *cl = codes + (k % kNoiseChunk) * G;
+        const uint8_t *cl = codes + at * G;
         uint32_t carry = 0, ez = 0;
         int nf = 0, wf = 0, ph = 0, cnt = 0;
-        // most layers draw no error: then every sum below stays zero
-        bool any = false;
-        for (int base = 0; base < G; base += WL) any |= base + lane < G && cl[base + lane] != 0;
-        const int first = __ballot(any) != 0 ? 0 : G;
-        for (int base = first; base < G; base += WL) {
+        for (int base = 0; base < G; base += WL) {
             const int e = base + lane;
             const bool valid = e < G;
             const int code = valid ? cl[e] : 0;
@@ -184,9 +286,9 @@ __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[N
             const bool flip = valid && (__popc(before & emask) & 1);
             const uint64_t bal = __ballot(flip);
             if (flip) {
-                const int at = nf + __popcll(bal & ((1ull << lane) - 1ull));
-                fm[at] = emask;
-                fw[at] = wt;
+                const int to = nf + __popcll(bal & ((1ull << lane) - 1ull));
+                fm[to] = emask;
+                fw[to] = wt;
             }
             nf += __popcll(bal);
             int sw = flip ? wt : 0;
@@ -218,74 +320,112 @@ __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[N
     }
     __syncthreads();
 
-    const int nf = __builtin_amdgcn_readfirstlane(sh.nf);
-    const int wf = __builtin_amdgcn_readfirstlane(sh.wf);
-    const uint32_t ez = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ez);
-    const uint32_t ex = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ex);
-
-    // cost phase, in the layout of this layer's first window
-    constexpr int s0 = ASC ? Cfg::pos(0) : Cfg::pos(NW - 1);
-    const int xb = win_elem(0, tid, s0, RB);
-    const int u0 = 2 * (int)np.W - wf;
-    int cf[NR];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) cf[r] = 0;
-    for (int f = 0; f < nf; ++f) {
-        const uint32_t mk = fm[f];
-        const int wk = fw[f];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const uint32_t y = (uint32_t)(xb | (r << s0)) ^ m;
-            cf[r] += (__popc(y & mk) & 1) ? wk : 0;
-        }
-    }
+    // cost phase, in the layout that the layer starts from
+    const auto c = [&](int r) {
+        if constexpr (ASC) return clo[r];
+        else return chi[r];
+    };
+    const int nf = errs ? __builtin_amdgcn_readfirstlane(sh.nf) : 0;
     V f[NR];
-    const int db = dg_slot((uint32_t)xb ^ m);  // per-thread part of the slot; the register part is a constant
+    if (nf == 0 && np.direct) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
-        f[r] = noise_phase<V, LV>(tab, np.levels, u0 - dg[db ^ dg_slot((uint32_t)r << s0)] + 2 * cf[r]);
-    if (ez != 0) {  // Z components of the layer's errors (rare): signs
+        for (int r = 0; r < NR; ++r) f[r] = tab[c(r)];
+    } else {
+        int cf[NR];
+        const int tf = noise_tid(tid);
 #pragma unroll
-        for (int r = 0; r < NR; ++r)
-            if (__popc((uint32_t)(xb | (r << s0)) & ez) & 1) f[r] = V{-f[r].x, -f[r].y};
+        for (int r = 0; r < NR; ++r) cf[r] = 0;
+        for (int i = 0; i < nf; ++i) {
+            const uint32_t mk = fm[i];
+            const int wk = fw[i];
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                cf[r] += (__popc((noise_x<N, !ASC>(r, tf) ^ m) & mk) & 1) ? wk : 0;
+        }
+        const int u0 = 2 * (int)np.W - (nf ? __builtin_amdgcn_readfirstlane(sh.wf) : 0);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) f[r] = noise_phase<V, LV>(two, np.levels, u0 - c(r) + 2 * cf[r]);
+    }
+    uint32_t ex = 0;
+    if (errs) {
+        const uint32_t ez = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ez);
+        ex = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ex);
+        if (ez != 0) {  // Z components of the layer's errors: signs
+            const int tz = noise_tid(tid);
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                if (__popc(noise_x<N, !ASC>(r, tz) & ez) & 1) f[r] = V{-f[r].x, -f[r].y};
+        }
+        phi = (phi + sh.ph + 2 * (__popc(ez & m) & 1)) & 3;
+        nerr += sh.cnt;
     }
 #pragma unroll
     for (int r = 0; r < NR; ++r) v[r] = cmul(v[r], f[r]);
-    phi = (phi + sh.ph + 2 * (__popc(ez & m) & 1)) & 3;
-    m ^= ex;
-    nerr += sh.cnt;
 
-    // mixer: RX on every qubit, window by window
+    // mixer: RX on every qubit; the registers' qubits of the starting layout,
+    // the middle ones, and after the exchange the other window's
     const R a = (R)lay[1], b = (R)lay[2];
+    noise_regs<N, MODE, 0>(v, a, b);
+    noise_mid<N, MODE, ASC>(v, a, b);
+    if constexpr (Cfg::TB > 0) {
 #pragma unroll
-    for (int jj = 0; jj < NW; ++jj) {
-        const int j = ASC ? jj : NW - 1 - jj;
-        if (jj > 0) exchange<RB>(v, lds, Cfg::pos(ASC ? j - 1 : j + 1), Cfg::pos(j), tid);
-        const uint32_t mask = Cfg::targets(j, ASC);
-        if constexpr (MODE == kModeTan) rxt_reg_all(v, mask, a);
-        else rx_reg_mask(v, mask, a, b);
+        for (int r = 0; r < NR; ++r) lds[noise_slot<N, !ASC>(r, tid)] = v[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < NR; ++r) v[r] = lds[noise_slot<N, ASC>(r, tid)];
+        // (n = 3: the windows share a qubit, already done)
+        if constexpr (ASC) noise_regs<N, MODE, (2 * RB > N ? 2 * RB - N : 0)>(v, a, b);
+        else if constexpr (2 * RB > N) noise_rx_reg<0, MODE>(v, a, b);
+        else noise_regs<N, MODE, 0>(v, a, b);
+    }
+    if (ex != 0) {  // the frame moves: so do the cut values
+        m ^= ex;
+        noise_cuts<N>(np.diag, m, tid, clo, chi);
     }
     fprev = lay[3];
 }
 
+// Norm, sum |a|^2 C and the final state: psi_true[x ^ m] = i^phi fs psi_stored[x].
+template <typename V, int N, bool TOP, int NR, typename R>
+__device__ __forceinline__ void noise_readout(const NoiseProg &np, const V (&v)[NR], const int32_t (&c)[NR], uint32_t m,
+                                              int phi, R fs, double (&acc)[2], int tid)
+{
+    V *out = np.states ? reinterpret_cast<V *>(np.states) + ((int64_t)blockIdx.x << N) : nullptr;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        V a = V{fs * v[r].x, fs * v[r].y};
+        const double pr = (double)a.x * (double)a.x + (double)a.y * (double)a.y;
+        acc[0] += pr;
+        acc[1] += pr * (double)c[r];
+        if (out) {
+            V t = a;
+            if (phi & 1) t = V{-a.y, a.x};
+            if (phi & 2) t = V{-t.x, -t.y};
+            out[noise_x<N, TOP>(r, tid) ^ m] = t;
+        }
+    }
+}
+
+// Registers for as many workgroups of n = 12 as share a CU's LDS.
 template <typename V, int N, int MODE, int LV>
-__global__ void __launch_bounds__(NoiseCfg<N>::NT) noise_kernel(NoiseProg np)
+__global__ void __launch_bounds__(NoiseCfg<N>::NT, (N < 11 ? 1 : sizeof(V) == 8 ? 4 : 2)) noise_kernel(NoiseProg np)
 {
     using Cfg = NoiseCfg<N>;
     using R = typename Real<V>::T;
-    constexpr int NR = Cfg::NR, NT = Cfg::NT, RB = Cfg::RB, NW = Cfg::NW, G = Cfg::G;
-    __shared__ V lds[1 << N];
-    __shared__ int32_t dg[1 << N];
-    __shared__ V tab[kTabMax];
+    constexpr int NR = Cfg::NR, NT = Cfg::NT, G = Cfg::G;
+    __shared__ V lds[kNoiseRow<N> << Cfg::RB];
+    __shared__ V tab[kNoiseDirect];
     __shared__ uint8_t codes[kNoiseChunk * G];
+    __shared__ uint8_t drawn[kNoiseChunk];
     __shared__ uint32_t fm[G];
     __shared__ int fw[G];
     __shared__ NoiseShared sh;
     __shared__ double red[2 * (NT < 64 ? 1 : NT / 64)];
     const int tid = threadIdx.x;
 
-    for (int i = tid; i < (1 << N); i += NT) dg[dg_slot((uint32_t)i)] = np.diag[i];
     V v[NR];
+    int32_t clo[NR], chi[NR];
+    noise_cuts<N>(np.diag, 0u, tid, clo, chi);
 #pragma unroll
     for (int r = 0; r < NR; ++r) v[r] = V{(R)np.amp0, (R)0};
     uint32_t m = 0;
@@ -294,32 +434,19 @@ __global__ void __launch_bounds__(NoiseCfg<N>::NT) noise_kernel(NoiseProg np)
 
     int k = 0;
     for (; k + 1 < np.p; k += 2) {
-        noise_layer<V, N, MODE, LV, true>(np, k, v, lds, dg, tab, codes, fm, fw, sh, m, phi, nerr, fprev, tid);
-        noise_layer<V, N, MODE, LV, false>(np, k + 1, v, lds, dg, tab, codes, fm, fw, sh, m, phi, nerr, fprev, tid);
+        noise_layer<V, N, MODE, LV, true>(np, k, v, lds, clo, chi, tab, codes, drawn, fm, fw, sh, m, phi, nerr, fprev,
+                                          tid);
+        noise_layer<V, N, MODE, LV, false>(np, k + 1, v, lds, clo, chi, tab, codes, drawn, fm, fw, sh, m, phi, nerr,
+                                           fprev, tid);
     }
-    if (k < np.p)
-        noise_layer<V, N, MODE, LV, true>(np, k, v, lds, dg, tab, codes, fm, fw, sh, m, phi, nerr, fprev, tid);
-    const int s = (np.p & 1) ? Cfg::pos(NW - 1) : Cfg::pos(0);
+    const bool top = k < np.p;
+    if (top)
+        noise_layer<V, N, MODE, LV, true>(np, k, v, lds, clo, chi, tab, codes, drawn, fm, fw, sh, m, phi, nerr, fprev,
+                                          tid);
 
-    // readout: psi_true[x ^ m] = i^phi fprev psi_stored[x]
-    const int xb = win_elem(0, tid, s, RB);
-    const R fs = (R)fprev;
     double acc[2] = {0.0, 0.0};
-    V *out = np.states ? reinterpret_cast<V *>(np.states) + ((int64_t)blockIdx.x << N) : nullptr;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const uint32_t x = (uint32_t)(xb | (r << s));
-        V a = V{fs * v[r].x, fs * v[r].y};
-        const double pr = (double)a.x * (double)a.x + (double)a.y * (double)a.y;
-        acc[0] += pr;
-        acc[1] += pr * (double)dg[dg_slot(x ^ m)];
-        if (out) {
-            V t = a;
-            if (phi & 1) t = V{-a.y, a.x};
-            if (phi & 2) t = V{-t.x, -t.y};
-            out[x ^ m] = t;
-        }
-    }
+    if (top) noise_readout<V, N, true>(np, v, chi, m, phi, (R)fprev, acc, tid);
+    else noise_readout<V, N, false>(np, v, clo, m, phi, (R)fprev, acc, tid);
     noise_sum<NT>(acc, red, tid);
     if (tid == 0) {
         np.exp_c[blockIdx.x] = acc[1] / acc[0] / 10.0;
@@ -329,14 +456,20 @@ __global__ void __launch_bounds__(NoiseCfg<N>::NT) noise_kernel(NoiseProg np)
 }
 
 // Phase table of every layer k: entry(u) = f_(k-1) exp(-i theta_zz,k (2u - 3W) / 20),
-// f_(k-1) the tangent-form factor of the previous layer's mixer (1 for k = 0).
+// f_(k-1) the tangent-form factor of the previous layer's mixer (1 for k = 0);
+// then, for cut value C of a layer without flips, the factor of u = 2W - C, as
+// the two levels give it.
 template <typename V>
 __global__ void __launch_bounds__(256) noise_table_kernel(NoiseProg np)
 {
     const int k = blockIdx.x;
     const double f = k == 0 ? 1.0 : np.layers[4 * (k - 1) + 3];
-    build_phase_table(reinterpret_cast<V *>(np.tabs) + (size_t)k * kTabMax, np.levels, -np.layers[4 * k],
-                      3 * np.W, f, threadIdx.x, 256);
+    V *tab = reinterpret_cast<V *>(np.tabs) + (size_t)k * (kTabMax + kNoiseDirect);
+    build_phase_table(tab, np.levels, -np.layers[4 * k], 3 * np.W, f, threadIdx.x, 256);
+    if (!np.direct) return;
+    __syncthreads();
+    for (int C = threadIdx.x; C <= (int)np.W; C += 256)
+        tab[kTabMax + C] = noise_phase<V, 2>(tab, np.levels, 2 * (int)np.W - C);
 }
 
 template <typename V, int MODE, int LV>
@@ -366,7 +499,9 @@ hipError_t launch_noise_v(const NoiseProg &np, int64_t ntraj, hipStream_t st)
 
 }  // namespace
 
-int noise_table_entries() { return kTabMax; }
+int noise_table_entries() { return kTabMax + kNoiseDirect; }
+
+int noise_direct(int64_t W, int levels) { return levels == 2 && W < kNoiseDirect ? 1 : 0; }
 
 int noise_threads(int n)
 {

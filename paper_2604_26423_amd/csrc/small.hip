@@ -44,39 +44,6 @@ template <int N> struct SmallCfg {
 // Phase-table entries in LDS: as many layers as fit are evaluated at once.
 template <typename V> constexpr int kSmallTab = sizeof(V) == 8 ? 3072 : 1536;
 
-// Value of the lane whose index differs in bit B.
-template <int B>
-__device__ __forceinline__ uint32_t lane_xor(uint32_t x)
-{
-    if constexpr (B == 0) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
-    } else if constexpr (B == 1) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, true);  // quad_perm [2,3,0,1]
-    } else if constexpr (B == 2) {  // half-row mirror (xor 7), then quad_perm [3,2,1,0] (xor 3)
-        const int t = __builtin_amdgcn_mov_dpp((int)x, 0x141, 0xF, 0xF, true);
-        return (uint32_t)__builtin_amdgcn_mov_dpp(t, 0x1B, 0xF, 0xF, true);
-    } else if constexpr (B == 3) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xF, 0xF, true);  // row rotate by 8
-    } else if constexpr (B == 4) {
-        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-        return (threadIdx.x & 16) ? r[0] : r[1];
-    } else {
-        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-        return (threadIdx.x & 32) ? r[0] : r[1];
-    }
-}
-template <int B>
-__device__ __forceinline__ float lane_xor(float x) { return __uint_as_float(lane_xor<B>(__float_as_uint(x))); }
-template <int B>
-__device__ __forceinline__ double lane_xor(double x)
-{
-    const uint64_t u = (uint64_t)__double_as_longlong(x);
-    const uint64_t lo = lane_xor<B>((uint32_t)u), hi = lane_xor<B>((uint32_t)(u >> 32));
-    return __longlong_as_double((long long)(hi << 32 | lo));
-}
-template <int B, typename V>
-__device__ __forceinline__ V lane_xor_v(V a) { return V{lane_xor<B>(a.x), lane_xor<B>(a.y)}; }
-
 // One half of an RX pair, a' = c a - i s b (b: the other amplitude).  Of the
 // two products of a part one is rounded and the other goes into the fused
 // multiply-add.  Which one is part of the result in complex64 (its last bit,
@@ -103,7 +70,7 @@ __device__ __forceinline__ V cmul_fma(V a, V b)
 template <int B, bool REV, typename V, int NR, typename R>
 __device__ __forceinline__ void rx_lane(V (&v)[NR], R c, R s)
 {
-    const bool hi = (threadIdx.x >> B) & 1;
+    const bool hi = (lane_index(threadIdx.x) >> B) & 1;
     const R sr = REV ? -s : s;
     const R fused = hi ? sr : c, plain = hi ? c : sr;
 #pragma unroll
@@ -220,7 +187,7 @@ template <int N, int LAYOUT>
 __device__ __forceinline__ int small_x(int r, int tid)
 {
     using Cfg = SmallCfg<N>;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = (int)lane_index(tid & 63), wave = tid >> 6;
     return LAYOUT == 1 ? lane | (wave << 6) | (r << (6 + Cfg::WB)) : lane | (r << 6) | (wave << (6 + Cfg::RB));
 }
 
