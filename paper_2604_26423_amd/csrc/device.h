@@ -446,10 +446,18 @@ __device__ __forceinline__ V &lds_at(V *lds, int byte_off)
     return *reinterpret_cast<V *>(reinterpret_cast<char *>(lds) + byte_off);
 }
 
-template <int RB, typename V>
-__device__ __forceinline__ int lds_reg_bytes(int r, int win)
+// (As in for_each_reg: the register bits' slots once per exchange, one XOR per
+// register.)
+template <int RB, typename V, int NR>
+__device__ __forceinline__ void lds_reg_bytes(int (&off)[NR], int win)
 {
-    return __builtin_amdgcn_readfirstlane(lds_slot<RB>(r << win) * (int)sizeof(V));
+    int bit[RB > 0 ? RB : 1];
+#pragma unroll
+    for (int k = 0; k < RB; ++k)
+        bit[k] = __builtin_amdgcn_readfirstlane(lds_slot<RB>(1 << (win + k))) * (int)sizeof(V);
+    off[0] = 0;
+#pragma unroll
+    for (int r = 1; r < NR; ++r) off[r] = off[r & (r - 1)] ^ bit[__builtin_ctz(r)];
 }
 
 // Byte offset of the thread's part of a layout, kept opaque so that the
@@ -469,12 +477,15 @@ __device__ __forceinline__ void exchange(V (&v)[NR], V *lds, int from, int to, i
 {
     const int tf = lds_thread_bytes<RB, V>(tid, from);
     const int tt = lds_thread_bytes<RB, V>(tid, to);
+    int off[NR];
+    lds_reg_bytes<RB, V>(off, from);
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < NR; ++r) lds_at(lds, tf ^ lds_reg_bytes<RB, V>(r, from)) = v[r];
+    for (int r = 0; r < NR; ++r) lds_at(lds, tf ^ off[r]) = v[r];
+    lds_reg_bytes<RB, V>(off, to);
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < NR; ++r) v[r] = lds_at(lds, tt ^ lds_reg_bytes<RB, V>(r, to));
+    for (int r = 0; r < NR; ++r) v[r] = lds_at(lds, tt ^ off[r]);
 }
 
 // The same move for two arrays at once through an LDS buffer of two tiles:
@@ -486,17 +497,20 @@ __device__ __forceinline__ void exchange2(V (&a)[NR], V (&b)[NR], V *lds, int fr
     V *ldb = lds + TILE;
     const int tf = lds_thread_bytes<RB, V>(tid, from);
     const int tt = lds_thread_bytes<RB, V>(tid, to);
+    int off[NR];
+    lds_reg_bytes<RB, V>(off, from);
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        const int o = tf ^ lds_reg_bytes<RB, V>(r, from);
+        const int o = tf ^ off[r];
         lds_at(lds, o) = a[r];
         lds_at(ldb, o) = b[r];
     }
+    lds_reg_bytes<RB, V>(off, to);
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        const int o = tt ^ lds_reg_bytes<RB, V>(r, to);
+        const int o = tt ^ off[r];
         a[r] = lds_at(lds, o);
         b[r] = lds_at(ldb, o);
     }
