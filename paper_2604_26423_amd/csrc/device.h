@@ -527,6 +527,16 @@ __host__ __device__ __forceinline__ constexpr uint32_t lane_index(uint32_t lane)
     return lane ^ (((lane >> 2) & 1u) * 3u);
 }
 
+// Hides the vector from the optimizer, which would otherwise keep conversions of
+// its parts in registers from one use to the next, or move the uses into each
+// other.
+template <typename V, int NR>
+__device__ __forceinline__ void pin_regs(V (&v)[NR])
+{
+#pragma unroll
+    for (int r = 0; r < NR; ++r) asm volatile("" : "+v"(v[r].x), "+v"(v[r].y));
+}
+
 // Value of the lane whose index (lane_index) differs in bit B.
 template <int B>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t x)

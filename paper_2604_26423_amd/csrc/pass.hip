@@ -394,19 +394,19 @@ void launch_adjoint_s(int prec, const PassProg &pp, int64_t grid, hipStream_t st
     else hipLaunchKernelGGL((adjoint_kernel<double2, kTileBitsC128, AT, TURN, MODE, SH, ONE>), g, b, 0, st, pp);
 }
 
-// complex64 one-tile tangent-form kernels: the instantiation for the pass's tail
-template <bool TURN, int SH, int AT>
-void launch_adjoint_k(int prec, const PassProg &pp, int64_t grid, hipStream_t st)
+// complex64 256-thread tangent-form kernels: the instantiation for the pass's tail
+template <bool TURN, int SH>
+void launch_adjoint_k(const PassProg &pp, int64_t grid, hipStream_t st)
 {
-    const int k = prec == 0 ? tail_k(pp, kTileBitsC64, AT, TURN ? 1 : 2) : 0;
+    constexpr int T = kTileBitsC64, AT = kAdjOneThreadBits;
     const dim3 g((unsigned)grid), b(1 << AT);
     auto go = [&](auto kern) { hipLaunchKernelGGL(kern, g, b, 0, st, pp); };
-    switch (k) {
-    case 1: go(adjoint_kernel<float2, kTileBitsC64, AT, TURN, kModeTan, SH, true, 1>); break;
-    case 2: go(adjoint_kernel<float2, kTileBitsC64, AT, TURN, kModeTan, SH, true, 2>); break;
-    case 3: go(adjoint_kernel<float2, kTileBitsC64, AT, TURN, kModeTan, SH, true, 3>); break;
-    case 4: go(adjoint_kernel<float2, kTileBitsC64, AT, TURN, kModeTan, SH, true, 4>); break;
-    default: launch_adjoint_s<kModeTan, TURN, SH, true, AT>(prec, pp, grid, st); break;
+    switch (tail_k(pp, T, AT, TURN ? 1 : 2)) {
+    case 1: go(adjoint_kernel<float2, T, AT, TURN, kModeTan, SH, true, 1>); break;
+    case 2: go(adjoint_kernel<float2, T, AT, TURN, kModeTan, SH, true, 2>); break;
+    case 3: go(adjoint_kernel<float2, T, AT, TURN, kModeTan, SH, true, 3>); break;
+    case 4: go(adjoint_kernel<float2, T, AT, TURN, kModeTan, SH, true, 4>); break;
+    default: launch_adjoint_s<kModeTan, TURN, SH, true, AT>(0, pp, grid, st); break;
     }
 }
 
@@ -439,14 +439,17 @@ int adjoint_variant(int prec, const PassProg &pp, int turnaround, int mode)
 template <int MODE, int AT>
 void launch_adjoint_m_at(int prec, const PassProg &pp, int turnaround, int64_t grid, hipStream_t st)
 {
-    if constexpr (MODE == kModeTan) {
+    // Compile-time tails in complex64 (measured against masks read from the
+    // program, p = 3 gradients: n = 20 (p = 10) 525 -> 500 us, 24 1042 -> 1026,
+    // 28 15349 -> 15220; the n = 32 kernels 253.8 -> 251.6 ms).  In complex128
+    // they gave n = 24 1904 -> 1875 us but n = 28 28.79 -> 28.96 ms: not taken.
+    if constexpr (MODE == kModeTan && AT == kAdjOneThreadBits) {
         if (prec == 0) {
             switch (adjoint_variant(prec, pp, turnaround, MODE)) {
-            case kAdjOneTurn: launch_adjoint_k<true, -1, AT>(prec, pp, grid, st); return;
-            // (the reverse of a plain pass and the reverse junction keep runtime
-            // masks: with compile-time tails their 512-thread code needs more
-            // than the 128 registers of two workgroups per CU and spills)
-            case kAdjOneFirst: launch_adjoint_k<false, kShInit | kShPhase | kShPost, AT>(prec, pp, grid, st); return;
+            case kAdjOneTurn: launch_adjoint_k<true, -1>(pp, grid, st); return;
+            case kAdjOnePlain: launch_adjoint_k<false, kShPost>(pp, grid, st); return;
+            case kAdjOneFirst: launch_adjoint_k<false, kShInit | kShPhase | kShPost>(pp, grid, st); return;
+            case kAdjOneJunc: launch_adjoint_k<false, kShPre | kShPhase | kShPost>(pp, grid, st); return;
             default: break;
             }
         }

@@ -128,15 +128,6 @@ __device__ __forceinline__ double im_dot(V l, V p)
     return (double)l.x * (double)p.y - (double)l.y * (double)p.x;
 }
 
-// Hides the vector from the optimizer, which would keep every part's FP64
-// conversion in registers from one use to the next, twice the vector's size.
-template <typename V, int NR>
-__device__ __forceinline__ void small_pin(V (&v)[NR])
-{
-#pragma unroll
-    for (int r = 0; r < NR; ++r) asm volatile("" : "+v"(v[r].x), "+v"(v[r].y));
-}
-
 // sum_q Im <lam| X_q |psi> = sum_x Im conj(l_x) sum_q p_(x ^ bit q): the
 // partners of each amplitude are added up first, in FP64, so that a bit costs
 // two conversions and two additions per amplitude; eight registers at a time.
@@ -152,7 +143,7 @@ __device__ __forceinline__ void sum_lanes(double2 (&s)[CH], V (&p)[NR], int n)
                 s[i].x += (double)t.x;
                 s[i].y += (double)t.y;
             }
-            small_pin(p);
+            pin_regs(p);
         }
         sum_lanes<AT, CH, B + 1>(s, p, n);
     }
@@ -175,8 +166,8 @@ __device__ __forceinline__ double im_sums(V (&l)[NR], V (&p)[NR], int n)
 #pragma unroll
     for (int i = 0; i < CH; ++i) g += (double)l[AT + i].x * s[i].y - (double)l[AT + i].y * s[i].x;
     if constexpr (AT + CH < NR) {
-        small_pin(p);
-        small_pin(l);
+        pin_regs(p);
+        pin_regs(l);
         g += im_sums<LO, HI, AT + CH>(l, p, n);
     }
     return g;
@@ -425,11 +416,11 @@ __global__ void __launch_bounds__(SmallCfg<N>::NT) small_adjoint(SmallProg sp)
             rx_regs<0, RB, true>(p, c, s);
             rx_regs<0, RB, true>(l, c, s);
             rx_lanes<true>(p, n, c, s);
-            small_pin(p);
-            small_pin(l);
+            pin_regs(p);
+            pin_regs(l);
             rx_lanes<true>(l, n, c, s);
-            small_pin(p);
-            small_pin(l);
+            pin_regs(p);
+            pin_regs(l);
         }
         if (sp.do_phase[L]) {
 #pragma unroll

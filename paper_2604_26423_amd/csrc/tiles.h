@@ -14,6 +14,8 @@
 // layer and the next (the "pre" and "post" stages).
 #pragma once
 
+#include <type_traits>
+
 #include "device.h"
 
 namespace qs {
@@ -330,16 +332,22 @@ __device__ __forceinline__ void unrun_stage(V (&p)[NR], V (&l)[NR], V *lds, cons
             }
             cur = w;
         };
+        // The window's terms are summed before its update (the sum is pinned):
+        // left to itself the scheduler mixes the two and the 256-thread junction
+        // spills 211-288 registers; pinned it fits, 247 of 256.
+        auto window = [&](auto mask, double scale) {
+            double g = imx_reg_const<mask.value>(l, p);
+            asm volatile("" : "+v"(g));
+            gx += scale * g;
+            rxt_reg_const<mask.value>(p, u);
+            rxt_reg_const<mask.value>(l, u);
+        };
         for (int i = seq.cnt - 1; i > 0; --i) {
             if (i < seq.cnt - 1) to(opaque(seq.s[i]));
-            gx += st.wsc[i] * imx_reg_const<FULL>(l, p);
-            rxt_reg_const<FULL>(p, u);
-            rxt_reg_const<FULL>(l, u);
+            window(std::integral_constant<uint32_t, FULL>{}, st.wsc[i]);
         }
         if (seq.cnt > 1) to(opaque(seq.s[0]));  // (opaque: see run_stage)
-        gx += st.wsc[0] * imx_reg_const<LAST>(l, p);
-        rxt_reg_const<LAST>(p, u);
-        rxt_reg_const<LAST>(l, u);
+        window(std::integral_constant<uint32_t, LAST>{}, st.wsc[0]);
         return;
     }
     uint32_t done = 0, pdone = 0;
