@@ -355,6 +355,7 @@ PassProg make_prog_raw(void *psi, int n, int prec, double *partials, const PassG
     if (pp.has_pre) stage_scales(pp.pre, pp.A, g.targets, g.pairs, T, tb);
     if (pp.has_post) stage_scales(pp.post, pp.B, g.targets, g.pairs, T, tb);
     pp.factor = pp.fpre * pp.fpost;
+    pp.stream = !pp.has_phase && !pp.readout && !pp.pairs;
     pp.phase_win = pp.has_pre ? last_window(pp.A) : pp.load_win;
     pp.final_win = last_window(pp.B);
     if (pp.has_phase) pp.theta_zz = cc.tzz[k.phase];
@@ -365,11 +366,38 @@ PassProg make_prog_raw(void *psi, int n, int prec, double *partials, const PassG
     return pp;
 }
 
+// Whether a pass of the full layout streams the state: nontemporal loads and
+// stores (the reverse junction and the turnaround load ordinarily).  Measured
+// on MI355X against ordinary accesses, by the size of the state:
+//   from 256 MB on (the size of the last-level cache) nothing of a vector
+//   survives to the next pass: n = 26 forward 1409 -> 1317 us, n = 30 21.96 ->
+//   20.89 ms, its p = 3 gradient 61.2 -> 60.0, complex128 n = 28 10.24 -> 9.77
+//   ms forward and 28.96 -> 27.44 gradient;
+//   up to 32 MB (the eight XCDs' L2 caches together) the stores of a launch
+//   would be written back at its end, for the other XCDs to read them: n = 22
+//   forward 98.5 -> 87.4 us, n = 20 gradient (p = 10) 509 -> 456, complex128
+//   n = 20 forward 78.7 -> 65.2; below 4 MB the forward passes gain nothing
+//   (n = 17 57.0 against 58.7), the reverse ones do (131.9 -> 124.7);
+//   between, the vectors stay in the last-level cache and streaming loses
+//   (n = 23 forward 162 -> 173 us, gradient 379 -> 390; n = 24 forward 375 ->
+//   394).
+// A forward pass that only applies a stage streams at every size, and the
+// complement-symmetric layout (two-bit factors, 6% slower with it) at none.
+int pass_streams(const PassProg &pp, int prec, int kind)
+{
+    if (pp.pairs) return 0;
+    if (kind == 0 && !pp.has_phase && !pp.readout) return 1;
+    const int64_t bytes = (prec == 0 ? (int64_t)sizeof(float2) : (int64_t)sizeof(double2)) << pp.n;
+    constexpr int64_t MB = 1 << 20;
+    return bytes >= 256 * MB || (bytes <= 32 * MB && (kind != 0 || bytes >= 4 * MB));
+}
+
 // kind: 0 = forward pass, 1 = turnaround, 2 = reverse pass (the cut table is
 // attached when the kernel for the pass takes one).
 PassProg make_prog(qs_state s, const PassGeom &g, const KSpec &k, const Circuit &cc, int tb, int kind = 0)
 {
     PassProg pp = make_prog_raw(s->psi, s->n, s->prec, (double *)s->partials.p, g, k, cc, tb, s->sym);
+    pp.stream = pass_streams(pp, s->prec, kind);
     if (s->cut_on && pass_takes_cut_table(s->prec, pp, kind)) {
         pp.ctab = (int32_t *)s->ctab.p;
         pp.wts = (const int32_t *)s->wts.p;

@@ -207,7 +207,9 @@ __global__ void __launch_bounds__(1 << TB, ONE ? (TB == 9 ? 4 : 2) : 1) adjoint_
             if constexpr (PREFETCH) {
                 if (tile + G < pp.ntiles) turn_load<V, T, TB>(pp, tile + G, np, tid);
             } else {
+                __builtin_amdgcn_s_setprio(2);  // (see fwd_tile)
                 turn_load<V, T, TB>(pp, tile, p, tid);
+                __builtin_amdgcn_s_setprio(0);
             }
             turn_compute<V, T, TB, MODE, PAIR, K>(pp, tile, p, dg, lds, acc, tid);
             if constexpr (PREFETCH) {
@@ -232,7 +234,9 @@ __global__ void __launch_bounds__(1 << TB, ONE ? (TB == 9 ? 4 : 2) : 1) adjoint_
             if constexpr (PREFETCH) {
                 if (tile + G < pp.ntiles) rev_load_vectors<V, T, TB>(pp, tile + G, np, nl, tid);
             } else {
-                rev_load_vectors<V, T, TB>(pp, tile, p, l, tid);
+                __builtin_amdgcn_s_setprio(2);
+                rev_load_vectors<V, T, TB, !LATE && TB == kAdjOneThreadBits>(pp, tile, p, l, tid);
+                __builtin_amdgcn_s_setprio(0);
             }
             rev_tile<V, T, TB, MODE, SH, PAIR, LATE, K>(pp, tile, p, l, dg, lds, tab, acc, tid);
             if constexpr (PREFETCH) {

@@ -456,26 +456,26 @@ __device__ __forceinline__ void fwd_tile(const PassProg &pp, int64_t tile, V *ld
     const int dwin = has_phase ? pp.phase_win : pp.final_win;
     const Geom g = geom_of(pp);
     const int64_t base = tile_base(tile, g.c, g.q0, g.m);
-    // A pass of the full layout that only applies a stage streams the state
-    // with nontemporal loads and stores (measured: plain passes 9% faster, the
-    // n = 32 forward 4%, the complex128 one 4-12%).  The passes that apply a
-    // phase or read out ran up to 14% slower with them, and the
-    // complement-symmetric layout (two-bit factors) 6% slower, so those keep
-    // ordinary accesses.
-    const bool stream = !has_phase && !readout && !pp.pairs;
     V v[NR];
     int32_t dg[NR];
     // C_t first, so that the latency of its loads overlaps stage A
     if (need_diag) load_cut<T, TB>(pp, tile, opaque(dwin), base, g.c, g.q0, tid, dg);
     int cur = opaque(pp.load_win);
+    // A wave's loads go before the arithmetic of the waves it shares its SIMD
+    // with: the memory requests of the next tile are out while another tile is
+    // computed (gradients at n = 26: 3954 -> 3864 us, n = 28 15.40 -> 15.09 ms,
+    // forward at n = 30 22.10 -> 21.96 ms; raised for the stores too, the n = 28
+    // gradient took 14.97 ms where this took 14.63).
+    __builtin_amdgcn_s_setprio(2);
     if (init) {
 #pragma unroll
         for (int r = 0; r < NR; ++r) v[r] = V{(R)pp.amp0, (R)0};
-    } else if (stream) {
+    } else if (pp.stream) {
         for_each_reg<NR>(win_addr(tid, cur, RB, base, g.c, g.q0), [&](int r, int64_t x) { v[r] = load_nt(&psi[x]); });
     } else {
         for_each_reg<NR>(win_addr(tid, cur, RB, base, g.c, g.q0), [&](int r, int64_t x) { v[r] = psi[x]; });
     }
+    __builtin_amdgcn_s_setprio(0);
     static_assert(K == 0 || (SH >= 0 && MODE == kModeTan), "compile-time tails need a fixed tangent-form shape");
     constexpr int TAIL_B = K == 0 ? 0 : ((SH & kShPre) != 0 ? -K : K);  // B is the second stage after A
     if (has_pre) run_stage<RB, MODE, K>(v, lds, pp.A, pp.targets, pp.pairs, pp.pre, cur, tid);
@@ -501,8 +501,8 @@ __device__ __forceinline__ void fwd_tile(const PassProg &pp, int64_t tile, V *ld
             acc[1] += pr * (double)dg[r];
         }
     }
-    if (stream)
-        for_each_reg<NR>(win_addr(tid, cur, RB, base, g.c, g.q0), [&](int r, int64_t x) { store_nt(&out[x], v[r]); });
+    if (pp.stream)
+        for_each_reg<NR, SH >= 0 && (SH & kShInit) != 0>(win_addr(tid, cur, RB, base, g.c, g.q0), [&](int r, int64_t x) { store_nt(&out[x], v[r]); });
     else
         for_each_reg<NR, SH >= 0 && (SH & kShInit) != 0>(win_addr(tid, cur, RB, base, g.c, g.q0),
                                                          [&](int r, int64_t x) { out[x] = v[r]; });
@@ -571,8 +571,11 @@ __device__ __forceinline__ void turn_compute(const PassProg &pp, int64_t tile, V
         l[r] = scale_v(p[r], (R)(((double)C - pp.lam_shift) * 0.1));
     }
     unrun_stage<RB, MODE, PAIR, -K>(p, l, lds, pp.B, pp.targets, pp.pairs, pp.post, cur, tid, acc[0]);
-    for_each_reg<NR>(win_addr(tid, cur, RB, base, gg.c, gg.q0),
-                     [&](int r, int64_t g) { lam[g] = scale_v(l[r], fpost); });
+    const auto at = win_addr(tid, cur, RB, base, gg.c, gg.q0);
+    if (TB == kAdjOneThreadBits && pp.stream)
+        for_each_reg<NR>(at, [&](int r, int64_t g) { store_nt(&lam[g], scale_v(l[r], fpost)); });
+    else
+        for_each_reg<NR>(at, [&](int r, int64_t g) { lam[g] = scale_v(l[r], fpost); });
 }
 
 template <typename V, int T, int TB, int MODE = kModeGeneral, int K = 0>
@@ -588,7 +591,8 @@ __device__ __forceinline__ void turn_tile(const PassProg &pp, int64_t tile, V *l
 
 // Reverse pass, loads: psi and lambda of a tile in the pass's load layout, and
 // C_t in the layout of the phase step.
-template <typename V, int T, int TB>
+// (STREAM: follow pp.stream; the junction spills with both kinds of loads)
+template <typename V, int T, int TB, bool STREAM = false>
 __device__ __forceinline__ void rev_load_vectors(const PassProg &pp, int64_t tile, V (&p)[TileCfg<V, T, TB>::NR],
                                                  V (&l)[TileCfg<V, T, TB>::NR], int tid)
 {
@@ -597,10 +601,18 @@ __device__ __forceinline__ void rev_load_vectors(const PassProg &pp, int64_t til
     const V *lam = reinterpret_cast<const V *>(pp.lam);
     const Geom gg = geom_of(pp);
     const int64_t base = tile_base(tile, gg.c, gg.q0, gg.m);
-    for_each_reg<Cfg::NR>(win_addr(tid, opaque(pp.load_win), Cfg::RB, base, gg.c, gg.q0), [&](int r, int64_t g) {
-        p[r] = psi[g];
-        l[r] = lam[g];
-    });
+    const auto at = win_addr(tid, opaque(pp.load_win), Cfg::RB, base, gg.c, gg.q0);
+    if (STREAM && pp.stream) {
+        for_each_reg<Cfg::NR>(at, [&](int r, int64_t g) {
+            p[r] = load_nt(&psi[g]);
+            l[r] = load_nt(&lam[g]);
+        });
+    } else {
+        for_each_reg<Cfg::NR>(at, [&](int r, int64_t g) {
+            p[r] = psi[g];
+            l[r] = lam[g];
+        });
+    }
 }
 
 template <typename V, int T, int TB>
@@ -692,14 +704,22 @@ __device__ __forceinline__ void rev_tile(const PassProg &pp, int64_t tile, V (&p
         }
     }
     if (!init) {
-        if (psi) {
-            for_each_reg<NR>(win_addr(tid, cur, RB, base, gg.c, gg.q0), [&](int r, int64_t g) {
+        const auto at = win_addr(tid, cur, RB, base, gg.c, gg.q0);
+        const bool nt = TB == kAdjOneThreadBits && pp.stream;
+        if (psi && nt) {
+            for_each_reg<NR>(at, [&](int r, int64_t g) {
+                store_nt(&psi[g], p[r]);
+                store_nt(&lam[g], l[r]);
+            });
+        } else if (psi) {
+            for_each_reg<NR>(at, [&](int r, int64_t g) {
                 psi[g] = p[r];
                 lam[g] = l[r];
             });
-        } else {  // psi of the next reverse pass comes from a checkpoint
-            for_each_reg<NR>(win_addr(tid, cur, RB, base, gg.c, gg.q0),
-                             [&](int r, int64_t g) { lam[g] = l[r]; });
+        } else if (nt) {  // psi of the next reverse pass comes from a checkpoint
+            for_each_reg<NR>(at, [&](int r, int64_t g) { store_nt(&lam[g], l[r]); });
+        } else {
+            for_each_reg<NR>(at, [&](int r, int64_t g) { lam[g] = l[r]; });
         }
     }
 }
