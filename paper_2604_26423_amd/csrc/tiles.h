@@ -437,7 +437,7 @@ __device__ __forceinline__ void load_phase_table(V *tab, const V *src, int level
 // Forward pass on one tile; with pp.readout, acc += (sum |a|^2, sum |a|^2 C_t).
 // K > 0 (a fixed shape SH in tangent form): the stages' tails are fixed at
 // compile time, +K for the first stage and -K for the second (run_stage).
-template <typename V, int T, int TB, int MODE = kModeGeneral, int SH = -1, int K = 0>
+template <typename V, int T, int TB, int MODE = kModeGeneral, int SH = -1, int K = 0, int STREAM = -1>
 __device__ __forceinline__ void fwd_tile(const PassProg &pp, int64_t tile, V *lds, const V *tab, double (&acc)[2],
                                          int tid)
 {
@@ -450,6 +450,7 @@ __device__ __forceinline__ void fwd_tile(const PassProg &pp, int64_t tile, V *ld
     const bool has_post = KS ? (SH & kShPost) != 0 : pp.has_post != 0;
     const bool init = KS ? (SH & kShInit) != 0 : pp.init != 0;
     const bool readout = KS ? (SH & kShReadout) != 0 : pp.readout != 0;
+    const bool stream = STREAM >= 0 ? STREAM != 0 : pp.stream != 0;
     const V *psi = reinterpret_cast<const V *>(pp.psi);
     V *out = reinterpret_cast<V *>(pp.psi_out);
     const bool need_diag = has_phase || readout;
@@ -470,7 +471,7 @@ __device__ __forceinline__ void fwd_tile(const PassProg &pp, int64_t tile, V *ld
     if (init) {
 #pragma unroll
         for (int r = 0; r < NR; ++r) v[r] = V{(R)pp.amp0, (R)0};
-    } else if (pp.stream) {
+    } else if (stream) {
         for_each_reg<NR>(win_addr(tid, cur, RB, base, g.c, g.q0), [&](int r, int64_t x) { v[r] = load_nt(&psi[x]); });
     } else {
         for_each_reg<NR>(win_addr(tid, cur, RB, base, g.c, g.q0), [&](int r, int64_t x) { v[r] = psi[x]; });
@@ -501,7 +502,7 @@ __device__ __forceinline__ void fwd_tile(const PassProg &pp, int64_t tile, V *ld
             acc[1] += pr * (double)dg[r];
         }
     }
-    if (pp.stream)
+    if (stream)
         for_each_reg<NR, SH >= 0 && (SH & kShInit) != 0>(win_addr(tid, cur, RB, base, g.c, g.q0), [&](int r, int64_t x) { store_nt(&out[x], v[r]); });
     else
         for_each_reg<NR, SH >= 0 && (SH & kShInit) != 0>(win_addr(tid, cur, RB, base, g.c, g.q0),
