@@ -5,7 +5,7 @@
 // those steps, whatever their shape.  The kernel boundary is the only
 // synchronisation.  (One persistent launch with a ticket queue and completion
 // counters, agent-scope release and acquire fences around every item, took
-// 20.6 ms instead of 13.9 for 128 circuits of 14 to 22 qubits, 79 instead of 52
+// 20.6 ms instead of 13.3 for 128 circuits of 14 to 22 qubits, 79 instead of 49
 // for 512, 4.6 instead of 0.8 for 64 circuits of 14 to 17: each fence writes
 // back or drops a whole L2, and halving the items' size doubled the time.)
 #include "tiles.h"
