@@ -488,14 +488,14 @@ hipError_t small_dispatch(int n, F &&launch)
 
 // Whole calls of Simulator.forward / adjoint (us; p = 10 layers), before: one
 // 1024-thread workgroup, the state in LDS, a barrier per qubit, a sine and
-// cosine per amplitude and layer; about 25 us of each are launch, copy and
+// cosine per amplitude and layer; about 15 us of each are launch and
 // synchronisation:
 //   n, precision     forward          forward + adjoint
-//    9, complex128    57 ->  43        132 ->  88
-//   10, complex64     61 ->  39        148 ->  77
-//   12, complex64    119 ->  57        343 -> 146
-//   12, complex128   144 ->  69        419 -> 184
-//   13, complex64    197 ->  84        614 -> 259
+//    9, complex128    57 ->  33        132 ->  73
+//   10, complex64     61 ->  30        148 ->  65
+//   12, complex64    119 ->  48        343 -> 132
+//   12, complex128   144 ->  59        419 -> 168
+//   13, complex64    197 ->  74        614 -> 242
 // What is left is the issue rate of one CU's vector units (about 2100
 // instructions per wave and reverse layer at n = 12, 8 waves).
 hipError_t launch_small_forward(int prec, const SmallProg &sp, hipStream_t st)
