@@ -1324,7 +1324,7 @@ qs_status qs_sample(qs_state s, uint64_t seed, int64_t shots, uint64_t *out, int
         dst = (uint64_t *)s->shots_out.p;
     }
     if (pin) {
-        *(int32_t *)pin = 0;
+        memset(b.flag, 0, 8);
     } else {
         hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s->stream, (double *)b.flag, 1);
         HIPCHK(hipGetLastError(), where);
@@ -1334,18 +1334,18 @@ qs_status qs_sample(qs_state s, uint64_t seed, int64_t shots, uint64_t *out, int
         HIPCHK(launch_sample(s->prec, s->psi, s->n, b, seed, shots, dst, s->stream, s->sym ? s->nq : 0), where);
         L.done();
     }
-    int32_t flag = 0;
-    if (!pin) HIPCHK(hipMemcpyAsync(&flag, b.flag, 4, hipMemcpyDeviceToHost, s->stream), where);
+    int32_t flag[2] = {0, 0};
+    if (!pin) HIPCHK(hipMemcpyAsync(flag, b.flag, sizeof flag, hipMemcpyDeviceToHost, s->stream), where);
     if (to_host)
         HIPCHK(hipMemcpyAsync(pin ? (void *)(pin + kHead) : (void *)out, dst, (size_t)shots * 8, hipMemcpyDeviceToHost,
                               s->stream), where);
     HIPCHK(hipStreamSynchronize(s->stream), where);
     if (pin) {
-        flag = *(int32_t *)pin;
+        memcpy(flag, pin, sizeof flag);
         if (to_host) memcpy(out, pin + kHead, (size_t)shots * 8);
     }
-    if (flag == 1) return fail(QS_ERR_STATE, "qs_sample: state has zero norm");
-    if (flag == 2) return fail(QS_ERR_STATE, "qs_sample: state norm too large (|a|^2 sums to 4 or more)");
+    if (flag[0] == 1 && !flag[1]) return fail(QS_ERR_STATE, "qs_sample: state has zero norm");
+    if (flag[1]) return fail(QS_ERR_STATE, "qs_sample: state norm too large (|a|^2 sums to 4 or more)");
     return QS_OK;
 }
 

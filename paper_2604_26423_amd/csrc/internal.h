@@ -389,7 +389,7 @@ struct SampleBufs {
     uint64_t *sub;     // in-block exclusive prefix of 64-amplitude sub-block sums
     uint64_t *blk;     // in-chunk exclusive prefix of block sums
     uint64_t *chunk;   // chunk sums
-    int32_t *flag;     // overflow / zero-total flag
+    int32_t *flag;     // [0]: the total is zero; [1]: a sum reached 2^64
 };
 void sample_sizes(int n, int64_t *nsub, int64_t *nblk, int64_t *nchunk);
 // sym_n > 0: psi is the complement-symmetric layout of sym_n qubits (n =

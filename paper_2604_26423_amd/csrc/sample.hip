@@ -9,6 +9,12 @@
 // 2^26-amplitude chunks, and chunks; integer sums make the result independent
 // of summation order.  Each shot then descends the three levels and scans 64
 // amplitudes.  Small states (n < 13) use a full CDF in LDS.
+//
+// A sum of 2^64 or more (a norm of 4 or more) cannot be sampled.  Every sum on
+// the way to T is checked where it is made: s = a + b wrapped if s < b, and in
+// an inclusive scan the first element to wrap is smaller than its own addend.
+// No partial sum exceeds T, so a wrap anywhere means T wraps, and T wraps only
+// if some partial sum does.  flag[0] = 1: T = 0; flag[1] = 2: T >= 2^64.
 #include <algorithm>
 
 #include "device.h"
@@ -96,6 +102,7 @@ __global__ void __launch_bounds__(256) sample_blocks_kernel(const V *psi, uint64
                                                             int32_t *flag)
 {
     constexpr int NL = (1 << kBlockBits) / 512;  // pairs per thread
+    int32_t over = 0;
     __shared__ uint64_t ssum[kSubPerBlock];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int64_t b = blockIdx.x;
@@ -108,25 +115,33 @@ __global__ void __launch_bounds__(256) sample_blocks_kernel(const V *psi, uint64
     for (int i = 0; i < NL; ++i) AmpPair<V>::load(blkp + ((i * 512 + 2 * tid) ^ fb), a[i], c[i]);
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-        uint64_t q = qval_of(a[i], flag) + qval_of(c[i], flag);
+        const uint64_t q1 = qval_of(c[i], &over);
+        uint64_t q = qval_of(a[i], &over) + q1;
+        over |= q < q1;
 #pragma unroll
-        for (int off = 16; off >= 1; off >>= 1) q += __shfl_xor(q, off, 64);
+        for (int off = 16; off >= 1; off >>= 1) {
+            const uint64_t t = __shfl_xor(q, off, 64);
+            q += t;
+            over |= q < t;
+        }
         if ((lane & 31) == 0) ssum[i * 8 + 2 * wave + (lane >> 5)] = q;
     }
     __syncthreads();
     if (wave == 0) {
         const uint64_t a0 = ssum[2 * lane], a1 = ssum[2 * lane + 1];
         const uint64_t incl = wave_scan_u64(a0 + a1, lane);
+        over |= a0 + a1 < a1 || incl < a0 + a1;
         const uint64_t excl = incl - (a0 + a1);
         sub[b * kSubPerBlock + 2 * lane] = excl;
         sub[b * kSubPerBlock + 2 * lane + 1] = excl + a0;
         if (lane == 63) blk[b] = incl;
     }
+    if (over) flag[1] = 2;
 }
 
 // Exclusive prefix over the workgroup of one value per thread (1024 threads at
-// most); *total: the sum.  red: 16 words of LDS.
-__device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t *red, int tid, uint64_t *total)
+// most); *total: the sum; over: set where a sum wraps.  red: 16 words of LDS.
+__device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t *red, int tid, uint64_t *total, int32_t &over)
 {
     const int wave = tid >> 6, lane = tid & 63, nw = blockDim.x >> 6;
     const uint64_t incl = wave_scan_u64(v, lane);
@@ -137,6 +152,7 @@ __device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t *red, in
         before += w < wave ? red[w] : 0;
         all += red[w];
     }
+    over |= incl < v || before + incl < incl;
     *total = all;
     return before + incl - v;
 }
@@ -146,18 +162,24 @@ __device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t *red, in
 // before any is summed (a serial pass of one thread over 256 partial sums took
 // 20 us at n = 27, this one 5).
 constexpr int kScanThreads = 1024;
-__global__ void __launch_bounds__(kScanThreads) scan_blocks_kernel(uint64_t *blk, int64_t nblk, uint64_t *chunk)
+__global__ void __launch_bounds__(kScanThreads) scan_blocks_kernel(uint64_t *blk, int64_t nblk, uint64_t *chunk,
+                                                                   int32_t *flag)
 {
     __shared__ uint64_t red[kScanThreads / 64];
     constexpr int per = kBlkPerChunk / kScanThreads;
     const int tid = threadIdx.x;
     const int64_t lo = (int64_t)blockIdx.x * kBlkPerChunk + (int64_t)tid * per;
     uint64_t v[per], loc = 0, total;
+    int32_t over = 0;
 #pragma unroll
     for (int k = 0; k < per; ++k) v[k] = lo + k < nblk ? blk[lo + k] : 0;
 #pragma unroll
-    for (int k = 0; k < per; ++k) loc += v[k];
-    uint64_t acc = block_scan_u64(loc, red, tid, &total);
+    for (int k = 0; k < per; ++k) {
+        loc += v[k];
+        over |= loc < v[k];
+    }
+    uint64_t acc = block_scan_u64(loc, red, tid, &total, over);
+    if (over) flag[1] = 2;
 #pragma unroll
     for (int k = 0; k < per; ++k) {
         if (lo + k < nblk) blk[lo + k] = acc;
@@ -202,7 +224,7 @@ __device__ __forceinline__ int64_t group_last_le(const uint64_t *a, int64_t len,
 // are read at once and scanned across the lanes (one lane per shot took 20
 // binary-search steps and a serial walk over the amplitudes: 24 us for 10,000
 // shots at n = 27, 10 us now).  The chunk sums are scanned by every workgroup
-// in LDS; the first one reports a zero total or a 64-bit wrap.  With shots
+// in LDS; the first one reports a zero total or a sum that wraps.  With shots
 // enough to fill the chip the latency is hidden and the work per shot counts:
 // a group then draws 16 shots in turn, so that the chunk scan is shared by 256
 // shots and a wave's lanes evaluate 64 Philox outputs at once (whole calls with
@@ -221,12 +243,11 @@ __global__ void __launch_bounds__(kShotThreads) sample_shots_kernel(const V *psi
     constexpr int kGroups = 64 / kShotLanes;  // of a wave
     const int tid = threadIdx.x, lane = tid & 63, g = lane & (kShotLanes - 1);
     uint64_t T;
-    const uint64_t mine = tid < nchunk ? chunk[tid] : 0;
-    const uint64_t excl = block_scan_u64(mine, red, tid, &T);
-    cs[tid] = excl;
+    int32_t over = 0;
+    cs[tid] = block_scan_u64(tid < nchunk ? chunk[tid] : 0, red, tid, &T, over);
     if (blockIdx.x == 0) {
-        if (excl + mine < excl) *flag = 2;
-        else if (T == 0 && tid == 0) *flag = 1;
+        if (over) flag[1] = 2;
+        if (T == 0 && tid == 0) flag[0] = 1;
     }
     __syncthreads();
     // lane i evaluates the draw of the wave's shot i (i < kGroups * rounds <= 64)
@@ -253,7 +274,7 @@ __global__ void __launch_bounds__(kShotThreads) sample_shots_kernel(const V *psi
         const V *p = psi + ((x0 + g * per) ^ fb);
         uint64_t q[per], loc = 0;
 #pragma unroll
-        for (int t = 0; t < per; ++t) q[t] = qval_of(p[t], flag);
+        for (int t = 0; t < per; ++t) q[t] = qval_of(p[t], flag + 1);
 #pragma unroll
         for (int t = 0; t < per; ++t) loc += q[t];
         uint64_t acc = loc;
@@ -300,19 +321,24 @@ __global__ void __launch_bounds__(kSmallShots) sample_small_kernel(const V *psi,
     __shared__ uint64_t red[kSmallShots / 64];
     const int tid = threadIdx.x, dim = 1 << n;
     uint64_t q[per], loc = 0, T;
+    int32_t over = 0;
 #pragma unroll
     for (int k = 0; k < per; ++k) {
         const int x = tid * per + k;
-        q[k] = x < dim ? qval_of(psi[x], flag) : 0;
+        q[k] = x < dim ? qval_of(psi[x], &over) : 0;
         loc += q[k];
+        over |= loc < q[k];
     }
-    uint64_t acc = block_scan_u64(loc, red, tid, &T);
+    uint64_t acc = block_scan_u64(loc, red, tid, &T, over);
 #pragma unroll
     for (int k = 0; k < per; ++k) {
         acc += q[k];
         F[tid * per + k] = acc;
     }
-    if (blockIdx.x == 0 && tid == 0 && T == 0) *flag = 1;
+    if (blockIdx.x == 0) {
+        if (over) flag[1] = 2;
+        if (T == 0 && tid == 0) flag[0] = 1;
+    }
     __syncthreads();
     const int64_t s = (int64_t)blockIdx.x * kSmallShots + tid;
     if (s >= shots) return;
@@ -365,7 +391,8 @@ hipError_t launch_sample(int prec, const void *psi, int n, const SampleBufs &b, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (nchunk > kMaxChunks) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)nchunk), dim3(kScanThreads), 0, st, b.blk, nblk, b.chunk);
+    hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)nchunk), dim3(kScanThreads), 0, st, b.blk, nblk, b.chunk,
+                       b.flag);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int rounds = shots < kManyShots ? 1 : kShotRounds;
     const dim3 g = groups((int64_t)(kShotThreads / kShotLanes) * rounds);
