@@ -103,8 +103,11 @@ struct DevBuf {
 // synchronisation.  A copy into pageable memory instead costs 10 us more per
 // call, a pinned allocation 28 us and its release 170 us, so buffers go back to
 // a process-wide pool: at most kPinnedKeep of them per size stay there.  A
-// handle owns its buffer between ensure and release, and returns it only once
-// its stream has finished.
+// handle owns its buffer between ensure and release.  From ensure to done (the
+// caller has waited for its stream) queued work may write the buffer; a call
+// that fails in between leaves it so, and the buffer is then settled -- that
+// stream is waited for -- before it is used again, before it goes back to the
+// pool and before the handle moves to another stream.
 constexpr size_t kPinnedSize[] = {(size_t)64 << 10, (size_t)1 << 20};
 constexpr int kPinnedClasses = 2, kPinnedKeep = 16;
 
@@ -121,20 +124,34 @@ struct PinnedPool {
 struct HostBuf {
     void *p = nullptr;
     int cls = -1;
+    bool busy = false;             // queued work may still write it ...
+    hipStream_t stream = nullptr;  // ... on this stream
     HostBuf() = default;
     HostBuf(const HostBuf &) = delete;
     HostBuf &operator=(const HostBuf &) = delete;
     ~HostBuf() { release(); }
-    // A buffer of at least need bytes, or null (too large, or none to be had):
-    // the caller then goes through pageable memory.  stream: the one whose work
-    // may still use the current buffer (after a call that failed half-way).
-    void *ensure(size_t need, hipStream_t stream)
+    void done() { busy = false; }
+    void settle()
     {
-        if (p && need <= kPinnedSize[cls]) return p;
+        if (busy) (void)hipStreamSynchronize(stream);
+        busy = false;
+    }
+    // A buffer of at least need bytes for work on stream st, or null (too
+    // large, or none to be had): the caller then goes through pageable memory.
+    void *ensure(size_t need, hipStream_t st)
+    {
+        settle();
+        if (!p || need > kPinnedSize[cls])
+            if (!acquire(need)) return nullptr;
+        busy = true;
+        stream = st;
+        return p;
+    }
+    void *acquire(size_t need)
+    {
         int c = 0;
         while (c < kPinnedClasses && need > kPinnedSize[c]) ++c;
         if (c == kPinnedClasses) return nullptr;
-        if (p) (void)hipStreamSynchronize(stream);
         release();
         PinnedPool &pool = PinnedPool::get();
         {
@@ -156,6 +173,7 @@ struct HostBuf {
     void release()
     {
         if (!p) return;
+        settle();
         PinnedPool &pool = PinnedPool::get();
         {
             std::lock_guard<std::mutex> g(pool.mu);
@@ -493,7 +511,10 @@ struct Results {
         if (!pinned)
             HIPCHK(hipMemcpyAsync(out, dev, (size_t)count * sizeof(double), hipMemcpyDeviceToHost, s->stream), where);
         HIPCHK(hipStreamSynchronize(s->stream), where);
-        if (pinned) memcpy(out, dev, (size_t)count * sizeof(double));
+        if (pinned) {
+            memcpy(out, dev, (size_t)count * sizeof(double));
+            s->host.done();
+        }
         return QS_OK;
     }
 };
@@ -1055,7 +1076,7 @@ qs_status qs_free(qs_state s)
     s->shots_out.release();
     s->xfer.release();
     s->lambda.release();
-    delete s;  // (its pinned buffer goes back to the pool: the stream is idle)
+    delete s;
     return QS_OK;
 }
 
@@ -1070,6 +1091,7 @@ qs_status qs_state_ptr(qs_state s, void **dev_ptr)
 qs_status qs_set_stream(qs_state s, void *hip_stream)
 {
     if (qs_status st = check_state(s)) return st;
+    s->host.settle();  // (a wait only after a call that failed half-way)
     s->stream = (hipStream_t)hip_stream;
     return QS_OK;
 }
@@ -1343,6 +1365,7 @@ qs_status qs_sample(qs_state s, uint64_t seed, int64_t shots, uint64_t *out, int
     if (pin) {
         memcpy(flag, pin, sizeof flag);
         if (to_host) memcpy(out, pin + kHead, (size_t)shots * 8);
+        s->host.done();
     }
     if (flag[0] == 1 && !flag[1]) return fail(QS_ERR_STATE, "qs_sample: state has zero norm");
     if (flag[1]) return fail(QS_ERR_STATE, "qs_sample: state norm too large (|a|^2 sums to 4 or more)");
@@ -1440,6 +1463,7 @@ qs_status qs_cost_histogram(qs_state s, const int32_t *diag_dev, int32_t nbins, 
     if (pin) {
         memcpy(head, pin, sizeof head);
         if (!out_on_device) memcpy(mass, dst, (size_t)nbins * 8);
+        s->host.done();
     }
     int32_t fl = 0;
     memcpy(&fl, &head[1], sizeof fl);
@@ -1696,7 +1720,10 @@ qs_status qs_batch_forward_grad(qs_batch b, const double *theta_zz, const double
         b->sums_h.resize((size_t)nsum * kSlots);
         if (!pin) HIPCHK(hipMemcpyAsync(b->sums_h.data(), sums, sbytes, hipMemcpyDeviceToHost, b->stream), where);
         HIPCHK(hipStreamSynchronize(b->stream), where);
-        if (pin) memcpy(b->sums_h.data(), pin, sbytes);
+        if (pin) {
+            memcpy(b->sums_h.data(), pin, sbytes);
+            b->host.done();
+        }
         std::vector<double> res;
         for (int j = 0; j < nsum;) {  // the steps of one circuit, in step order
             const int c = b->steps_h[(size_t)b->summed_h[(size_t)j]].circuit, p = b->p[c];

@@ -1,0 +1,164 @@
+// Host-only driver for libqs's handling of its pinned result buffers: this
+// program defines every HIP entry point that the library imports (an
+// executable's symbols come before those of the shared objects it loads), so
+// that the library's host code runs without a device.  Launches and waits are
+// recorded, and launches fail on demand.
+// Built and run by tests/test_host_runtime.py; prints "ok <case>" and exits 0.
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "qs.h"
+
+namespace {
+struct Event {
+    char kind;  // 'L' launch, 'S' wait for a stream, 'H' / 'F' pinned allocation / release, 'M' copy
+    void *stream;
+    uint64_t threads;
+};
+std::vector<Event> events;
+long fail_launch = -1;  // launches until one fails
+int last_error = 0;
+
+void note(char kind, void *stream, uint64_t threads = 0)
+{
+    events.push_back({kind, stream, threads});
+}
+// Events of a kind on a stream after position from (stream null: any).
+int count(char kind, void *stream, size_t from)
+{
+    int c = 0;
+    for (size_t i = from; i < events.size(); ++i)
+        c += events[i].kind == kind && (!stream || events[i].stream == stream);
+    return c;
+}
+size_t first(char kind, size_t from)
+{
+    size_t i = from;
+    while (i < events.size() && events[i].kind != kind) ++i;
+    return i;
+}
+}  // namespace
+
+extern "C" {
+struct Dim3 {
+    uint32_t x, y, z;
+};
+static struct {
+    Dim3 grid, block;
+    size_t shared;
+    void *stream;
+} config;
+int __hipPushCallConfiguration(Dim3 grid, Dim3 block, size_t shared, void *stream)
+{
+    config = {grid, block, shared, stream};
+    return 0;
+}
+int __hipPopCallConfiguration(Dim3 *grid, Dim3 *block, size_t *shared, void **stream)
+{
+    *grid = config.grid;
+    *block = config.block;
+    *shared = config.shared;
+    *stream = config.stream;
+    return 0;
+}
+void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
+void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipUnregisterFatBinary(void **) {}
+int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
+int hipDeviceSynchronize() { note('S', nullptr); return 0; }
+int hipEventCreate(void **e) { *e = nullptr; return 0; }
+int hipEventDestroy(void *) { return 0; }
+int hipEventElapsedTime(float *ms, void *, void *) { *ms = 0; return 0; }
+int hipEventRecord(void *, void *) { return 0; }
+int hipEventSynchronize(void *) { return 0; }
+int hipMalloc(void **p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? 0 : 2; }
+int hipFree(void *p) { free(p); return 0; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+const char *hipGetErrorString(int) { return "error"; }
+int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
+int hipGetSymbolAddress(void **, const void *) { return 1; }
+int hipHostMalloc(void **p, size_t n, unsigned) { note('H', nullptr); *p = calloc(1, n); return 0; }
+int hipHostFree(void *p) { note('F', nullptr); free(p); return 0; }
+int hipLaunchKernel(const void *, Dim3 grid, Dim3 block, void **, size_t, void *stream)
+{
+    const uint64_t threads = (uint64_t)grid.x * block.x;
+    if (fail_launch >= 0 && fail_launch-- == 0) return last_error = 719;
+    note('L', stream, threads);
+    return 0;
+}
+int hipMemcpyAsync(void *, const void *, size_t, int, void *stream) { note('M', stream); return 0; }
+int hipStreamSynchronize(void *stream) { note('S', stream); return 0; }
+}
+
+#define CHECK(cond)                                                           \
+    do {                                                                      \
+        if (!(cond)) {                                                        \
+            printf("%s:%d: %s (%s)\n", __FILE__, __LINE__, #cond, qs_last_error()); \
+            return 1;                                                         \
+        }                                                                     \
+    } while (0)
+
+static void *const A = (void *)0xA000, *const B = (void *)0xB000;
+
+static qs_state handle(int n, void *stream)
+{
+    qs_state s = nullptr;
+    return qs_alloc(n, QS_C64, nullptr, 0, stream, &s) == QS_OK ? s : nullptr;
+}
+static int32_t *diagonal(int n)
+{
+    void *p = nullptr;
+    hipMalloc(&p, sizeof(int32_t) << n);
+    memset(p, 0, sizeof(int32_t) << n);
+    return (int32_t *)p;
+}
+
+// A call that fails half-way leaves launches behind that may still write the
+// handle's pinned buffer: their stream is waited for before the buffer serves
+// anything else, also when the handle has moved to another stream since.
+static int failed_call(bool switch_stream)
+{
+    const int n = 16, p = 3;
+    const double tzz[p] = {0.1, 0.2, 0.3}, tx[p] = {-0.9, -0.6, -0.3};
+    int32_t *diag = diagonal(n);
+    double e = 0, nrm = 0, g[2 * p];
+    qs_state s = handle(n, A);
+    CHECK(s && qs_adjoint_grad(s, diag, 40, p, tzz, tx, nullptr, 0, &e, g, g + p) == QS_OK);
+    fail_launch = 7;
+    CHECK(qs_adjoint_grad(s, diag, 40, p, tzz, tx, nullptr, 0, &e, g, g + p) == QS_ERR_HIP);
+    fail_launch = -1;
+    const size_t at = events.size();
+    if (switch_stream) {
+        CHECK(qs_set_stream(s, B) == QS_OK);
+        CHECK(qs_free(s) == QS_OK);  // the buffer goes back to the pool
+        CHECK(count('S', A, at) >= 1);
+        qs_state t = handle(n, B);  // and from there to another handle
+        CHECK(t && qs_expect(t, diag, &e, &nrm) == QS_OK && qs_free(t) == QS_OK);
+        CHECK(count('H', nullptr, at) == 0);
+    } else {
+        // the next call clears its flags in the buffer from the host
+        uint64_t shot;
+        CHECK(qs_sample(s, 1, 1, &shot, 0) == QS_OK);
+        CHECK(first('S', at) < first('L', at));
+        const size_t then = events.size();
+        CHECK(qs_set_stream(s, B) == QS_OK);  // nothing left to wait for
+        CHECK(events.size() == then);
+        CHECK(qs_free(s) == QS_OK);
+    }
+    return 0;
+}
+
+int main(int argc, char **argv)
+{
+    const std::string which = argc > 1 ? argv[1] : "";
+    int rc = 2;
+    if (which == "switched_stream") rc = failed_call(true);
+    else if (which == "same_stream") rc = failed_call(false);
+    if (rc == 0) printf("ok %s\n", which.c_str());
+    return rc;
+}
