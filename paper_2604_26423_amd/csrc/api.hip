@@ -153,13 +153,15 @@ struct HostBuf {
         while (c < kPinnedClasses && need > kPinnedSize[c]) ++c;
         if (c == kPinnedClasses) return nullptr;
         release();
-        PinnedPool &pool = PinnedPool::get();
-        {
+        try {
+            PinnedPool &pool = PinnedPool::get();
             std::lock_guard<std::mutex> g(pool.mu);
             if (!pool.spare[c].empty()) {
                 p = pool.spare[c].back();
                 pool.spare[c].pop_back();
             }
+        } catch (...) {  // (no host memory for the pool; entry points without a handler of their own come here)
+            return nullptr;
         }
         // (portable and mapped on every device: a pooled buffer serves any of them)
         if (!p && hipHostMalloc(&p, kPinnedSize[c], hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
@@ -174,16 +176,14 @@ struct HostBuf {
     {
         if (!p) return;
         settle();
-        PinnedPool &pool = PinnedPool::get();
-        {
+        try {
+            PinnedPool &pool = PinnedPool::get();
             std::lock_guard<std::mutex> g(pool.mu);
-            try {
-                if (pool.spare[cls].size() < (size_t)kPinnedKeep) {
-                    pool.spare[cls].push_back(p);
-                    p = nullptr;
-                }
-            } catch (...) {
+            if (pool.spare[cls].size() < (size_t)kPinnedKeep) {
+                pool.spare[cls].push_back(p);
+                p = nullptr;
             }
+        } catch (...) {
         }
         if (p) (void)hipHostFree(p);
         p = nullptr;

@@ -2,12 +2,13 @@
 // program defines every HIP entry point that the library imports (an
 // executable's symbols come before those of the shared objects it loads), so
 // that the library's host code runs without a device.  Launches and waits are
-// recorded, and launches fail on demand.
+// recorded, launches fail on demand, and operator new throws on demand.
 // Built and run by tests/test_host_runtime.py; prints "ok <case>" and exits 0.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -21,11 +22,15 @@ struct Event {
 };
 std::vector<Event> events;
 long fail_launch = -1;  // launches until one fails
+bool fail_new = false;
 int last_error = 0;
 
 void note(char kind, void *stream, uint64_t threads = 0)
 {
+    const bool f = fail_new;
+    fail_new = false;
     events.push_back({kind, stream, threads});
+    fail_new = f;
 }
 // Events of a kind on a stream after position from (stream null: any).
 int count(char kind, void *stream, size_t from)
@@ -42,6 +47,19 @@ size_t first(char kind, size_t from)
     return i;
 }
 }  // namespace
+
+void *operator new(size_t n)
+{
+    if (fail_new) throw std::bad_alloc();
+    void *p = malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void *operator new[](size_t n) { return operator new(n); }
+void operator delete(void *p) noexcept { free(p); }
+void operator delete[](void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
+void operator delete[](void *p, size_t) noexcept { free(p); }
 
 extern "C" {
 struct Dim3 {
@@ -153,12 +171,41 @@ static int failed_call(bool switch_stream)
     return 0;
 }
 
+// No exception leaves the library: without host memory for the pool of pinned
+// buffers the results go through pageable memory.
+static int no_memory()
+{
+    const int n = 14;
+    int32_t *diag = diagonal(n);
+    double e = 0, nrm = 0;
+    uint64_t out[64];
+    qs_state s = handle(n, A);
+    CHECK(s);
+    fail_new = true;
+    int threw = 0;
+    qs_status st[3] = {};
+    try {
+        st[0] = qs_expect(s, diag, &e, &nrm);
+        st[1] = qs_sample(s, 1, 64, out, 0);
+        st[2] = qs_cost_histogram(s, diag, 64, out, 0);
+    } catch (...) {
+        threw = 1;
+    }
+    fail_new = false;
+    CHECK(!threw);
+    CHECK(st[0] == QS_OK && st[1] == QS_OK && st[2] == QS_OK);
+    CHECK(count('H', nullptr, 0) == 0);
+    CHECK(qs_free(s) == QS_OK);
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
     int rc = 2;
     if (which == "switched_stream") rc = failed_call(true);
     else if (which == "same_stream") rc = failed_call(false);
+    else if (which == "no_memory") rc = no_memory();
     if (rc == 0) printf("ok %s\n", which.c_str());
     return rc;
 }
