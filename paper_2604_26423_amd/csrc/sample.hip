@@ -310,8 +310,11 @@ __global__ void __launch_bounds__(kShotThreads) sample_shots_kernel(const V *psi
 }
 
 // n < 13: every workgroup builds the whole CDF in LDS and draws kSmallShots
-// shots, one per thread.
+// shots, one per thread; kSmallGroups workgroups at most (more shots than
+// that: several rounds each), so that a launch stays far below the 2^32 threads
+// that the runtime accepts.
 constexpr int kSmallShots = 1024;
+constexpr int64_t kSmallGroups = 1 << 16;
 template <typename V>
 __global__ void __launch_bounds__(kSmallShots) sample_small_kernel(const V *psi, int n, uint64_t seed, int64_t shots,
                                                                    uint64_t *out, int32_t *flag)
@@ -340,16 +343,16 @@ __global__ void __launch_bounds__(kSmallShots) sample_small_kernel(const V *psi,
         if (T == 0 && tid == 0) flag[0] = 1;
     }
     __syncthreads();
-    const int64_t s = (int64_t)blockIdx.x * kSmallShots + tid;
-    if (s >= shots) return;
-    const uint64_t u = __umul64hi(philox_word0((uint64_t)s, seed), T);
-    int lo = 0, hi = dim - 1;  // first x with F[x] > u
-    while (lo < hi) {
-        const int mid = (lo + hi) / 2;
-        if (F[mid] > u) hi = mid;
-        else lo = mid + 1;
+    for (int64_t s = (int64_t)blockIdx.x * kSmallShots + tid; s < shots; s += (int64_t)gridDim.x * kSmallShots) {
+        const uint64_t u = __umul64hi(philox_word0((uint64_t)s, seed), T);
+        int lo = 0, hi = dim - 1;  // first x with F[x] > u
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (F[mid] > u) hi = mid;
+            else lo = mid + 1;
+        }
+        out[s] = (uint64_t)lo;
     }
-    out[s] = (uint64_t)lo;
 }
 
 }  // namespace
@@ -372,12 +375,13 @@ hipError_t launch_sample(int prec, const void *psi, int n, const SampleBufs &b, 
     // (also without shots: a workgroup reports a state that cannot be sampled)
     const auto groups = [&](int64_t per) { return dim3((unsigned)std::max<int64_t>(1, (shots + per - 1) / per)); };
     if (n < kBlockBits) {
+        const dim3 g((unsigned)std::min<int64_t>(kSmallGroups, groups(kSmallShots).x));
         if (prec == 0)
-            hipLaunchKernelGGL(sample_small_kernel<float2>, groups(kSmallShots), dim3(kSmallShots), 0, st,
-                               (const float2 *)psi, n, seed, shots, out, b.flag);
+            hipLaunchKernelGGL(sample_small_kernel<float2>, g, dim3(kSmallShots), 0, st, (const float2 *)psi, n, seed,
+                               shots, out, b.flag);
         else
-            hipLaunchKernelGGL(sample_small_kernel<double2>, groups(kSmallShots), dim3(kSmallShots), 0, st,
-                               (const double2 *)psi, n, seed, shots, out, b.flag);
+            hipLaunchKernelGGL(sample_small_kernel<double2>, g, dim3(kSmallShots), 0, st, (const double2 *)psi, n,
+                               seed, shots, out, b.flag);
         return hipGetLastError();
     }
     int64_t nsub, nblk, nchunk;

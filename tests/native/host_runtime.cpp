@@ -1,8 +1,8 @@
-// Host-only driver for libqs's handling of its pinned result buffers: this
-// program defines every HIP entry point that the library imports (an
-// executable's symbols come before those of the shared objects it loads), so
-// that the library's host code runs without a device.  Launches and waits are
-// recorded, launches fail on demand, and operator new throws on demand.
+// Host-only driver for libqs's handling of its pinned result buffers and launch
+// sizes: this program defines every HIP entry point that the library imports
+// (an executable's symbols come before those of the shared objects it loads),
+// so that the library's host code runs without a device.  Launches and waits
+// are recorded, launches fail on demand, and operator new throws on demand.
 // Built and run by tests/test_host_runtime.py; prints "ok <case>" and exits 0.
 #include <cstdint>
 #include <cstdio>
@@ -199,6 +199,23 @@ static int no_memory()
     return 0;
 }
 
+// Launches stay below 2^32 threads, the runtime's limit, for every number of
+// shots of a small state.
+static int many_shots()
+{
+    uint64_t *out = (uint64_t *)0x100000;  // never touched: the shots would go to device memory
+    qs_state s = handle(5, A);
+    CHECK(s);
+    for (const int64_t shots : {(int64_t)1, (int64_t)1 << 20, ((int64_t)1 << 32) + 5, (int64_t)1 << 39}) {
+        const size_t at = events.size();
+        CHECK(qs_sample(s, 1, shots, out, 1) == QS_OK);
+        CHECK(count('L', A, at) >= 1);
+        for (size_t i = at; i < events.size(); ++i) CHECK(events[i].threads < ((uint64_t)1 << 32));
+    }
+    CHECK(qs_free(s) == QS_OK);
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
@@ -206,6 +223,7 @@ int main(int argc, char **argv)
     if (which == "switched_stream") rc = failed_call(true);
     else if (which == "same_stream") rc = failed_call(false);
     else if (which == "no_memory") rc = no_memory();
+    else if (which == "many_shots") rc = many_shots();
     if (rc == 0) printf("ok %s\n", which.c_str());
     return rc;
 }
