@@ -278,6 +278,23 @@ hipError_t launch_batch_reduce(const BatchStep *steps, const int *summed, int co
                                double *sums, hipStream_t st);
 int batch_table_entries();
 
+// Phase-table entries that the single-workgroup kernels keep in LDS.
+constexpr int small_table_room(int prec) { return prec == 0 ? 3072 : 1536; }
+
+// Entries of one layer's phase table in those kernels: one per cut value 0 ..
+// W_t, or none, and then every amplitude evaluates its own factor.  A table
+// costs half as many sines and cosines as it has entries (C and W_t - C share
+// one), the direct way one per amplitude (64 at least: every lane of the wave
+// evaluates), so the table is taken while it is the fewer.  Forward / gradient,
+// complex64, p = 10, us, table and direct: n = 4, W_t = 1400 62 / 120 and 23 /
+// 41; n = 7, 3000 96 / 191 and 26 / 49; n = 7, 200 26 / 48 either way; n = 10,
+// 1400 40 / 84 either way; n = 11, 1400 48 / 115 and 69 / 156.
+constexpr int small_table_entries(int prec, int n, int64_t W)
+{
+    const int64_t dim = (int64_t)1 << (n < 6 ? 6 : n);
+    return W + 1 <= small_table_room(prec) && (W + 2) / 2 <= dim ? (int)(W + 1) : 0;
+}
+
 // Single-workgroup kernels for n <= T: a chunk of up to kSmallMaxLayers layers.
 struct SmallProg {
     void *psi;

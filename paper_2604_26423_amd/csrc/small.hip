@@ -18,7 +18,7 @@
 // waves at most: with sixteen each exchange costs more than its halved
 // register work saves.  The phase factors are a table over the cut values
 // 0..W_t, evaluated once per layer, instead of a sine and cosine per
-// amplitude and layer.  The factors, the order of the qubits (0 to n - 1
+// amplitude and layer, where that is fewer (small_table_entries).  The factors, the order of the qubits (0 to n - 1
 // forward, back in reverse) and each operation's rounding are those of a plain
 // loop over the qubits.  Measured against that loop in LDS (1024 threads, one
 // barrier per qubit): see launch_small_forward.
@@ -42,7 +42,7 @@ template <int N> struct SmallCfg {
 };
 
 // Phase-table entries in LDS: as many layers as fit are evaluated at once.
-template <typename V> constexpr int kSmallTab = sizeof(V) == 8 ? 3072 : 1536;
+template <typename V> constexpr int kSmallTab = small_table_room(sizeof(V) == 8 ? 0 : 1);
 
 // One half of an RX pair, a' = c a - i s b (b: the other amplitude).  Of the
 // two products of a part one is rounded and the other goes into the fused
@@ -199,7 +199,7 @@ __device__ __forceinline__ void small_get(V (&v)[NR], const V *lds, int tid)
 
 // Phase factors of the thread's amplitudes: from the layer's table, or
 // evaluated here where the table does not hold C (a diagonal outside 0..W_t,
-// or a W_t that is too large for a table): one pass of the loop per such
+// or a W_t for which there is no table): one pass of the loop per such
 // register, so that the sine and cosine are in the code once.
 template <typename V, int NR>
 __device__ __forceinline__ void small_factors(V (&f)[NR], const V *tab, int entries, const int32_t (&C)[NR],
@@ -232,11 +232,11 @@ struct SmallLds {
     double red[2 * 8];
 };
 
-// Entries of one layer's table (0: none fits) and the layers held at once.
-template <typename V>
+// Entries of one layer's table (0: none) and the layers held at once.
+template <typename V, int N>
 __device__ __forceinline__ void small_tab_geom(int64_t W, int &entries, int &group)
 {
-    entries = W + 1 <= kSmallTab<V> ? (int)(W + 1) : 0;
+    entries = small_table_entries(sizeof(V) == 8 ? 0 : 1, N, W);
     group = entries ? kSmallTab<V> / entries : kSmallMaxLayers;
 }
 
@@ -281,7 +281,7 @@ __global__ void __launch_bounds__(SmallCfg<N>::NT) small_forward(SmallProg sp)
         sh.s[tid] = (R)sin(0.5 * sp.tx[tid]);
     }
     int entries, group, base = 0;
-    small_tab_geom<V>(sp.W, entries, group);
+    small_tab_geom<V, N>(sp.W, entries, group);
     if (!sp.diag) group = kSmallMaxLayers;
     for (int L = 0; L < sp.nlayers; ++L) {
         if (L % group == 0) {
@@ -384,7 +384,7 @@ __global__ void __launch_bounds__(SmallCfg<N>::NT) small_adjoint(SmallProg sp)
         }
     }
     int entries, group, base = sp.nlayers;
-    small_tab_geom<V>(sp.W, entries, group);
+    small_tab_geom<V, N>(sp.W, entries, group);
     for (int L = sp.nlayers - 1; L >= 0; --L) {
         if (L < base) {
             __syncthreads();
