@@ -408,6 +408,31 @@ struct SampleBufs {
     uint64_t *chunk;   // chunk sums
     int32_t *flag;     // [0]: the total is zero; [1]: a sum reached 2^64
 };
+// Whether a state of 2^n stored amplitudes, n >= 13, has its shots drawn by one
+// lane each rather than by 16 lanes each (sample.hip).  Few shots are bound by
+// the chain of one shot, which 16 lanes shorten (10,000 at n = 27: 24 -> 10 us;
+// 2^16 shots take the same either way); many by their instructions and their
+// traffic.  Then one lane per shot is ahead while the prefix sums it searches
+// stay in the caches near the CU, and again when the shots are so many that
+// each amplitude's line serves several of them; complex128, whose 64 amplitudes
+// are 1 KB that 16 lanes read whole, keeps it for longer.  Whole calls, us, one
+// lane / 16 lanes (16 shots in turn from 2^19 on):
+//   shots        n = 14        n = 16         n = 20         n = 24         n = 27
+//   complex64
+//   2^18       47 /   80      56 /   81      74 /   85     104 /  114     266 /  270
+//   2^20      103 /  130     145 /  131     196 /  166     309 /  253     592 /  480
+//   2^24     1211 / 1535    1948 / 1535    2644 / 2073    3075 / 2839    3962 / 4585
+//   complex128
+//   2^18       47 /   81      58 /   81      77 /   88     133 /  146     469 /  485
+//   2^20      115 /  146     157 /  174     211 /  228     386 /  361     812 /  790
+//   2^24     1421 / 1803    2103 / 2306    2648 / 3101    3534 / 4293    4813 / 6588
+constexpr bool shot_lanes(int prec, int n, int64_t shots)
+{
+    if (shots < 1 << 17) return false;
+    if (shots < 1 << 19) return true;
+    if (prec == 0) return n <= 15 || (n >= 25 && shots >= 1 << 23);
+    return n <= 22 || shots >= 1 << 22;
+}
 void sample_sizes(int n, int64_t *nsub, int64_t *nblk, int64_t *nchunk);
 // sym_n > 0: psi is the complement-symmetric layout of sym_n qubits (n =
 // sym_n - 1 stored bits); each drawn z is returned as the full index y(z) or

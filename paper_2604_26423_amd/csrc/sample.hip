@@ -188,13 +188,44 @@ __global__ void __launch_bounds__(kScanThreads) scan_blocks_kernel(uint64_t *blk
     if (tid == 0) chunk[blockIdx.x] = total;
 }
 
+constexpr int kShotThreads = 256;
+constexpr int kMaxChunks = 256;  // 2^34 stored amplitudes
+
+// Exclusive prefixes of the chunk sums into cs, by every workgroup, and the
+// total; the first workgroup reports a zero total or a sum that wraps.
+__device__ __forceinline__ uint64_t scan_chunks(const uint64_t *chunk, int64_t nchunk, uint64_t *cs, uint64_t *red,
+                                                int tid, int32_t *flag)
+{
+    uint64_t T;
+    int32_t over = 0;
+    cs[tid] = block_scan_u64(tid < nchunk ? chunk[tid] : 0, red, tid, &T, over);
+    if (blockIdx.x == 0) {
+        if (over) flag[1] = 2;
+        if (T == 0 && tid == 0) flag[0] = 1;
+    }
+    __syncthreads();
+    return T;
+}
+
+// The basis state of stored index x; r1: word 1 of the shot's Philox output.
+// Complement-symmetric layout (sym_n qubits): z -> y(z) (suffix XOR), or its
+// complement.
+__device__ __forceinline__ uint64_t shot_state(int64_t x, uint64_t r1, int sym_n)
+{
+    uint64_t xo = (uint64_t)x;
+    if (sym_n) {
+#pragma unroll
+        for (int sh = 1; sh < 64; sh <<= 1) xo ^= xo >> sh;
+        if (r1 >> 63) xo ^= (~0ull) >> (64 - sym_n);
+    }
+    return xo;
+}
+
 // Lanes that work on one shot together, and the shots that such a group draws
 // one after the other: one, or kShotRounds from kManyShots on.
 constexpr int kShotLanes = 16;
-constexpr int kShotThreads = 256;
 constexpr int64_t kManyShots = 1 << 19;
 constexpr int kShotRounds = 16;
-constexpr int kMaxChunks = 256;  // 2^34 stored amplitudes
 
 // Number of leading lanes of the shot's group for which yes holds.
 __device__ __forceinline__ int group_count(bool yes)
@@ -223,14 +254,10 @@ __device__ __forceinline__ int64_t group_last_le(const uint64_t *a, int64_t len,
 // find the block of 8192 in a chunk, two the sub-block, and the 64 amplitudes
 // are read at once and scanned across the lanes (one lane per shot took 20
 // binary-search steps and a serial walk over the amplitudes: 24 us for 10,000
-// shots at n = 27, 10 us now).  The chunk sums are scanned by every workgroup
-// in LDS; the first one reports a zero total or a sum that wraps.  With shots
-// enough to fill the chip the latency is hidden and the work per shot counts:
-// a group then draws 16 shots in turn, so that the chunk scan is shared by 256
-// shots and a wave's lanes evaluate 64 Philox outputs at once (whole calls with
-// 10^6 shots, n = 16 / 27: one lane per shot 167 / 612 us, a group's single
-// shot 218 / 487, 16 in turn 131 / 488; with 10^5 shots at n = 27 16 in turn leave
-// the chip idle, 269 against 233; four lanes per shot lost, 289 / 888).
+// shots at n = 27, 10 us now).  With shots enough to fill the chip the latency is
+// hidden and the work per shot counts: a group then draws 16 shots in turn, so
+// that the chunk scan is shared by 256 shots and a wave's lanes evaluate 64
+// Philox outputs at once, or every lane draws a shot of its own (shot_lanes).
 template <typename V>
 __global__ void __launch_bounds__(kShotThreads) sample_shots_kernel(const V *psi, const uint64_t *sub,
                                                                     const uint64_t *blk, const uint64_t *chunk,
@@ -242,14 +269,7 @@ __global__ void __launch_bounds__(kShotThreads) sample_shots_kernel(const V *psi
     __shared__ uint64_t red[kShotThreads / 64];
     constexpr int kGroups = 64 / kShotLanes;  // of a wave
     const int tid = threadIdx.x, lane = tid & 63, g = lane & (kShotLanes - 1);
-    uint64_t T;
-    int32_t over = 0;
-    cs[tid] = block_scan_u64(tid < nchunk ? chunk[tid] : 0, red, tid, &T, over);
-    if (blockIdx.x == 0) {
-        if (over) flag[1] = 2;
-        if (T == 0 && tid == 0) flag[0] = 1;
-    }
-    __syncthreads();
+    const uint64_t T = scan_chunks(chunk, nchunk, cs, red, tid, flag);
     // lane i evaluates the draw of the wave's shot i (i < kGroups * rounds <= 64)
     const int64_t s0 = ((int64_t)blockIdx.x * (kShotThreads / 64) + (tid >> 6)) * (kGroups * rounds);
     uint64_t w0, w1;
@@ -298,15 +318,61 @@ __global__ void __launch_bounds__(kShotThreads) sample_shots_kernel(const V *psi
                     found = true;
                 }
             }
-            uint64_t xo = (uint64_t)x;
-            if (sym_n) {  // z -> y(z) (suffix XOR), or its complement over sym_n bits
-#pragma unroll
-                for (int sh = 1; sh < 64; sh <<= 1) xo ^= xo >> sh;
-                if (r1 >> 63) xo ^= (~0ull) >> (64 - sym_n);
-            }
-            out[s] = xo;
+            out[s] = shot_state(x, r1, sym_n);
         }
     }
+}
+
+// Largest i in [0, len) with a[i] <= u (a nondecreasing, a[0] = 0 <= u).
+__device__ __forceinline__ int64_t last_le(const uint64_t *a, int64_t len, uint64_t u)
+{
+    int64_t lo = 0, hi = len - 1;
+    while (lo < hi) {
+        const int64_t mid = lo + (hi - lo + 1) / 2;
+        if (a[mid] <= u) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// One lane per shot: a long chain (20 probes and a walk over the amplitudes),
+// but few instructions, for many shots (shot_lanes).
+template <typename V>
+__global__ void __launch_bounds__(kShotThreads) sample_lanes_kernel(const V *psi, const uint64_t *sub,
+                                                                    const uint64_t *blk, const uint64_t *chunk,
+                                                                    int64_t nchunk, int64_t nblk, uint64_t seed,
+                                                                    int64_t shots, uint64_t *out, int32_t *flag,
+                                                                    int sym_n)
+{
+    __shared__ uint64_t cs[kMaxChunks];
+    __shared__ uint64_t red[kShotThreads / 64];
+    const int tid = threadIdx.x;
+    const uint64_t T = scan_chunks(chunk, nchunk, cs, red, tid, flag);
+    const int64_t s = (int64_t)blockIdx.x * kShotThreads + tid;
+    if (s >= shots) return;
+    uint64_t r0, r1;
+    philox_words01((uint64_t)s, seed, r0, r1);
+    uint64_t u = __umul64hi(r0, T);
+    const int64_t c = last_le(cs, nchunk, u);
+    u -= cs[c];
+    const int64_t b0 = c * kBlkPerChunk;
+    const int64_t blen = (nblk - b0) < kBlkPerChunk ? (nblk - b0) : kBlkPerChunk;
+    const int64_t b = b0 + last_le(blk + b0, blen, u);
+    u -= blk[b];
+    const int64_t j = last_le(sub + b * kSubPerBlock, kSubPerBlock, u);
+    u -= sub[b * kSubPerBlock + j];
+    const int64_t x0 = (b << kBlockBits) + (j << kSubBits);
+    const int64_t fb = swz_fold(b) << kSwzDst;
+    uint64_t acc = 0;
+    int64_t x = x0 + 63;
+    for (int t = 0; t < 64; ++t) {
+        acc += qval_of(psi[(x0 + t) ^ fb], flag + 1);
+        if (acc > u) {
+            x = x0 + t;
+            break;
+        }
+    }
+    out[s] = shot_state(x, r1, sym_n);
 }
 
 // n < 13: every workgroup builds the whole CDF in LDS and draws kSmallShots
@@ -398,6 +464,18 @@ hipError_t launch_sample(int prec, const void *psi, int n, const SampleBufs &b, 
     hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)nchunk), dim3(kScanThreads), 0, st, b.blk, nblk, b.chunk,
                        b.flag);
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (shot_lanes(prec, n, shots)) {
+        const dim3 g = groups(kShotThreads);
+        if (prec == 0)
+            hipLaunchKernelGGL(sample_lanes_kernel<float2>, g, dim3(kShotThreads), 0, st, (const float2 *)psi,
+                               (const uint64_t *)b.sub, (const uint64_t *)b.blk, (const uint64_t *)b.chunk, nchunk,
+                               nblk, seed, shots, out, b.flag, sym_n);
+        else
+            hipLaunchKernelGGL(sample_lanes_kernel<double2>, g, dim3(kShotThreads), 0, st, (const double2 *)psi,
+                               (const uint64_t *)b.sub, (const uint64_t *)b.blk, (const uint64_t *)b.chunk, nchunk,
+                               nblk, seed, shots, out, b.flag, sym_n);
+        return hipGetLastError();
+    }
     const int rounds = shots < kManyShots ? 1 : kShotRounds;
     const dim3 g = groups((int64_t)(kShotThreads / kShotLanes) * rounds);
     if (prec == 0)

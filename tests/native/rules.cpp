@@ -19,6 +19,23 @@ int main()
                     return 1;
                 }
             }
+    // Shots: 16 lanes each below 2^17, one lane each wherever that is the faster
+    // way (measured, see shot_lanes), and the same for every larger count once
+    // the largest threshold is passed.
+    struct Shots {
+        int prec, n;
+        int64_t shots;
+        bool lanes;
+    };
+    const Shots want[] = {{0, 27, 100000, false}, {0, 13, 1, false},        {0, 13, 400000, true},  {0, 20, 400000, true},
+                          {0, 14, 4000000, true}, {0, 16, 1000000, false},  {0, 24, 1 << 24, false}, {0, 27, 1 << 24, true},
+                          {1, 14, 1000000, true}, {1, 20, 4000000, true},   {1, 24, 1000000, false}, {1, 27, 1 << 22, true},
+                          {1, 34, 1LL << 39, true}};
+    for (const Shots &w : want)
+        if (qs::shot_lanes(w.prec, w.n, w.shots) != w.lanes) {
+            std::printf("shots: precision %d, n = %d, %lld\n", w.prec, w.n, (long long)w.shots);
+            return 1;
+        }
     std::printf("ok\n");
     return 0;
 }
