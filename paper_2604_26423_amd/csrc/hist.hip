@@ -90,9 +90,11 @@ __global__ void __launch_bounds__(kHT) hist_kernel(const V *__restrict__ psi, co
 
 // Sums of the rows, kRowBins bins per workgroup: kRowLanes lanes share a bin's
 // rows, reading kRowBins consecutive words of a row at a time (one lane per
-// bin over all 512 rows took 129 us for 1,900 bins, this 7).  Workgroup 0 also
-// adds up the workgroups' FP64 masses, in order.
-constexpr int kRowBins = 32, kRowLanes = 32;
+// bin over all 512 rows took 129 us for 1,900 bins, 32 lanes 7).  A single row
+// (one workgroup's, or that of the global atomics, which may have 2^24 bins)
+// takes one lane per bin: a whole call with 10^6 bins 23 us, with 32 lanes 85.
+// Workgroup 0 also adds up the workgroups' FP64 masses, in order.
+template <int kRowBins, int kRowLanes>
 __global__ void __launch_bounds__(kRowBins *kRowLanes) hist_rows_kernel(const uint64_t *rows, int nrows, int nbins,
                                                                         int shift, uint64_t *out, const double *fsum,
                                                                         int ngroups, double *total)
@@ -162,9 +164,12 @@ hipError_t launch_histogram(int prec, const void *psi, const int32_t *diag, int 
                                nbins, rows, fsum, flag);
     }
     if (hipError_t e = hipGetLastError()) return e;
-    hipLaunchKernelGGL(hist_rows_kernel, dim3((unsigned)((nbins + kRowBins - 1) / kRowBins)),
-                       dim3(kRowBins * kRowLanes), 0, st, rows, (int)g.rows, nbins, shift, out, fsum, (int)g.groups,
-                       total);
+    if (g.rows == 1)
+        hipLaunchKernelGGL((hist_rows_kernel<256, 1>), dim3((unsigned)((nbins + 255) / 256)), dim3(256), 0, st, rows,
+                           (int)g.rows, nbins, shift, out, fsum, (int)g.groups, total);
+    else
+        hipLaunchKernelGGL((hist_rows_kernel<32, 32>), dim3((unsigned)((nbins + 31) / 32)), dim3(1024), 0, st, rows,
+                           (int)g.rows, nbins, shift, out, fsum, (int)g.groups, total);
     return hipGetLastError();
 }
 

@@ -216,6 +216,22 @@ static int many_shots()
     return 0;
 }
 
+// A histogram with more bins than a workgroup's LDS holds has one row of sums:
+// one thread per bin each to clear it and to write it out, not dozens.
+static int many_bins()
+{
+    const int n = 10, nbins = 1 << 20;
+    int32_t *diag = diagonal(n);
+    uint64_t *out = (uint64_t *)0x100000;  // never touched: the masses would go to device memory
+    qs_state s = handle(n, A);
+    CHECK(s && qs_cost_histogram(s, diag, nbins, out, 1) == QS_OK);
+    uint64_t threads = 0;
+    for (const Event &e : events) threads += e.threads;
+    CHECK(threads <= 2ull * nbins + (1u << 16));
+    CHECK(qs_free(s) == QS_OK);
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
@@ -224,6 +240,7 @@ int main(int argc, char **argv)
     else if (which == "same_stream") rc = failed_call(false);
     else if (which == "no_memory") rc = no_memory();
     else if (which == "many_shots") rc = many_shots();
+    else if (which == "many_bins") rc = many_bins();
     if (rc == 0) printf("ok %s\n", which.c_str());
     return rc;
 }
