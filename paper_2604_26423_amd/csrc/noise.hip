@@ -27,13 +27,22 @@
 // Nothing of this reaches HBM; the vector units bound it (about 640
 // instructions per wave and layer at n = 12, 384 of them the RX updates), then
 // LDS.  So the layer is kept short: a register's cut values stay in registers
-// (reloaded when the frame moves), a layer without flips takes its phase from
-// one table entry per cut value, four qubits are updated across lanes instead
-// of through a second exchange, and the exchange has one barrier.  20,000
-// trajectories, p = 10, eps = 0.003, before (diagonal and two-level table in
-// LDS, two exchanges of two barriers) and now: n = 12 complex64 1546 -> 1120
-// us, complex128 3203 -> 1971, n = 11 669 -> 525, n = 9 186 -> 151.  Registers
-// for three workgroups per CU instead of four: 8% slower.
+// (a layout's are reloaded when a layer is about to start from it in another
+// frame), a layer without errors takes its phase from one table entry per cut
+// value, four qubits are updated across lanes instead of through a second
+// exchange, the exchange has one barrier, and which layers of a chunk have
+// errors is one word.  20,000 trajectories, p = 10, us, before (diagonal and
+// two-level table in LDS, two exchanges of two barriers) and now:
+//   n, precision     eps = 0.0005    0.003           0.05
+//   12, complex64    1363 ->  790    1544 -> 1000    3118 -> 2506
+//   12, complex128   2816 -> 1500                    6007 -> 3979
+//   11, complex64                     672 ->  500    1258 -> 1197
+//   10, complex64                     384 ->  275     633 ->  564
+//    9, complex64     176 ->  135                     286 ->  274
+// 200 trajectories leave most of the chip idle and are bound by one
+// trajectory's chain: n = 12, eps = 0.003 64 -> 66.  Registers for three
+// workgroups of n = 12 per CU instead of four: 8% slower.  The n = 11
+// complex64 kernel spills 6 of its 128 registers, the others none.
 #include "tiles.h"
 
 namespace qs {
@@ -145,11 +154,20 @@ __host__ __device__ __forceinline__ constexpr int noise_slot(int r, int tid)
 // product of the two levels, when they are at most kNoiseDirect (this many let
 // four workgroups of n = 12 share a CU's LDS).
 constexpr int kNoiseDirect = 528;
+// The layer's table goes through LDS from n = 9 on; below, a trajectory's 2^n
+// amplitudes read fewer entries than its 2^(n-2) threads would copy.  20,000
+// trajectories, p = 10, us, through LDS / from global memory: n = 12, eps = 0.05
+// 2556 / 3299; eps = 0.003, n = 10, W_t = 962 307 / 359; n = 8, W_t = 658 113 /
+// 109; n = 6, W_t = 848 160 / 129; n = 4, W_t = 987 333 / 162.
+template <int N> constexpr bool kNoiseStage = N >= 9;
+static_assert(kNoiseDirect >= kTabMax, "the levels of a table take its place in LDS");
 
 struct NoiseShared {
     int nf, wf, ph, cnt;
     uint32_t ex, ez;
+    uint32_t drawn;  // bit i: layer i of the chunk has an error
 };
+static_assert(kNoiseChunk <= 32, "one bit per layer of a chunk");
 
 // LV = 2: two-level phase table (3 W < 2^13, every graph with weights up to
 // 10 tenths at n <= 12); LV = 0: levels read at run time.
@@ -205,16 +223,15 @@ __device__ __forceinline__ int noise_tid(int tid)
     return tid;
 }
 
-// Cut values of the thread's registers in both layouts, for frame m.
-template <int N, int NR>
-__device__ __forceinline__ void noise_cuts(const int32_t *diag, uint32_t m, int tid, int32_t (&lo)[NR], int32_t (&hi)[NR])
+// Cut values of the thread's registers in the top or the low layout, and the
+// frame that they are for.
+template <int N, bool TOP, int NR>
+__device__ __forceinline__ void noise_cuts(const int32_t *diag, uint32_t m, int tid, int32_t (&c)[NR], uint32_t &frame)
 {
     tid = noise_tid(tid);
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        lo[r] = diag[noise_x<N, false>(r, tid) ^ m];
-        hi[r] = diag[noise_x<N, true>(r, tid) ^ m];
-    }
+    for (int r = 0; r < NR; ++r) c[r] = diag[noise_x<N, TOP>(r, tid) ^ m];
+    frame = m;
 }
 
 // Cost layer with its errors, then the mixer, for layer k.  Ascending layers
@@ -222,7 +239,7 @@ __device__ __forceinline__ void noise_cuts(const int32_t *diag, uint32_t m, int 
 template <typename V, int N, int MODE, int LV, bool ASC>
 __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[NoiseCfg<N>::NR], V *lds,
                                             int32_t (&clo)[NoiseCfg<N>::NR], int32_t (&chi)[NoiseCfg<N>::NR],
-                                            V *tab, uint8_t *codes, uint8_t *drawn, uint32_t *fm, int *fw,
+                                            uint32_t &mlo, uint32_t &mhi, V *tab, uint8_t *codes, uint32_t &drawn, uint32_t *fm, int *fw,
                                             NoiseShared &sh, uint32_t &m, int &phi, int &nerr, double &fprev, int tid)
 {
     using Cfg = NoiseCfg<N>;
@@ -236,7 +253,7 @@ __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[N
     if (at == 0) {
         const int len = np.p - k < kNoiseChunk ? np.p - k : kNoiseChunk;
         __syncthreads();  // the previous chunk's codes are no longer read
-        for (int i = tid; i < len; i += NT) drawn[i] = 0;
+        if (tid == 0) sh.drawn = 0;
         __syncthreads();
         for (int i = tid; i < len * G; i += NT) {
             uint8_t c = 0;
@@ -246,18 +263,24 @@ __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[N
                 c = (r0 >> 11) < np.thr ? (uint8_t)(r1 & 15u) : (uint8_t)0;
             }
             codes[i] = c;
-            if (c) drawn[i / G] = 1;
+            if (c) atomicOr(&sh.drawn, 1u << (i / G));
         }
         __syncthreads();
+        drawn = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.drawn);
     }
-    const bool errs = __builtin_amdgcn_readfirstlane(drawn[at]) != 0;
+    const bool errs = (drawn >> at) & 1u;
 
-    // Table of a layer without flips (the same for every trajectory, built by
-    // noise_table_kernel).  The last reads of the previous layer's table and
-    // flags lie before that layer's exchange.
-    const V *two = reinterpret_cast<const V *>(np.tabs) + (size_t)k * (kTabMax + kNoiseDirect);
-    if (np.direct)
-        for (int i = tid; i <= (int)np.W; i += NT) tab[i] = two[kTabMax + i];
+    // Table of the layer (the same for every trajectory, built by
+    // noise_table_kernel): an entry per cut value if nothing flips a sign, else,
+    // and for more cut values than that, its levels.  The last reads of the
+    // previous layer's table and flags lie before that layer's exchange.
+    const bool flat = np.direct && !errs;
+    const V *src = reinterpret_cast<const V *>(np.tabs) + (size_t)k * (kTabMax + kNoiseDirect) + (flat ? kTabMax : 0);
+    if constexpr (kNoiseStage<N>) {
+        const int len = flat ? (int)np.W + 1 : 64 * (np.levels - 1) + 128;
+        for (int i = tid; i < len; i += NT) tab[i] = src[i];
+        src = tab;
+    }
 
     // the layer's errors, moved to its end (one wave, gates in order)
     if (errs && tid < WL) {
@@ -320,6 +343,16 @@ __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[N
     }
     __syncthreads();
 
+    // The frame moves at the end of the layer, and with it the cut values of the
+    // layout that the next one starts from (the other's when a layer starts from
+    // it); their loads go ahead of this layer's arithmetic.
+    const uint32_t next = errs ? m ^ (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ex) : m;
+    if constexpr (ASC) {
+        if (mhi != next) noise_cuts<N, true>(np.diag, next, tid, chi, mhi);
+    } else {
+        if (mlo != next) noise_cuts<N, false>(np.diag, next, tid, clo, mlo);
+    }
+
     // cost phase, in the layout that the layer starts from
     const auto c = [&](int r) {
         if constexpr (ASC) return clo[r];
@@ -327,9 +360,9 @@ __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[N
     };
     const int nf = errs ? __builtin_amdgcn_readfirstlane(sh.nf) : 0;
     V f[NR];
-    if (nf == 0 && np.direct) {
+    if (flat) {
 #pragma unroll
-        for (int r = 0; r < NR; ++r) f[r] = tab[c(r)];
+        for (int r = 0; r < NR; ++r) f[r] = src[c(r)];
     } else {
         int cf[NR];
         const int tf = noise_tid(tid);
@@ -344,12 +377,10 @@ __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[N
         }
         const int u0 = 2 * (int)np.W - (nf ? __builtin_amdgcn_readfirstlane(sh.wf) : 0);
 #pragma unroll
-        for (int r = 0; r < NR; ++r) f[r] = noise_phase<V, LV>(two, np.levels, u0 - c(r) + 2 * cf[r]);
+        for (int r = 0; r < NR; ++r) f[r] = noise_phase<V, LV>(src, np.levels, u0 - c(r) + 2 * cf[r]);
     }
-    uint32_t ex = 0;
     if (errs) {
         const uint32_t ez = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ez);
-        ex = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ex);
         if (ez != 0) {  // Z components of the layer's errors: signs
             const int tz = noise_tid(tid);
 #pragma unroll
@@ -378,10 +409,7 @@ __device__ __forceinline__ void noise_layer(const NoiseProg &np, int k, V (&v)[N
         else if constexpr (2 * RB > N) noise_rx_reg<0, MODE>(v, a, b);
         else noise_regs<N, MODE, 0>(v, a, b);
     }
-    if (ex != 0) {  // the frame moves: so do the cut values
-        m ^= ex;
-        noise_cuts<N>(np.diag, m, tid, clo, chi);
-    }
+    m = next;
     fprev = lay[3];
 }
 
@@ -406,17 +434,17 @@ __device__ __forceinline__ void noise_readout(const NoiseProg &np, const V (&v)[
     }
 }
 
-// Registers for as many workgroups of n = 12 as share a CU's LDS.
+// Registers for as many workgroups of n >= 11 (complex128: 10) as share a CU's
+// LDS; bounded like that the n = 10 complex64 kernel lost 4%.
 template <typename V, int N, int MODE, int LV>
-__global__ void __launch_bounds__(NoiseCfg<N>::NT, (N < 11 ? 1 : sizeof(V) == 8 ? 4 : 2)) noise_kernel(NoiseProg np)
+__global__ void __launch_bounds__(NoiseCfg<N>::NT, (N < (sizeof(V) == 8 ? 11 : 10) ? 1 : sizeof(V) == 8 ? 4 : 2)) noise_kernel(NoiseProg np)
 {
     using Cfg = NoiseCfg<N>;
     using R = typename Real<V>::T;
     constexpr int NR = Cfg::NR, NT = Cfg::NT, G = Cfg::G;
     __shared__ V lds[kNoiseRow<N> << Cfg::RB];
-    __shared__ V tab[kNoiseDirect];
+    __shared__ V tab[kNoiseStage<N> ? kNoiseDirect : 1];
     __shared__ uint8_t codes[kNoiseChunk * G];
-    __shared__ uint8_t drawn[kNoiseChunk];
     __shared__ uint32_t fm[G];
     __shared__ int fw[G];
     __shared__ NoiseShared sh;
@@ -425,7 +453,9 @@ __global__ void __launch_bounds__(NoiseCfg<N>::NT, (N < 11 ? 1 : sizeof(V) == 8 
 
     V v[NR];
     int32_t clo[NR], chi[NR];
-    noise_cuts<N>(np.diag, 0u, tid, clo, chi);
+    uint32_t mlo, mhi, drawn = 0;
+    noise_cuts<N, false>(np.diag, 0u, tid, clo, mlo);
+    noise_cuts<N, true>(np.diag, 0u, tid, chi, mhi);
 #pragma unroll
     for (int r = 0; r < NR; ++r) v[r] = V{(R)np.amp0, (R)0};
     uint32_t m = 0;
@@ -434,15 +464,15 @@ __global__ void __launch_bounds__(NoiseCfg<N>::NT, (N < 11 ? 1 : sizeof(V) == 8 
 
     int k = 0;
     for (; k + 1 < np.p; k += 2) {
-        noise_layer<V, N, MODE, LV, true>(np, k, v, lds, clo, chi, tab, codes, drawn, fm, fw, sh, m, phi, nerr, fprev,
-                                          tid);
-        noise_layer<V, N, MODE, LV, false>(np, k + 1, v, lds, clo, chi, tab, codes, drawn, fm, fw, sh, m, phi, nerr,
-                                           fprev, tid);
+        noise_layer<V, N, MODE, LV, true>(np, k, v, lds, clo, chi, mlo, mhi, tab, codes, drawn, fm, fw, sh, m, phi,
+                                          nerr, fprev, tid);
+        noise_layer<V, N, MODE, LV, false>(np, k + 1, v, lds, clo, chi, mlo, mhi, tab, codes, drawn, fm, fw, sh, m,
+                                           phi, nerr, fprev, tid);
     }
     const bool top = k < np.p;
     if (top)
-        noise_layer<V, N, MODE, LV, true>(np, k, v, lds, clo, chi, tab, codes, drawn, fm, fw, sh, m, phi, nerr, fprev,
-                                          tid);
+        noise_layer<V, N, MODE, LV, true>(np, k, v, lds, clo, chi, mlo, mhi, tab, codes, drawn, fm, fw, sh, m, phi,
+                                          nerr, fprev, tid);
 
     double acc[2] = {0.0, 0.0};
     if (top) noise_readout<V, N, true>(np, v, chi, m, phi, (R)fprev, acc, tid);
