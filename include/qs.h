@@ -303,8 +303,9 @@ qs_status qs_adjoint_ckpt_bytes(qs_state s, int p, size_t *bytes);
  * Batched circuits (target workload: hundreds of small, uneven circuits).
  * Each circuit has its own instance, depth and angles; all of them run the
  * forward circuit and the adjoint gradient of qs_adjoint_grad in rounds:
- * launch r works on pass r of every circuit that has one.  Single-circuit tile
- * kernels and the batched kernel compute the same arithmetic.
+ * round r works on pass r of every circuit that has one.  Single-circuit tile
+ * kernels and the batched kernels compute the same arithmetic; a circuit's
+ * results do not depend on the circuits that share its batch.
  */
 #define QS_BATCH_MAX_QUBITS 30
 

@@ -43,8 +43,9 @@ int qs_plan_check(int n, int prec, int p, char *msg, size_t msg_len);
  * allocation without overlap; the steps of a circuit are consecutive; round
  * r's work items are exactly the chunks of step r of every circuit that has
  * one; chunks cover each pass's tiles; table offsets, rows of partial sums and
- * result slots are in range; each circuit has 2 (p (P - 1) + 1) - 1 steps.
- * Returns 0 if every check holds, 1 with a message otherwise, 2 for invalid
+ * result slots are in range; each circuit has 2 (p (P - 1) + 1) - 1 steps; the
+ * kernel of a step follows from its own angles (checked with small angles, with
+ * one large one in every third circuit and with large ones only).  Returns 0 if every check holds, 1 with a message otherwise, 2 for invalid
  * arguments.
  */
 struct qs_circuit;

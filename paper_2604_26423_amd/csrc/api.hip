@@ -905,8 +905,7 @@ void plan_batch(qs_batch b)
 
 struct BatchSchedule {
     int64_t rows = 0, tabs = 0;
-    bool fast = false;   // every stage in tangent form (see batch.hip)
-    int tb = 0;          // log2 threads of the kernel
+    std::vector<char> kernels;  // per round: bit 0: some step is general, bit 1: some step is fast
 };
 
 // The steps of every circuit (forward passes, turnaround, reverse passes) with
@@ -916,10 +915,7 @@ BatchSchedule build_batch_schedule(qs_batch b, const double *theta_zz, const dou
 {
     BatchSchedule sch;
     const int T = tile_bits(b->prec);
-    double factor;
-    sch.fast = true;
-    for (int64_t k = 0; k < b->angle_off.back(); ++k) sch.fast = sch.fast && rx_stage(theta_x[k], 1, &factor).tan;
-    sch.tb = batch_thread_bits(b->prec, sch.fast);
+    sch.kernels.assign(b->round_items.size(), 0);
     b->steps_h.clear();
     b->summed_h.clear();
     const int tabn = batch_table_entries();
@@ -934,7 +930,16 @@ BatchSchedule build_batch_schedule(qs_batch b, const double *theta_zz, const dou
         const int64_t ntiles = (int64_t)1 << (n - T);
         auto add = [&](const KSpec &k, int kind) {
             BatchStep s{};
-            s.pp = make_prog_raw(psi, n, b->prec, nullptr, geo[k.pass], k, cc, sch.tb);
+            // the kernel is chosen step by step: it does not depend on the other
+            // circuits, and neither do the step's results
+            for (int fast = 1; fast >= 0; --fast) {
+                const int tb = batch_thread_bits(b->prec, fast != 0);
+                s.pp = make_prog_raw(psi, n, b->prec, nullptr, geo[k.pass], k, cc, tb);
+                s.mode = tile_mode(s.pp, T, tb);
+                s.fast = fast;
+                if (batch_step_fast(s)) break;
+            }
+            sch.kernels[b->steps_h.size() - (size_t)b->step0[c]] |= (char)(1 << s.fast);
             s.pp.xcd_remap = 0;
             s.kind = kind;
             s.circuit = c;
@@ -950,7 +955,6 @@ BatchSchedule build_batch_schedule(qs_batch b, const double *theta_zz, const dou
                 s.map[1] = k.phase >= 0 ? 2 + k.phase : -1;
                 s.map[2] = k.pre >= 0 ? 2 + p + k.pre : -1;
             }
-            s.mode = tile_mode(s.pp, T, sch.tb);
             s.tiles_per_chunk = batch_chunk(ntiles);
             s.chunks = (int)((ntiles + s.tiles_per_chunk - 1) / s.tiles_per_chunk);
             s.row0 = -1;
@@ -1715,7 +1719,9 @@ qs_status qs_batch_forward_grad(qs_batch b, const double *theta_zz, const double
         args.tabs = b->tabs.p;
         HIPCHK(launch_batch_tables(b->prec, args.steps, nsteps, b->tabs.p, b->stream), where);
         for (size_t r = 0; r < b->round_items.size(); ++r)
-            HIPCHK(launch_batch_round(b->prec, sch.fast, args, (int)r, b->round_items[r], b->stream), where);
+            for (int fast = 1; fast >= 0; --fast)
+                if (sch.kernels[r] >> fast & 1)
+                    HIPCHK(launch_batch_round(b->prec, fast != 0, args, (int)r, b->round_items[r], b->stream), where);
         HIPCHK(launch_batch_reduce(args.steps, (const int *)b->index.p, nsum, args.partials, sums, b->stream), where);
         b->sums_h.resize((size_t)nsum * kSlots);
         if (!pin) HIPCHK(hipMemcpyAsync(b->sums_h.data(), sums, sbytes, hipMemcpyDeviceToHost, b->stream), where);
@@ -1880,19 +1886,19 @@ __attribute__((format(printf, 3, 4))) int plan_fail(char *msg, size_t len, const
 
 extern "C" {
 
-int qs_batch_plan_check(int count, const qs_circuit *circuits, int prec, char *msg, size_t msg_len)
+namespace {
+// qs_batch_plan_check for one set of angles: large = 0 none beyond the tangent
+// form, 1 one layer of every third circuit, 2 all of them.
+int batch_plan_check(int count, const qs_circuit *circuits, int prec, int large, char *msg, size_t msg_len)
 {
 #define bad(...) plan_fail(msg, msg_len, __VA_ARGS__)
-    if (msg && msg_len) msg[0] = 0;
-    if (count < 1 || !circuits || (prec != QS_C64 && prec != QS_C128)) return 2;
     const int T = tile_bits(prec);
-    for (int i = 0; i < count; ++i)
-        if (circuits[i].n <= T || circuits[i].n > QS_BATCH_MAX_QUBITS || circuits[i].p < 1 || !circuits[i].w_tenths)
-            return 2;
     qs_batch_s b;
     const size_t total = layout_batch(&b, count, circuits, prec);
     b.mem = (void *)(uintptr_t)((uint64_t)1 << 40);  // never dereferenced
-    std::vector<double> tzz(b.angle_off.back(), 0.3), tx(b.angle_off.back(), 0.4);
+    std::vector<double> tzz(b.angle_off.back(), 0.3), tx(b.angle_off.back(), large == 2 ? 2.4 : 0.4);
+    if (large == 1)
+        for (int c = 0; c < count; c += 3) tx[(size_t)b.angle_off[c] + (size_t)b.p[c] / 2] = -2.4;
     plan_batch(&b);
     const BatchSchedule sch = build_batch_schedule(&b, tzz.data(), tx.data());
     const std::vector<BatchStep> &st = b.steps_h;
@@ -1936,8 +1942,13 @@ int qs_batch_plan_check(int count, const qs_circuit *circuits, int prec, char *m
         if (s.tab_off >= 0 && (s.tab_off % tabn || s.tab_off / tabn >= sch.tabs)) return bad("step %d: table offset", i);
         for (int k = 0; k < kSlots; ++k)
             if (s.map[k] >= 2 + 2 * b.p[s.circuit]) return bad("step %d: result slot", i);
-        if (s.mode != tile_mode(s.pp, T, sch.tb) || (sch.fast && !batch_step_fast(s)))
-            return bad("step %d: stage mode", i);
+        // the kernel: the fast one exactly for steps in tangent form, with windows
+        // planned for its threads, launched in the step's round
+        const bool tan = !(s.pp.has_pre && !s.pp.pre.tan) && !(s.pp.has_post && !s.pp.post.tan);
+        if ((s.fast != 0) != tan || s.pp.tb != batch_thread_bits(prec, s.fast != 0) ||
+            s.mode != tile_mode(s.pp, T, s.pp.tb) || (s.fast && !batch_step_fast(s)) ||
+            !(sch.kernels[(size_t)(i - b.step0[s.circuit])] >> s.fast & 1))
+            return bad("step %d: kernel", i);
     }
     if (row != sch.rows || nsum != (int)b.summed_h.size()) return bad("row count");
     for (int c = 0; c < count; ++c) {
@@ -1962,6 +1973,20 @@ int qs_batch_plan_check(int count, const qs_circuit *circuits, int prec, char *m
     }
     if (next != b.items_h.size() || (int)b.round_items.size() != (count ? seen[b.order[0]] : 0)) return bad("item count");
 #undef bad
+    return 0;
+}
+}  // namespace
+
+int qs_batch_plan_check(int count, const qs_circuit *circuits, int prec, char *msg, size_t msg_len)
+{
+    if (msg && msg_len) msg[0] = 0;
+    if (count < 1 || !circuits || (prec != QS_C64 && prec != QS_C128)) return 2;
+    for (int i = 0; i < count; ++i)
+        if (circuits[i].n <= tile_bits(prec) || circuits[i].n > QS_BATCH_MAX_QUBITS || circuits[i].p < 1 ||
+            !circuits[i].w_tenths)
+            return 2;
+    for (int large = 0; large <= 2; ++large)
+        if (int rc = batch_plan_check(count, circuits, prec, large, msg, msg_len)) return rc;
     return 0;
 }
 

@@ -246,6 +246,7 @@ struct BatchStep {
     PassProg pp;
     int kind;             // 0 = forward pass, 1 = turnaround, 2 = reverse pass
     int mode;             // stage code path (tile_mode)
+    int fast;             // which of the two batch kernels runs it (batch_step_fast)
     int circuit;
     int chunks;           // work items of this step (the same for every step of a circuit)
     int64_t tiles_per_chunk;
@@ -268,9 +269,9 @@ struct BatchArgs {
     void *tabs;                  // phase tables (float2 / double2)
 };
 
-// fast: every stage in tangent form, every step one that batch_step_fast accepts (see batch.hip)
+// fast: the kernel for steps in tangent form (see batch.hip)
 int batch_thread_bits(int prec, bool fast);  // log2 threads its windows are planned for
-bool batch_step_fast(const BatchStep &s);
+bool batch_step_fast(const BatchStep &s);  // s (pp, mode) can take that kernel
 hipError_t launch_batch_tables(int prec, const BatchStep *steps, int nsteps, void *tabs, hipStream_t st);
 hipError_t launch_batch_round(int prec, bool fast, const BatchArgs &a, int round, int64_t nitems, hipStream_t st);
 // sums[kSlots * j + k] = slot k of step summed[j], over its items in a fixed order, j < count.
