@@ -45,7 +45,9 @@ int qs_plan_check(int n, int prec, int p, char *msg, size_t msg_len);
  * one; chunks cover each pass's tiles; table offsets, rows of partial sums and
  * result slots are in range; each circuit has 2 (p (P - 1) + 1) - 1 steps; the
  * kernel of a step follows from its own angles (checked with small angles, with
- * one large one in every third circuit and with large ones only).  Returns 0 if every check holds, 1 with a message otherwise, 2 for invalid
+ * one large one in every third circuit and with large ones only), its kind of
+ * memory access from the size of its own circuit.
+ * Returns 0 if every check holds, 1 with a message otherwise, 2 for invalid
  * arguments.
  */
 struct qs_circuit;

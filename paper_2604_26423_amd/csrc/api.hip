@@ -373,7 +373,6 @@ PassProg make_prog_raw(void *psi, int n, int prec, double *partials, const PassG
     if (pp.has_pre) stage_scales(pp.pre, pp.A, g.targets, g.pairs, T, tb);
     if (pp.has_post) stage_scales(pp.post, pp.B, g.targets, g.pairs, T, tb);
     pp.factor = pp.fpre * pp.fpost;
-    pp.stream = !pp.has_phase && !pp.readout && !pp.pairs;
     pp.phase_win = pp.has_pre ? last_window(pp.A) : pp.load_win;
     pp.final_win = last_window(pp.B);
     if (pp.has_phase) pp.theta_zz = cc.tzz[k.phase];
@@ -405,6 +404,11 @@ PassProg make_prog_raw(void *psi, int n, int prec, double *partials, const PassG
 // streamed, forward junction 15.8 against 18.8).
 // A forward pass that only applies a stage streams at every size, and the
 // complement-symmetric layout (two-bit factors, 6% slower with it) at none.
+// A batch's steps follow the same rule, by the size of their own circuit (the
+// complex64 batch kernel's reverse steps always take ordinary accesses): one
+// circuit of 20 qubits in complex128 162 -> 153 us, 64 of 18 to 20 qubits 6.15
+// -> 5.63 ms, complex64 3.73 -> 3.65, against nontemporal stores in every plain
+// and turnaround step, at 26 qubits 28.4 -> 28.8 ms.
 int pass_streams(const PassProg &pp, int prec, int kind)
 {
     if (pp.pairs) return 0;
@@ -941,6 +945,7 @@ BatchSchedule build_batch_schedule(qs_batch b, const double *theta_zz, const dou
             }
             sch.kernels[b->steps_h.size() - (size_t)b->step0[c]] |= (char)(1 << s.fast);
             s.pp.xcd_remap = 0;
+            s.pp.stream = pass_streams(s.pp, b->prec, kind);
             s.kind = kind;
             s.circuit = c;
             for (int j = 0; j < kSlots; ++j) s.map[j] = -1;
@@ -1949,6 +1954,7 @@ int batch_plan_check(int count, const qs_circuit *circuits, int prec, int large,
             s.mode != tile_mode(s.pp, T, s.pp.tb) || (s.fast && !batch_step_fast(s)) ||
             !(sch.kernels[(size_t)(i - b.step0[s.circuit])] >> s.fast & 1))
             return bad("step %d: kernel", i);
+        if (s.pp.stream != pass_streams(s.pp, prec, s.kind)) return bad("step %d: streaming", i);
     }
     if (row != sch.rows || nsum != (int)b.summed_h.size()) return bad("row count");
     for (int c = 0; c < count; ++c) {
