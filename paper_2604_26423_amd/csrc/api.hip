@@ -910,7 +910,18 @@ void plan_batch(qs_batch b)
 struct BatchSchedule {
     int64_t rows = 0, tabs = 0;
     std::vector<char> kernels;  // per round: bit 0: some step is general, bit 1: some step is fast
+    // Rounds whose sums wait for their reduction together: from round `begin`
+    // (to the next group's) on, summed steps `first` .. `first + count - 1`.
+    struct Group {
+        size_t begin;
+        int first, count;
+    };
+    std::vector<Group> groups;
 };
+
+// Rows that the partial sums of a group of rounds take at most (one round's, if
+// those are more).
+constexpr int64_t kBatchMaxRows = kMaxRows;
 
 // The steps of every circuit (forward passes, turnaround, reverse passes) with
 // their rows and tables.  Host only: pointers into b->mem are computed, never
@@ -963,17 +974,36 @@ BatchSchedule build_batch_schedule(qs_batch b, const double *theta_zz, const dou
             s.tiles_per_chunk = batch_chunk(ntiles);
             s.chunks = (int)((ntiles + s.tiles_per_chunk - 1) / s.tiles_per_chunk);
             s.row0 = -1;
-            if (kind >= 1) {
-                s.row0 = sch.rows;
-                sch.rows += s.chunks;
-                b->summed_h.push_back((int)b->steps_h.size());
-            }
             s.tab_off = s.pp.has_phase ? (sch.tabs++) * tabn : -1;
             b->steps_h.push_back(s);
         };
         for (size_t i = 0; i + 1 < ks.size(); ++i) add(ks[i], 0);
         add(ks.back(), 1);
         for (int i = (int)ks.size() - 2; i >= 0; --i) add(ks[i], 2);
+    }
+    // rows of the steps that write sums, round by round
+    int64_t used = 0;
+    for (size_t r = 0; r < b->round_items.size(); ++r) {
+        auto each = [&](auto &&f) {  // the steps of round r that write sums
+            for (int c : b->order) {
+                const size_t i = (size_t)b->step0[c] + r;
+                if (i >= b->steps_h.size() || b->steps_h[i].circuit != c) break;  // (most steps first)
+                if (b->steps_h[i].kind >= 1) f(i);
+            }
+        };
+        int64_t rows = 0;
+        each([&](size_t i) { rows += b->steps_h[i].chunks; });
+        if (r == 0 || used + rows > kBatchMaxRows) {
+            sch.groups.push_back({r, (int)b->summed_h.size(), 0});
+            used = 0;
+        }
+        each([&](size_t i) {
+            b->steps_h[i].row0 = used;
+            used += b->steps_h[i].chunks;
+            b->summed_h.push_back((int)i);
+            ++sch.groups.back().count;
+        });
+        sch.rows = std::max(sch.rows, used);
     }
     return sch;
 }
@@ -1723,11 +1753,18 @@ qs_status qs_batch_forward_grad(qs_batch b, const double *theta_zz, const double
         args.partials = (double *)b->partials.p;
         args.tabs = b->tabs.p;
         HIPCHK(launch_batch_tables(b->prec, args.steps, nsteps, b->tabs.p, b->stream), where);
-        for (size_t r = 0; r < b->round_items.size(); ++r)
-            for (int fast = 1; fast >= 0; --fast)
-                if (sch.kernels[r] >> fast & 1)
-                    HIPCHK(launch_batch_round(b->prec, fast != 0, args, (int)r, b->round_items[r], b->stream), where);
-        HIPCHK(launch_batch_reduce(args.steps, (const int *)b->index.p, nsum, args.partials, sums, b->stream), where);
+        for (size_t g = 0; g < sch.groups.size(); ++g) {
+            const BatchSchedule::Group &gr = sch.groups[g];
+            const size_t end = g + 1 < sch.groups.size() ? sch.groups[g + 1].begin : b->round_items.size();
+            for (size_t r = gr.begin; r < end; ++r)
+                for (int fast = 1; fast >= 0; --fast)
+                    if (sch.kernels[r] >> fast & 1)
+                        HIPCHK(launch_batch_round(b->prec, fast != 0, args, (int)r, b->round_items[r], b->stream),
+                               where);
+            if (gr.count > 0)
+                HIPCHK(launch_batch_reduce(args.steps, (const int *)b->index.p + gr.first, gr.count, args.partials,
+                                           sums + (int64_t)gr.first * kSlots, b->stream), where);
+        }
         b->sums_h.resize((size_t)nsum * kSlots);
         if (!pin) HIPCHK(hipMemcpyAsync(b->sums_h.data(), sums, sbytes, hipMemcpyDeviceToHost, b->stream), where);
         HIPCHK(hipStreamSynchronize(b->stream), where);
@@ -1735,15 +1772,17 @@ qs_status qs_batch_forward_grad(qs_batch b, const double *theta_zz, const double
             memcpy(b->sums_h.data(), pin, sbytes);
             b->host.done();
         }
-        std::vector<double> res;
-        for (int j = 0; j < nsum;) {  // the steps of one circuit, in step order
-            const int c = b->steps_h[(size_t)b->summed_h[(size_t)j]].circuit, p = b->p[c];
-            res.assign(2 + 2 * (size_t)p, 0.0);
-            for (; j < nsum && b->steps_h[(size_t)b->summed_h[(size_t)j]].circuit == c; ++j) {
-                const BatchStep &st = b->steps_h[(size_t)b->summed_h[(size_t)j]];
-                for (int k = 0; k < kSlots; ++k)
-                    if (st.map[k] >= 0) res[(size_t)st.map[k]] += b->sums_h[(size_t)j * kSlots + k];
-            }
+        // circuit c's results: 2 + 2 p values from 2 c + 2 (the layers before it)
+        std::vector<double> all(2 * (size_t)b->count + 2 * (size_t)b->angle_off.back(), 0.0);
+        auto results = [&](int c) { return all.data() + 2 * (size_t)c + 2 * (size_t)b->angle_off[c]; };
+        for (int j = 0; j < nsum; ++j) {  // a circuit's steps come in their order
+            const BatchStep &st = b->steps_h[(size_t)b->summed_h[(size_t)j]];
+            for (int k = 0; k < kSlots; ++k)
+                if (st.map[k] >= 0) results(st.circuit)[st.map[k]] += b->sums_h[(size_t)j * kSlots + k];
+        }
+        for (int c = 0; c < b->count; ++c) {
+            const double *res = results(c);
+            const int p = b->p[c];
             exp_c[c] = (res[1] / 10.0) / res[0];
             for (int k = 0; k < p; ++k) {
                 d_theta_zz[b->angle_off[c] + k] = res[2 + k] / res[0];
@@ -1918,9 +1957,7 @@ int batch_plan_check(int count, const qs_circuit *circuits, int prec, int large,
             return bad("circuit %d: buffers overlap or exceed the allocation", c);
         if (c + 1 < count && b.off_diag[c] + db > b.off_psi[c + 1]) return bad("circuits %d, %d overlap", c, c + 1);
     }
-    // steps: consecutive per circuit, starting from |+>; rows contiguous in step order
-    int64_t row = 0;
-    int nsum = 0;
+    // steps: consecutive per circuit, starting from |+>
     std::vector<int> seen(count, 0);
     for (int i = 0; i < nsteps; ++i) {
         const BatchStep &s = st[i];
@@ -1932,12 +1969,8 @@ int batch_plan_check(int count, const qs_circuit *circuits, int prec, int large,
             return bad("step %d: chunks do not cover the tiles", i);
         if (s.pp.ntiles != ntiles) return bad("step %d: tile count", i);
         if ((seen[s.circuit] == 0) != (s.pp.init != 0 && s.kind == 0)) return bad("step %d: first step must start from |+>", i);
-        if ((s.kind >= 1) != (s.row0 >= 0)) return bad("step %d: rows", i);
-        if (s.row0 >= 0) {
-            if (s.row0 != row || nsum >= (int)b.summed_h.size() || b.summed_h[nsum] != i) return bad("step %d: rows", i);
-            row += s.chunks;
-            ++nsum;
-        }
+        if ((s.kind >= 1) != (s.row0 >= 0) || (s.row0 >= 0 && s.row0 + s.chunks > sch.rows))
+            return bad("step %d: rows", i);
         ++seen[s.circuit];
         const char *psi = (const char *)s.pp.psi, *dg = (const char *)s.pp.diag;
         if (psi != lo + b.off_psi[s.circuit] || s.pp.psi_out != s.pp.psi || dg != lo + b.off_diag[s.circuit] ||
@@ -1956,7 +1989,30 @@ int batch_plan_check(int count, const qs_circuit *circuits, int prec, int large,
             return bad("step %d: kernel", i);
         if (s.pp.stream != pass_streams(s.pp, prec, s.kind)) return bad("step %d: streaming", i);
     }
-    if (row != sch.rows || nsum != (int)b.summed_h.size()) return bad("row count");
+    // sums: every step that writes some once, in a group that holds its round,
+    // a circuit's steps in their order, rows without overlap within a group and
+    // no more of them than the limit allows
+    std::vector<int> last(count, -1), times(nsteps, 0);
+    for (size_t g = 0, at = 0; g < sch.groups.size(); ++g) {
+        const BatchSchedule::Group &gr = sch.groups[g];
+        const size_t end = g + 1 < sch.groups.size() ? sch.groups[g + 1].begin : b.round_items.size();
+        if (gr.begin >= end || (g == 0 && gr.begin != 0) || gr.first != (int)at) return bad("group %d", (int)g);
+        int64_t row = 0, most = 0;
+        for (int k = 0; k < gr.count; ++k, ++at) {
+            if (at >= b.summed_h.size()) return bad("group %d: steps", (int)g);
+            const int i = b.summed_h[at];
+            const BatchStep &s = st[i];
+            const size_t r = (size_t)(i - b.step0[s.circuit]);
+            if (r < gr.begin || r >= end || s.row0 != row || i <= last[s.circuit]) return bad("group %d: step %d", (int)g, i);
+            row += s.chunks;
+            if (r == gr.begin) most += s.chunks;
+            last[s.circuit] = i;
+            ++times[i];
+        }
+        if (row > std::max(kBatchMaxRows, most) || row > sch.rows) return bad("group %d: rows", (int)g);
+    }
+    for (int i = 0; i < nsteps; ++i)
+        if (times[i] != (st[i].kind >= 1 ? 1 : 0)) return bad("step %d: summed %d times", i, times[i]);
     for (int c = 0; c < count; ++c) {
         const int P = (int)plan_passes(b.n[c], prec).size();
         const int fwd = b.p[c] * (P - 1) + 1;

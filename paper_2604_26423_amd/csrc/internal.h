@@ -251,7 +251,7 @@ struct BatchStep {
     int chunks;           // work items of this step (the same for every step of a circuit)
     int64_t tiles_per_chunk;
     int map[kSlots];      // result index of each partial-sum slot (-1: unused)
-    int64_t row0;         // first row of partial sums, -1 if none (forward passes)
+    int64_t row0;         // first row of partial sums (in its group of rounds), -1 if none (forward passes)
     int64_t tab_off;      // offset of this step's phase table (entries), -1 if none
 };
 

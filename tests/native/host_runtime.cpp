@@ -16,9 +16,9 @@
 
 namespace {
 struct Event {
-    char kind;  // 'L' launch, 'S' wait for a stream, 'H' / 'F' pinned allocation / release, 'M' copy
+    char kind;  // 'L' launch, 'S' wait for a stream, 'H' / 'F' pinned allocation / release, 'M' copy, 'A' allocation
     void *stream;
-    uint64_t threads;
+    uint64_t threads;  // launch: threads; allocation: bytes
 };
 std::vector<Event> events;
 long fail_launch = -1;  // launches until one fails
@@ -94,7 +94,7 @@ int hipEventDestroy(void *) { return 0; }
 int hipEventElapsedTime(float *ms, void *, void *) { *ms = 0; return 0; }
 int hipEventRecord(void *, void *) { return 0; }
 int hipEventSynchronize(void *) { return 0; }
-int hipMalloc(void **p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? 0 : 2; }
+int hipMalloc(void **p, size_t n) { note('A', nullptr, n); *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? 0 : 2; }
 int hipFree(void *p) { free(p); return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
 const char *hipGetErrorString(int) { return "error"; }
@@ -210,7 +210,7 @@ static int many_shots()
         const size_t at = events.size();
         CHECK(qs_sample(s, 1, shots, out, 1) == QS_OK);
         CHECK(count('L', A, at) >= 1);
-        for (size_t i = at; i < events.size(); ++i) CHECK(events[i].threads < ((uint64_t)1 << 32));
+        for (size_t i = at; i < events.size(); ++i) CHECK(events[i].kind != 'L' || events[i].threads < ((uint64_t)1 << 32));
     }
     CHECK(qs_free(s) == QS_OK);
     return 0;
@@ -226,9 +226,27 @@ static int many_bins()
     qs_state s = handle(n, A);
     CHECK(s && qs_cost_histogram(s, diag, nbins, out, 1) == QS_OK);
     uint64_t threads = 0;
-    for (const Event &e : events) threads += e.threads;
+    for (const Event &e : events) threads += e.kind == 'L' ? e.threads : 0;
     CHECK(threads <= 2ull * nbins + (1u << 16));
     CHECK(qs_free(s) == QS_OK);
+    return 0;
+}
+
+// The partial sums of a deep batch are reduced in groups of rounds: its working
+// memory beside states, steps and phase tables stays bounded.
+static int deep_batch()
+{
+    const int n = 22, p = 6000, ne = n * (n - 1) / 2;
+    std::vector<int32_t> w(ne, 3);
+    const qs_circuit c = {n, p, w.data()};
+    qs_batch b = nullptr;
+    CHECK(qs_batch_create(1, &c, QS_C64, A, &b) == QS_OK);
+    std::vector<double> tzz(p, 0.1), tx(p, -0.2), gz(p), gx(p);
+    double e = 0;
+    const size_t at = events.size();
+    CHECK(qs_batch_forward_grad(b, tzz.data(), tx.data(), &e, gz.data(), gx.data()) == QS_OK);
+    for (size_t i = at; i < events.size(); ++i) CHECK(events[i].kind != 'A' || events[i].threads <= (64u << 20));
+    CHECK(qs_batch_free(b) == QS_OK);
     return 0;
 }
 
@@ -241,6 +259,7 @@ int main(int argc, char **argv)
     else if (which == "no_memory") rc = no_memory();
     else if (which == "many_shots") rc = many_shots();
     else if (which == "many_bins") rc = many_bins();
+    else if (which == "deep_batch") rc = deep_batch();
     if (rc == 0) printf("ok %s\n", which.c_str());
     return rc;
 }
