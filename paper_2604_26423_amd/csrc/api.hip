@@ -404,11 +404,6 @@ PassProg make_prog_raw(void *psi, int n, int prec, double *partials, const PassG
 // streamed, forward junction 15.8 against 18.8).
 // A forward pass that only applies a stage streams at every size, and the
 // complement-symmetric layout (two-bit factors, 6% slower with it) at none.
-// A batch's steps follow the same rule, by the size of their own circuit (the
-// complex64 batch kernel's reverse steps always take ordinary accesses): one
-// circuit of 20 qubits in complex128 162 -> 153 us, 64 of 18 to 20 qubits 6.15
-// -> 5.63 ms, complex64 3.73 -> 3.65, against nontemporal stores in every plain
-// and turnaround step, at 26 qubits 28.4 -> 28.8 ms.
 int pass_streams(const PassProg &pp, int prec, int kind)
 {
     if (pp.pairs) return 0;
@@ -418,6 +413,22 @@ int pass_streams(const PassProg &pp, int prec, int kind)
     const int64_t bytes = amp << pp.n;
     constexpr int64_t MB = 1 << 20;
     return bytes >= 256 * MB || (bytes <= 32 * MB && (kind != 0 || bytes >= 4 * MB));
+}
+
+// The same for a step of a batch, where other circuits' vectors pass through the
+// caches between two steps of one circuit.  Steps without a phase stream at
+// every size (12 circuits of 22 and 23 qubits, complex128, 19.3 ms, with the
+// rule above 19.8; one of 26 qubits 28.5 / 28.8; the reverse steps of the
+// complex64 kernel load and store ordinarily all the same).  Steps with a phase
+// stream in complex128 where the rule above streams a state that fits the L2
+// caches (64 circuits of 18 to 20 qubits 6.15 -> 5.64 ms, one of 20 167 -> 155
+// us), in complex64 not at all: the few circuits that gain 2% (64 of 18 to 20
+// 3.74 -> 3.65 ms) do not make up for the many that lose (512 of 14 to 22 40.1
+// -> 40.6 ms).
+int batch_streams(const PassProg &pp, int prec, int kind)
+{
+    if (!pp.has_phase) return 1;
+    return prec != 0 && ((int64_t)sizeof(double2) << pp.n) <= (32 << 20) && pass_streams(pp, prec, kind);
 }
 
 // kind: 0 = forward pass, 1 = turnaround, 2 = reverse pass (the cut table is
@@ -956,7 +967,7 @@ BatchSchedule build_batch_schedule(qs_batch b, const double *theta_zz, const dou
             }
             sch.kernels[b->steps_h.size() - (size_t)b->step0[c]] |= (char)(1 << s.fast);
             s.pp.xcd_remap = 0;
-            s.pp.stream = pass_streams(s.pp, b->prec, kind);
+            s.pp.stream = batch_streams(s.pp, b->prec, kind);
             s.kind = kind;
             s.circuit = c;
             for (int j = 0; j < kSlots; ++j) s.map[j] = -1;
@@ -1987,7 +1998,7 @@ int batch_plan_check(int count, const qs_circuit *circuits, int prec, int large,
             s.mode != tile_mode(s.pp, T, s.pp.tb) || (s.fast && !batch_step_fast(s)) ||
             !(sch.kernels[(size_t)(i - b.step0[s.circuit])] >> s.fast & 1))
             return bad("step %d: kernel", i);
-        if (s.pp.stream != pass_streams(s.pp, prec, s.kind)) return bad("step %d: streaming", i);
+        if (s.pp.stream != batch_streams(s.pp, prec, s.kind)) return bad("step %d: streaming", i);
     }
     // sums: every step that writes some once, in a group that holds its round,
     // a circuit's steps in their order, rows without overlap within a group and

@@ -70,7 +70,7 @@ struct PassProg {
     int ntargets;         // factors per stage: popcount(targets) + popcount(pairs)
     int width;            // strided tile bits T - c
     int xcd_remap;        // map consecutive tiles to one XCD
-    int stream;           // nontemporal loads and stores of the vectors (pass_streams in api.hip)
+    int stream;           // nontemporal loads and stores of the vectors (pass_streams, batch_streams in api.hip)
     int init;             // start from |+>^n instead of loading
     int has_pre, has_phase, has_post, readout;
     int load_win;         // layout of the first global access
