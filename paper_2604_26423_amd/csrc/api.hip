@@ -803,10 +803,10 @@ qs_status run_adjoint(qs_state s, const Circuit &cc, void *lam, double *r, const
     auto ck = [&](int i) -> void * { return i == P - 2 ? s->psi : (void *)((char *)ckpt + (size_t)i * sb); };
     // one-tile kernels run 256 threads (5-bit windows), the persistent
     // kernel 512; the complement-symmetric layout keeps 512 threads (256
-    // measured no faster there)
+    // measured no faster there, with runtime masks and unpinned window sums)
     auto adjoint_prog = [&](const KSpec &k, int kind) {
-        PassProg pp = make_prog(s, geo[k.pass], k, cc, kAdjOneThreadBits, kind);
-        if (s->sym || !adjoint_one_tile(s->prec, pp, kind == 1))
+        PassProg pp = make_prog(s, geo[k.pass], k, cc, s->sym ? kAdjThreadBits : kAdjOneThreadBits, kind);
+        if (!s->sym && !adjoint_one_tile(s->prec, pp, kind == 1))
             pp = make_prog(s, geo[k.pass], k, cc, kAdjThreadBits, kind);
         pp.lam = lam;
         return pp;

@@ -28,8 +28,8 @@ namespace {
 // 58.5 ms, now 40.4, without it 39.6.)
 template <typename V, bool FAST> constexpr int batch_tb = FAST && sizeof(V) == 16 ? 8 : 9;
 
-// Tiles [t0, t1) of one step, with the stage code path of that step.
-template <typename V, int T, int MODE>
+// Tiles [t0, t1) of one step, general stage code.
+template <typename V, int T>
 __device__ __forceinline__ void run_item(const BatchStep &st, int64_t t0, int64_t t1, V *lds, const V *tab,
                                          double (&acc)[kSlots], int tid)
 {
@@ -37,18 +37,18 @@ __device__ __forceinline__ void run_item(const BatchStep &st, int64_t t0, int64_
     const PassProg &pp = st.pp;
     if (st.kind == 0) {
         double fa[2] = {0.0, 0.0};
-        for (int64_t t = t0; t < t1; ++t) fwd_tile<V, T, TB, MODE>(pp, t, lds, tab, fa, tid);
+        for (int64_t t = t0; t < t1; ++t) fwd_tile<V, T, TB, kModeGeneral>(pp, t, lds, tab, fa, tid);
         acc[0] = fa[0];
         acc[1] = fa[1];
     } else if (st.kind == 1) {
-        for (int64_t t = t0; t < t1; ++t) turn_tile<V, T, TB, MODE>(pp, t, lds, acc, tid);
+        for (int64_t t = t0; t < t1; ++t) turn_tile<V, T, TB, kModeGeneral>(pp, t, lds, acc, tid);
     } else {
         for (int64_t t = t0; t < t1; ++t) {
             V p[NR], l[NR];
             int32_t dg[NR];
             if (pp.has_phase) rev_load_diag<V, T, TB>(pp, t, dg, tid);
             rev_load_vectors<V, T, TB>(pp, t, p, l, tid);
-            rev_tile<V, T, TB, MODE>(pp, t, p, l, dg, lds, tab, acc, tid);
+            rev_tile<V, T, TB, kModeGeneral>(pp, t, p, l, dg, lds, tab, acc, tid);
         }
     }
 }
@@ -134,8 +134,7 @@ __global__ void __launch_bounds__((1 << batch_tb<V, FAST>), (!FAST ? 1 : batch_t
     }
     double acc[kSlots] = {0.0, 0.0, 0.0, 0.0};
     if constexpr (FAST) run_item_fast<V, T>(st, t0, t1, lds, tab, acc, tid);
-    else if (st.mode == kModeTan) run_item<V, T, kModeTan>(st, t0, t1, lds, tab, acc, tid);
-    else run_item<V, T, kModeGeneral>(st, t0, t1, lds, tab, acc, tid);
+    else run_item<V, T>(st, t0, t1, lds, tab, acc, tid);
     if (st.kind == 0) return;
     block_sum(acc, red, tid, NT);
     if (tid == 0) {
@@ -153,7 +152,7 @@ __global__ void __launch_bounds__(256) batch_table_kernel(const BatchStep *steps
 {
     const BatchStep &st = steps[blockIdx.x];
     if (!st.pp.has_phase || st.tab_off < 0) return;
-    const bool fold = st.kind == 2 && st.mode == kModeTan && !st.pp.init;  // run_item runs kModeTan or general
+    const bool fold = st.kind == 2 && st.mode == kModeTan && !st.pp.init;  // (the fast kernel's)
     const double f = st.kind == 0 || fold ? st.pp.factor : 1.0;
     build_phase_table(tabs + st.tab_off, st.pp.phase_levels, st.pp.theta_zz, st.pp.W, f, threadIdx.x, 256);
 }

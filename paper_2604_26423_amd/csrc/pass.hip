@@ -228,7 +228,9 @@ __global__ void __launch_bounds__(1 << TB, ONE ? (TB == 9 ? 4 : 2) : 1) adjoint_
             // this tile's diagonal is requested before the next tile's vectors:
             // memory counters retire in order, so the phase step then waits
             // only for these loads.  The one-tile junction loads it at the
-            // phase point instead (LATE), to stay within 128 registers.
+            // phase point instead (LATE): loaded early, the diagonal's 32
+            // registers beside both vectors' 128 cost n = 20 gradients 7%
+            // (and gained n = 28 ones 1%).
             constexpr bool LATE = ONE && SH == (kShPre | kShPhase | kShPost);
             if (!LATE && (SH >= 0 ? (SH & kShPhase) != 0 : pp.has_phase != 0))
                 rev_load_diag<V, T, TB>(pp, tile, dg, tid);
@@ -376,28 +378,33 @@ void launch_pass_k(int prec, const PassProg &pp, int64_t grid, hipStream_t st)
 // stage), a junction (stage, phase, stage), the last pass (stage and readout)
 // and, in tangent form, a plain stage with its compile-time tail (102-136
 // registers against 240 with runtime masks; bit-identical, a plain contiguous
-// pass ~0.1 ms faster at n = 32); anything else uses the runtime-shape
-// kernel.
-template <int MODE>
-void launch_pass_m(int prec, const PassProg &pp, int64_t grid, hipStream_t st)
+// pass ~0.1 ms faster at n = 32).  No other shape is planned in the full
+// layout; the complement-symmetric one, which never streams, runs its plain
+// stages on the runtime-shape kernel.
+constexpr int kFirst = kShInit | kShPhase | kShPost, kJunc = kShPre | kShPhase | kShPost, kLast = kShPost | kShReadout;
+
+hipError_t launch_pass_tan(int prec, const PassProg &pp, int64_t grid, hipStream_t st)
 {
-    constexpr int kFirst = kShInit | kShPhase | kShPost, kJunc = kShPre | kShPhase | kShPost,
-                  kLast = kShPost | kShReadout;
-    if constexpr (MODE == kModeTan) {
-        switch (pass_shape(pp)) {
-        case kFirst: launch_pass_k<kFirst>(prec, pp, grid, st); return;
-        case kJunc: launch_pass_k<kJunc>(prec, pp, grid, st); return;
-        case kLast: launch_pass_k<kLast>(prec, pp, grid, st); return;
-        case kShPost: launch_pass_k<kShPost>(prec, pp, grid, st); return;
-        default: launch_pass_s<MODE, -1>(prec, pp, grid, st); return;
-        }
-    }
     switch (pass_shape(pp)) {
-    case kFirst: launch_pass_s<MODE, kFirst>(prec, pp, grid, st); break;
-    case kJunc: launch_pass_s<MODE, kJunc>(prec, pp, grid, st); break;
-    case kLast: launch_pass_s<MODE, kLast>(prec, pp, grid, st); break;
-    default: launch_pass_s<MODE, -1>(prec, pp, grid, st); break;
+    case kFirst: launch_pass_k<kFirst>(prec, pp, grid, st); break;
+    case kJunc: launch_pass_k<kJunc>(prec, pp, grid, st); break;
+    case kLast: launch_pass_k<kLast>(prec, pp, grid, st); break;
+    case kShPost: launch_pass_k<kShPost>(prec, pp, grid, st); break;
+    default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_pass_sym(int prec, const PassProg &pp, int64_t grid, hipStream_t st)
+{
+    if (pp.stream) return hipErrorInvalidValue;
+    switch (pass_shape(pp)) {
+    case kFirst: launch_pass_s<kModeTanSym, kFirst, 0, 0>(prec, pp, grid, st); break;
+    case kJunc: launch_pass_s<kModeTanSym, kJunc, 0, 0>(prec, pp, grid, st); break;
+    case kLast: launch_pass_s<kModeTanSym, kLast, 0, 0>(prec, pp, grid, st); break;
+    default: launch_pass_s<kModeTanSym, -1, 0, 0>(prec, pp, grid, st); break;
+    }
+    return hipGetLastError();
 }
 
 template <int MODE, bool TURN, int SH, bool ONE, int AT = kAdjThreadBits>
@@ -429,10 +436,10 @@ void launch_adjoint_k(const PassProg &pp, int64_t grid, hipStream_t st)
 // workgroup, without prefetch, in the registers of two workgroups per CU: the
 // turnaround, a reverse pass of plain stages, the reverse of the first
 // forward pass (phase of layer 1, no writes) and the reverse junction (stage,
-// phase, stage; its diagonal is loaded at the phase point).  They run 256
-// threads (pp.tb = 8: 5-bit windows, up to 256 registers); planned for 512
-// threads (128 registers) the complex128 turnaround and junction spill and
-// take the persistent kernel instead.
+// phase, stage; its diagonal is loaded at the phase point).  In the full layout
+// they run 256 threads (pp.tb = 8: 5-bit windows, up to 256 registers), in the
+// complement-symmetric one 512 (128 registers), where the complex128
+// turnaround and junction spill and take the persistent kernel instead.
 enum { kAdjPersistent, kAdjOneTurn, kAdjOnePlain, kAdjOneFirst, kAdjOneJunc };
 
 int adjoint_variant(int prec, const PassProg &pp, int turnaround, int mode)
@@ -442,51 +449,60 @@ int adjoint_variant(int prec, const PassProg &pp, int turnaround, int mode)
     if (turnaround) return spills ? kAdjPersistent : kAdjOneTurn;
     switch (pass_shape(pp)) {
     case kShPost: return kAdjOnePlain;
-    case kShInit | kShPhase | kShPost: return kAdjOneFirst;
-    case kShPre | kShPhase | kShPost: return spills ? kAdjPersistent : kAdjOneJunc;
+    case kFirst: return kAdjOneFirst;
+    case kJunc: return spills ? kAdjPersistent : kAdjOneJunc;
     default: return kAdjPersistent;
     }
 }
 
-// AT: thread bits of the one-tile kernels (pp.tb); the persistent kernels
-// are 512-thread only.
-template <int MODE, int AT>
-void launch_adjoint_m_at(int prec, const PassProg &pp, int turnaround, int64_t grid, hipStream_t st)
+// The full layout in tangent form.  Compile-time tails in complex64 (measured
+// against masks read from the program, p = 3 gradients: n = 20 (p = 10) 525 ->
+// 500 us, 24 1042 -> 1026, 28 15349 -> 15220; the n = 32 kernels 253.8 -> 251.6
+// ms).  In complex128 they gave n = 24 1904 -> 1875 us but n = 28 28.79 -> 28.96
+// ms: not taken.
+hipError_t launch_adjoint_tan(int prec, const PassProg &pp, int turnaround, int64_t grid, hipStream_t st)
 {
-    // Compile-time tails in complex64 (measured against masks read from the
-    // program, p = 3 gradients: n = 20 (p = 10) 525 -> 500 us, 24 1042 -> 1026,
-    // 28 15349 -> 15220; the n = 32 kernels 253.8 -> 251.6 ms).  In complex128
-    // they gave n = 24 1904 -> 1875 us but n = 28 28.79 -> 28.96 ms: not taken.
-    if constexpr (MODE == kModeTan && AT == kAdjOneThreadBits) {
-        if (prec == 0) {
-            switch (adjoint_variant(prec, pp, turnaround, MODE)) {
-            case kAdjOneTurn: launch_adjoint_k<true, -1>(pp, grid, st); return;
-            case kAdjOnePlain: launch_adjoint_k<false, kShPost>(pp, grid, st); return;
-            case kAdjOneFirst: launch_adjoint_k<false, kShInit | kShPhase | kShPost>(pp, grid, st); return;
-            case kAdjOneJunc: launch_adjoint_k<false, kShPre | kShPhase | kShPost>(pp, grid, st); return;
-            default: break;
-            }
-        }
-    }
-    switch (adjoint_variant(prec, pp, turnaround, MODE)) {
-    case kAdjOneTurn: launch_adjoint_s<MODE, true, -1, true, AT>(prec, pp, grid, st); break;
-    case kAdjOnePlain: launch_adjoint_s<MODE, false, kShPost, true, AT>(prec, pp, grid, st); break;
-    case kAdjOneFirst: launch_adjoint_s<MODE, false, kShInit | kShPhase | kShPost, true, AT>(prec, pp, grid, st); break;
-    case kAdjOneJunc: launch_adjoint_s<MODE, false, kShPre | kShPhase | kShPost, true, AT>(prec, pp, grid, st); break;
-    default:
-        if constexpr (AT == kAdjThreadBits) {
-            if (turnaround) launch_adjoint_s<MODE, true, -1, false>(prec, pp, grid, st);
-            else launch_adjoint_s<MODE, false, -1, false>(prec, pp, grid, st);
-        }
+    constexpr int AT = kAdjOneThreadBits;
+    const bool k = prec == 0;
+    switch (adjoint_variant(prec, pp, turnaround, kModeTan)) {
+    case kAdjOneTurn:
+        if (k) launch_adjoint_k<true, -1>(pp, grid, st);
+        else launch_adjoint_s<kModeTan, true, -1, true, AT>(prec, pp, grid, st);
         break;
+    case kAdjOnePlain:
+        if (k) launch_adjoint_k<false, kShPost>(pp, grid, st);
+        else launch_adjoint_s<kModeTan, false, kShPost, true, AT>(prec, pp, grid, st);
+        break;
+    case kAdjOneFirst:
+        if (k) launch_adjoint_k<false, kFirst>(pp, grid, st);
+        else launch_adjoint_s<kModeTan, false, kFirst, true, AT>(prec, pp, grid, st);
+        break;
+    case kAdjOneJunc:
+        if (k) launch_adjoint_k<false, kJunc>(pp, grid, st);
+        else launch_adjoint_s<kModeTan, false, kJunc, true, AT>(prec, pp, grid, st);
+        break;
+    default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
 }
 
-template <int MODE>
-void launch_adjoint_m(int prec, const PassProg &pp, int turnaround, int64_t grid, hipStream_t st)
+// The complement-symmetric layout in tangent form.
+hipError_t launch_adjoint_sym(int prec, const PassProg &pp, int turnaround, int64_t grid, hipStream_t st)
 {
-    if (pp.tb == kAdjOneThreadBits) launch_adjoint_m_at<MODE, kAdjOneThreadBits>(prec, pp, turnaround, grid, st);
-    else launch_adjoint_m_at<MODE, kAdjThreadBits>(prec, pp, turnaround, grid, st);
+    // (turnaround and junction: complex64 only, see adjoint_variant)
+    constexpr int T = kTileBitsC64, AT = kAdjThreadBits;
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1 << AT), 0, st, pp); };
+    switch (adjoint_variant(prec, pp, turnaround, kModeTanSym)) {
+    case kAdjOneTurn: go(adjoint_kernel<float2, T, AT, true, kModeTanSym, -1, true>); break;
+    case kAdjOnePlain: launch_adjoint_s<kModeTanSym, false, kShPost, true>(prec, pp, grid, st); break;
+    case kAdjOneFirst: launch_adjoint_s<kModeTanSym, false, kFirst, true>(prec, pp, grid, st); break;
+    case kAdjOneJunc: go(adjoint_kernel<float2, T, AT, false, kModeTanSym, kJunc, true>); break;
+    default:
+        if (turnaround) launch_adjoint_s<kModeTanSym, true, -1, false>(prec, pp, grid, st);
+        else launch_adjoint_s<kModeTanSym, false, -1, false>(prec, pp, grid, st);
+        break;
+    }
+    return hipGetLastError();
 }
 
 // Stage code path of an adjoint pass, for the threads its windows are planned for.
@@ -496,8 +512,8 @@ int adjoint_mode(int prec, const PassProg &pp) { return tile_mode(pp, tile_bits(
 // Whether the kernel that launch_pass / launch_adjoint_pass pick for pp (kind
 // 0 = forward pass, 1 = turnaround, 2 = reverse pass) needs C_t and takes it
 // from a cut table: every forward and turnaround kernel does, and every
-// reverse kernel but the complex64 one-tile junction, which loads the
-// diagonal.
+// reverse kernel but the one-tile junction of either precision, which loads
+// the diagonal.
 bool pass_takes_cut_table(int prec, const PassProg &pp, int kind)
 {
     if (kind == 0) return pp.has_phase || pp.readout;
@@ -510,10 +526,10 @@ bool pass_takes_cut_table(int prec, const PassProg &pp, int kind)
 // (complex64) or 16 (complex128): their windows of 5 (4) register bits need
 // fewer exchanges per stage than those of 512 threads (a 13-qubit stage three
 // windows instead of four, a 9- or 10-qubit stage two instead of three), at
-// 164-246 registers for two workgroups per CU; planned for 256 threads the
-// complex128 turnaround and junction fit too.  The host plans a pass for 256
-// threads first and falls back to 512 (the persistent kernel) when this
-// returns false.
+// 164-248 registers for two workgroups per CU; planned for 256 threads the
+// complex128 turnaround and junction fit too.  The host plans a pass of the full
+// layout for 256 threads first and falls back to 512 (the persistent kernel)
+// when this returns false.
 bool adjoint_one_tile(int prec, const PassProg &pp, int turnaround)
 {
     return adjoint_variant(prec, pp, turnaround, adjoint_mode(prec, pp)) != kAdjPersistent;
@@ -574,24 +590,22 @@ hipError_t launch_pass(int prec, const PassProg &pp, int64_t grid, hipStream_t s
     if (pp.has_phase && !pp.tab) return hipErrorInvalidValue;
     if (hipError_t e = launch_cut_table(prec, pp, 0, kFwdThreadBits, st)) return e;
     switch (tile_mode(pp, tile_bits(prec), kFwdThreadBits)) {
-    case kModeTan: launch_pass_m<kModeTan>(prec, pp, grid, st); break;
-    case kModeTanSym: launch_pass_m<kModeTanSym>(prec, pp, grid, st); break;
-    default: launch_pass_s<kModeGeneral, -1>(prec, pp, grid, st); break;
+    case kModeTan: return launch_pass_tan(prec, pp, grid, st);
+    case kModeTanSym: return launch_pass_sym(prec, pp, grid, st);
+    default: launch_pass_s<kModeGeneral, -1>(prec, pp, grid, st); return hipGetLastError();
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_adjoint_pass(int prec, const PassProg &pp, int turnaround, int64_t grid, hipStream_t st)
 {
-    // a program planned for 256 threads must take a one-tile kernel
-    if (pp.tb != kAdjThreadBits && (pp.tb != kAdjOneThreadBits || !adjoint_one_tile(prec, pp, turnaround)))
-        return hipErrorInvalidValue;
+    // 256 threads: the full layout in tangent form; else 512
     const int mode = adjoint_mode(prec, pp);
+    if (pp.tb != (mode == kModeTan ? kAdjOneThreadBits : kAdjThreadBits)) return hipErrorInvalidValue;
     if (pp.has_phase && !pp.tab) return hipErrorInvalidValue;
     if (hipError_t e = launch_cut_table(prec, pp, turnaround ? 1 : 2, pp.tb, st)) return e;
     switch (mode) {
-    case kModeTan: launch_adjoint_m<kModeTan>(prec, pp, turnaround, grid, st); break;
-    case kModeTanSym: launch_adjoint_m<kModeTanSym>(prec, pp, turnaround, grid, st); break;
+    case kModeTan: return launch_adjoint_tan(prec, pp, turnaround, grid, st);
+    case kModeTanSym: return launch_adjoint_sym(prec, pp, turnaround, grid, st);
     default:
         if (turnaround) launch_adjoint_s<kModeGeneral, true, -1, false>(prec, pp, grid, st);
         else launch_adjoint_s<kModeGeneral, false, -1, false>(prec, pp, grid, st);

@@ -66,37 +66,27 @@ __global__ void __launch_bounds__(kExpectThreads) expect_kernel(const V *psi, co
             acc[1] += pr * (double)c[k];
         }
     };
-    if (dim < K) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            V a[K] = {};
-            int32_t c[K] = {};
-            a[0] = psi[0];
-            c[0] = diag[0];
-            add(a, c);
-        }
-    } else {
-        // a contiguous range per workgroup (dim and the grid are powers of two;
-        // at least one stride)
-        const int64_t S = kExpectThreads * K, per = dim / gridDim.x, lo = blockIdx.x * per, hi = lo + per;
-        int64_t x = lo + (int64_t)threadIdx.x * K;
-        for (; x + (U - 1) * S < hi; x += U * S) {
-            V a[U][K];
-            int32_t c[U][K];
+    // a contiguous range per workgroup (dim and the grid are powers of two, dim
+    // at least 2)
+    const int64_t S = kExpectThreads * K, per = dim / gridDim.x, lo = blockIdx.x * per, hi = lo + per;
+    int64_t x = lo + (int64_t)threadIdx.x * K;
+    for (; x + (U - 1) * S < hi; x += U * S) {
+        V a[U][K];
+        int32_t c[U][K];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                Wd::load(psi, x + u * S, a[u]);
-                Wd::load_c(diag, x + u * S, c[u]);
-            }
+        for (int u = 0; u < U; ++u) {
+            Wd::load(psi, x + u * S, a[u]);
+            Wd::load_c(diag, x + u * S, c[u]);
+        }
 #pragma unroll
-            for (int u = 0; u < U; ++u) add(a[u], c[u]);
-        }
-        for (; x < hi; x += S) {
-            V a[K];
-            int32_t c[K];
-            Wd::load(psi, x, a);
-            Wd::load_c(diag, x, c);
-            add(a, c);
-        }
+        for (int u = 0; u < U; ++u) add(a[u], c[u]);
+    }
+    for (; x < hi; x += S) {
+        V a[K];
+        int32_t c[K];
+        Wd::load(psi, x, a);
+        Wd::load_c(diag, x, c);
+        add(a, c);
     }
     block_sum(acc, red, threadIdx.x, kExpectThreads);
     if (threadIdx.x == 0) {

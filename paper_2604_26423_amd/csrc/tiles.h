@@ -672,8 +672,9 @@ __device__ __forceinline__ void rev_tile(const PassProg &pp, int64_t tile, V (&p
         }
     }
     if (has_phase) {
-        // (the late load reads the diagonal: within the one-tile junction's 128
-        // registers the cut table's terms would spill)
+        // (the late load reads the diagonal: the one-tile junction takes 246-248 of
+        // its 256 registers, and all 128 with 512 threads, so none are left for
+        // the cut table's terms)
         if constexpr (LATE) load_diag<T, TB>(pp, opaque(pp.phase_win), base, gg.c, gg.q0, tid, dg);
         // sum of (C - c) Im(conj(l) p) over the thread's amplitudes (c: see
         // turn_compute): each amplitude's Im(conj(l) p) in the state

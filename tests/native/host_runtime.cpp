@@ -232,6 +232,31 @@ static int many_bins()
     return 0;
 }
 
+// Every size, precision and layout, angles in tangent form and beyond: each pass
+// finds a kernel.
+static int every_plan()
+{
+    void *const psi = (void *)0x10000000, *const lam = (void *)0x20000000;  // never touched
+    const int32_t *diag = (const int32_t *)0x30000000;
+    for (int prec : {(int)QS_C64, (int)QS_C128, QS_C64 | QS_SYM, QS_C128 | QS_SYM})
+        for (int n = 1; n <= 35; ++n) {
+            const size_t bytes = qs_state_bytes(n, prec);
+            if (!bytes) continue;
+            qs_state s = nullptr;
+            CHECK(qs_alloc(n, prec, psi, bytes, A, &s) == QS_OK);
+            for (int p = 1; p <= 3; ++p)
+                for (double large : {0.0, 2.4}) {
+                    const double tzz[3] = {0.1, 0.2, 0.3}, tx[3] = {large ? large : -0.9, large ? large : -0.6, -0.3};
+                    double e = 0, nrm = 0, g[6];
+                    CHECK(qs_forward(s, diag, 300, p, tzz, tx, &e, &nrm) == QS_OK);
+                    CHECK(n < 2 || qs_adjoint_grad(s, diag, 300, p, tzz, tx, lam, bytes, &e, g, g + 3) == QS_OK);
+                    CHECK(qs_apply_mixer(s, tx[1]) == QS_OK);
+                }
+            CHECK(qs_free(s) == QS_OK);
+        }
+    return 0;
+}
+
 // The partial sums of a deep batch are reduced in groups of rounds: its working
 // memory beside states, steps and phase tables stays bounded.
 static int deep_batch()
@@ -260,6 +285,7 @@ int main(int argc, char **argv)
     else if (which == "many_shots") rc = many_shots();
     else if (which == "many_bins") rc = many_bins();
     else if (which == "deep_batch") rc = deep_batch();
+    else if (which == "every_plan") rc = every_plan();
     if (rc == 0) printf("ok %s\n", which.c_str());
     return rc;
 }

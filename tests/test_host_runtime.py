@@ -10,7 +10,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_2604_26423_amd")
 
-CASES = ["switched_stream", "same_stream", "no_memory", "many_shots", "many_bins", "deep_batch"]
+CASES = ["switched_stream", "same_stream", "no_memory", "many_shots", "many_bins", "deep_batch", "every_plan"]
 
 
 @pytest.fixture(scope="module")
