@@ -17,10 +17,12 @@ namespace {
 // Kernel shapes.  FAST: the steps whose stages are in tangent form; each pass
 // runs code fixed for its shape (see pass_shape), psi and lambda are exchanged
 // one after the other through a one-tile buffer, and two workgroups share a
-// CU: 512 threads within 128 registers in complex64, 256 threads within 256 in
-// complex128 (the thread counts of the single-circuit kernels that do not
-// spill).  One workgroup's loads and barriers then overlap the other's
-// arithmetic.  The other steps (a mixer angle with |cos(theta / 2)| < 1/2) run
+// CU: 512 threads within 128 registers in complex64 (127, no spill), 256 threads
+// within 256 in complex128 (252; with 512 the single circuits' junction
+// spills).  One workgroup's loads and barriers then overlap the other's
+// arithmetic.  (Complex64 with the 256 threads
+// and 5-bit windows of the single circuits' reverse kernels has not been
+// tried.)  The other steps (a mixer angle with |cos(theta / 2)| < 1/2) run
 // runtime-shape code, 512 threads, one workgroup per CU with a two-tile buffer.
 // A round that has steps of both kinds launches both kernels over all its
 // items, and a workgroup leaves when its item's step is the other's.  (One such

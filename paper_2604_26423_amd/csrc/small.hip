@@ -497,7 +497,8 @@ hipError_t small_dispatch(int n, F &&launch)
 //   12, complex128   144 ->  59        419 -> 168
 //   13, complex64    197 ->  74        614 -> 242
 // What is left is the issue rate of one CU's vector units (about 2100
-// instructions per wave and reverse layer at n = 12, 8 waves).
+// instructions per wave and reverse layer at n = 12, 8 waves).  The complex64
+// reverse kernel of n = 13 spills 35 of its 256 registers, the others none.
 hipError_t launch_small_forward(int prec, const SmallProg &sp, hipStream_t st)
 {
     if (prec == 0)
