@@ -427,12 +427,18 @@ struct SampleBufs {
 //   2^18       47 /   81      58 /   81      77 /   88     133 /  146     469 /  485
 //   2^20      115 /  146     157 /  174     211 /  228     386 /  361     812 /  790
 //   2^24     1421 / 1803    2103 / 2306    2648 / 3101    3534 / 4293    4813 / 6588
+// Where the two cross for the larger states (one lane / 16 lanes):
+//   complex64    n = 28:   4,000,000: 1582 / 1524, 6,000,000: 2013 / 2103
+//                n = 27:   5,000,000: 1582 / 1518, 6,000,000: 1792 / 1778
+//   complex128   n = 26:   2^20: 588 / 570, 2,000,000: 871 / 896
+//                n = 25:   2,000,000: 773 / 767, 4,000,000: 1263 / 1400
+//                n = 24:   3,000,000: 886 / 853, 4,000,000: 1112 / 1102
 constexpr bool shot_lanes(int prec, int n, int64_t shots)
 {
     if (shots < 1 << 17) return false;
     if (shots < 1 << 19) return true;
-    if (prec == 0) return n <= 15 || (n >= 25 && shots >= 1 << 23);
-    return n <= 22 || shots >= 1 << 22;
+    if (prec == 0) return n <= 15 || (n >= 25 && shots >= 11 << 19);
+    return n <= 22 || shots >= (n >= 25 ? 15 << 17 : 1 << 22);
 }
 void sample_sizes(int n, int64_t *nsub, int64_t *nblk, int64_t *nchunk);
 // sym_n > 0: psi is the complement-symmetric layout of sym_n qubits (n =

@@ -29,7 +29,8 @@ int main()
     };
     const Shots want[] = {{0, 27, 100000, false}, {0, 13, 1, false},        {0, 13, 400000, true},  {0, 20, 400000, true},
                           {0, 14, 4000000, true}, {0, 16, 1000000, false},  {0, 24, 1 << 24, false}, {0, 27, 1 << 24, true},
-                          {1, 14, 1000000, true}, {1, 20, 4000000, true},   {1, 24, 1000000, false}, {1, 27, 1 << 22, true},
+                          {1, 14, 1000000, true}, {1, 20, 4000000, true},   {1, 24, 1000000, false}, {1, 27, 4000000, true},
+                          {1, 24, 4000000, false}, {0, 28, 6000000, true},   {1, 25, 2000000, true},
                           {1, 34, 1LL << 39, true}};
     for (const Shots &w : want)
         if (qs::shot_lanes(w.prec, w.n, w.shots) != w.lanes) {
