@@ -1770,7 +1770,8 @@ qs_status qs_batch_forward_grad(qs_batch b, const double *theta_zz, const double
             for (size_t r = gr.begin; r < end; ++r)
                 for (int fast = 1; fast >= 0; --fast)
                     if (sch.kernels[r] >> fast & 1)
-                        HIPCHK(launch_batch_round(b->prec, fast != 0, args, (int)r, b->round_items[r], b->stream),
+                        HIPCHK(launch_batch_round(b->prec, fast != 0, sch.kernels[r] == 3, args, (int)r,
+                                                  b->round_items[r], b->stream),
                                where);
             if (gr.count > 0)
                 HIPCHK(launch_batch_reduce(args.steps, (const int *)b->index.p + gr.first, gr.count, args.partials,

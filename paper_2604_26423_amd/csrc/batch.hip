@@ -25,9 +25,13 @@ namespace {
 // tried.)  The other steps (a mixer angle with |cos(theta / 2)| < 1/2) run
 // runtime-shape code, 512 threads, one workgroup per CU with a two-tile buffer.
 // A round that has steps of both kinds launches both kernels over all its
-// items, and a workgroup leaves when its item's step is the other's.  (One such
-// angle among 512 circuits used to take the general kernel for all of them:
-// 58.5 ms, now 40.4, without it 39.6.)
+// items, and a workgroup leaves when its item's step is the other's; other
+// rounds do not look, since that read ahead of the step's others cost 0.5-1% (60
+// rounds of one circuit of 14 qubits 1955 us, without it 1941).  The general
+// kernel for all 512 circuits takes 58.2 ms when one of them has such an angle,
+// this 40.4, and 39.6 without the angle; where rounds are short the second
+// launches cost more than that saves (64 circuits of 14 to 17: 688 and 718 us),
+// but a circuit's results do not depend on the others.
 template <typename V, bool FAST> constexpr int batch_tb = FAST && sizeof(V) == 16 ? 8 : 9;
 
 // Tiles [t0, t1) of one step, general stage code.
@@ -114,7 +118,7 @@ constexpr int kBatchRun = 16;
 
 template <typename V, int T, bool FAST>
 __global__ void __launch_bounds__((1 << batch_tb<V, FAST>), (!FAST ? 1 : batch_tb<V, FAST> == 9 ? 4 : 2))
-    batch_kernel(BatchArgs a, int round, int64_t nitems)
+    batch_kernel(BatchArgs a, int round, int64_t nitems, int mixed)
 {
     constexpr int NT = 1 << batch_tb<V, FAST>;
     __shared__ V lds[(FAST ? 1 : 2) << T];
@@ -126,7 +130,7 @@ __global__ void __launch_bounds__((1 << batch_tb<V, FAST>), (!FAST ? 1 : batch_t
     if (item >= nitems) return;
     const BatchItem it = a.items[item];
     const BatchStep &st = a.steps[__builtin_amdgcn_readfirstlane(it.step0) + round];
-    if ((st.fast != 0) != FAST) return;
+    if (mixed && (st.fast != 0) != FAST) return;
     const PassProg &pp = st.pp;
     const int64_t t0 = (int64_t)__builtin_amdgcn_readfirstlane(it.chunk) * st.tiles_per_chunk;
     const int64_t t1 = t0 + st.tiles_per_chunk < pp.ntiles ? t0 + st.tiles_per_chunk : pp.ntiles;
@@ -217,11 +221,12 @@ hipError_t launch_batch_tables(int prec, const BatchStep *steps, int nsteps, voi
     return hipGetLastError();
 }
 
-hipError_t launch_batch_round(int prec, bool fast, const BatchArgs &a, int round, int64_t nitems, hipStream_t st)
+hipError_t launch_batch_round(int prec, bool fast, bool mixed, const BatchArgs &a, int round, int64_t nitems,
+                              hipStream_t st)
 {
     const int64_t per = 8 * kBatchRun, grid = (nitems + per - 1) / per * per;
     return with_batch_kernel(prec, fast, [&](auto kern, int threads) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, st, a, round, nitems);
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, st, a, round, nitems, mixed ? 1 : 0);
         return hipGetLastError();
     });
 }

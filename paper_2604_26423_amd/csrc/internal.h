@@ -273,7 +273,9 @@ struct BatchArgs {
 int batch_thread_bits(int prec, bool fast);  // log2 threads its windows are planned for
 bool batch_step_fast(const BatchStep &s);  // s (pp, mode) can take that kernel
 hipError_t launch_batch_tables(int prec, const BatchStep *steps, int nsteps, void *tabs, hipStream_t st);
-hipError_t launch_batch_round(int prec, bool fast, const BatchArgs &a, int round, int64_t nitems, hipStream_t st);
+// mixed: the round has steps of both kernels, and a workgroup leaves when its step is the other's
+hipError_t launch_batch_round(int prec, bool fast, bool mixed, const BatchArgs &a, int round, int64_t nitems,
+                              hipStream_t st);
 // sums[kSlots * j + k] = slot k of step summed[j], over its items in a fixed order, j < count.
 hipError_t launch_batch_reduce(const BatchStep *steps, const int *summed, int count, const double *partials,
                                double *sums, hipStream_t st);
